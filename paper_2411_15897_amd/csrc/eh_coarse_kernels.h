@@ -1,4 +1,4 @@
-// Block-tridiagonal direct solve of the coarsest multigrid level (FP64).
+// Direct solve of the coarsest multigrid level by block elimination (FP64).
 //
 // The paper solves the coarsest grid of every block directly (Section
 // 4.4.1, "Multigrid setup").  A coarse stencil of half width w_a along axis
@@ -6,15 +6,26 @@
 // cutting the grid into groups of w_a consecutive planes (lines in 2D)
 // normal to a makes the operator block tridiagonal:
 //     L_I x_{I-1} + D_I x_I + U_I x_{I+1} = f_I.
-// Setup (block LU without pivoting between groups):
-//     S_0 = D_0,  S_I = D_I - L_I W_{I-1},  W_I = S_I^-1 U_I,
-// each S_I inverted by blocked Gauss-Jordan (32 x 32 pivot blocks, partial
-// pivoting inside each pivot block).  Stored per group, negated couplings:
-//     F_I = [S_I^-1 | -S_I^-1 L_I]   (b_I x (b_I + b_{I-1}), row-major)
-//     B_I = -W_I                     (b_I x b_{I+1})
-// Solve: forward y_I = S_I^-1 f_I - S_I^-1 L_I y_{I-1} = F_I [f_I; y_{I-1}],
-// back x_I = y_I + B_I x_{I+1}.  One launch per group and sweep, the right-
-// hand sides of a chunk sharing each matrix row read.
+// Groups are eliminated in levels.  A level removes a set of groups no two
+// of which are neighbours in the current chain; the groups left form a
+// block-tridiagonal chain again, with
+//     G_l = -L_K S_e1^-1, G_r = -U_K S_e2^-1         (K kept, e1 / e2 removed beside it)
+//     D_K += G_l U_e1 + G_r L_e2,  L_K <- G_l L_e1,  U_K <- G_r U_e2
+//     f_K += G_l f_e1 + G_r f_e2
+// and, going back,
+//     x_e = S_e^-1 f_e - S_e^-1 L_e x_l - S_e^-1 U_e x_r.
+// Removing every other group (cyclic reduction) halves the chain per level;
+// the last few groups are inverted as one dense matrix.  Stored per removed
+// group: [S_e^-1 | -S_e^-1 L_e | -S_e^-1 U_e], per kept group beside one:
+// [G_l | G_r], row-major; five matrices per group in all.  A solve is one
+// launch per level down, one for the dense rest and one per level back up.
+//
+// Why levels: a sweep over the groups one after the other needs two launches
+// per group, each a few microseconds of dependent latency however small its
+// matrix; here the launches number 2 log2(groups), and a level's groups run
+// side by side.  The price is 5 b^2 matrix entries per group instead of 3.
+// Inverses by blocked Gauss-Jordan (32 x 32 pivot blocks, partial pivoting
+// inside each pivot block).
 #pragma once
 
 #include "eh_common.h"
@@ -57,101 +68,115 @@ struct BTPart {
 // ---------------------------------------------------------------------------
 // setup
 
-// M = S_I = D_I - L_I W_{I-1} for group I, padded to bp x bp with the
-// identity.  st: FP64 stencil [nst][N]; Wp: W_{I-1} stored negated
-// (b_{I-1} x b_I, row-major), so the update adds L_I Wp.
+// Dense block (I, I + dir) of the operator, padded to bp x bp (the diagonal
+// block with the identity, the couplings with 0).  One matrix per blockIdx.z.
+struct BTBlock {
+    c128* M;
+    int I, dir;
+};
 __global__ void __launch_bounds__(256)
-k_bt_schur(BTPart pt, const c128* __restrict__ st, int I, const c128* __restrict__ Wp, c128* __restrict__ M,
-           int bp) {
+k_bt_couple_dense(BTPart pt, const c128* __restrict__ st, const BTBlock* __restrict__ blocks, int bp) {
+    const BTBlock bl = blocks[blockIdx.z];
     const int col = blockIdx.x * blockDim.x + threadIdx.x;
     const int row = blockIdx.y;
-    if (col >= bp || row >= bp) return;
-    const int b = pt.bsize(I);
-    c128* out = M + (int64_t)row * bp + col;
-    if (row >= b || col >= b) {
-        *out = mk(row == col ? 1.0 : 0.0, 0.0);
-        return;
-    }
-    int cr[3], cc[3];
-    pt.coords(I, row, cr);
-    pt.coords(I, col, cc);
-    const int64_t N = pt.d.np();
-    const int64_t pr = pt.point(cr);
-    c128 v = mk(0.0, 0.0);
-    const int ox = cc[0] - cr[0], oy = cc[1] - cr[1], oz = cc[2] - cr[2];
-    if (abs(ox) <= pt.w.w[0] && abs(oy) <= pt.w.w[1] && abs(oz) <= pt.w.w[2])
-        v = st[(int64_t)pt.offset_index(ox, oy, oz) * N + pr];
-    if (I > 0) {
-        const int bnext = b;   // columns of Wp
-        for (int dz = -pt.w.w[2]; dz <= pt.w.w[2]; ++dz)
-        for (int dy = -pt.w.w[1]; dy <= pt.w.w[1]; ++dy)
-        for (int dx = -pt.w.w[0]; dx <= pt.w.w[0]; ++dx) {
-            int cn[3] = {cr[0] + dx, cr[1] + dy, cr[2] + dz};
-            if (!pt.inside(cn) || pt.group(cn) != I - 1) continue;
-            const c128 l = st[(int64_t)pt.offset_index(dx, dy, dz) * N + pr];
-            v = v + l * Wp[(int64_t)pt.local(cn) * bnext + col];
-        }
+    if (col >= bp) return;
+    c128* out = bl.M + (int64_t)row * bp + col;
+    c128 v = mk(bl.dir == 0 && row == col ? 1.0 : 0.0, 0.0);
+    if (row < pt.bsize(bl.I) && col < pt.bsize(bl.I + bl.dir)) {
+        int cr[3], cc[3];
+        pt.coords(bl.I, row, cr);
+        pt.coords(bl.I + bl.dir, col, cc);
+        const int ox = cc[0] - cr[0], oy = cc[1] - cr[1], oz = cc[2] - cr[2];
+        v = mk(0.0, 0.0);
+        if (abs(ox) <= pt.w.w[0] && abs(oy) <= pt.w.w[1] && abs(oz) <= pt.w.w[2])
+            v = st[(int64_t)pt.offset_index(ox, oy, oz) * pt.d.np() + pt.point(cr)];
     }
     *out = v;
 }
 
 constexpr int GJB = 32;   // pivot block of the blocked Gauss-Jordan inversion
 
+// Matrices inverted side by side, one per blockIdx.z: bp x bp, bp a multiple
+// of GJB (padded with the identity).  Matrices of a launch may differ in
+// bp; those with fewer pivot blocks drop out.
+struct GJMat {
+    c128* M;
+    int bp;
+};
+
 // Pivot block K of M (bp x bp, in place): A_KK <- A_KK^-1 by Gauss-Jordan
-// with partial pivoting on [A_KK | I] in LDS.  A zero pivot sets *bad.
+// with partial pivoting on [A_KK | I].  A zero pivot sets *bad.
+//
+// The 32 steps are a serial chain of one workgroup, so each keeps its
+// matrix in registers: thread t owns column t % 64 and the rows t / 64 + 4 q
+// and only the pivot column and two rows pass through LDS, in two buffers,
+// two barriers per step.  Every wavefront finds the pivot by itself.
 __global__ void __launch_bounds__(256)
-k_gj_diag(c128* __restrict__ M, int bp, int K, int* __restrict__ bad) {
-    __shared__ c128 A[GJB][2 * GJB];
-    __shared__ c128 mult[GJB];
-    __shared__ int piv;
-    const int tid = threadIdx.x;
-    const int k0 = K * GJB;
-    for (int e = tid; e < GJB * 2 * GJB; e += 256) {
-        const int i = e / (2 * GJB), j = e % (2 * GJB);
-        A[i][j] = j < GJB ? M[(int64_t)(k0 + i) * bp + k0 + j] : mk(j - GJB == i ? 1.0 : 0.0, 0.0);
+k_gj_diag(const GJMat* __restrict__ mats, int K, int* __restrict__ bad) {
+    __shared__ c128 col[2][GJB], rowk[2][2 * GJB], rowp[2][2 * GJB];
+    const GJMat gm = mats[blockIdx.z];
+    if (K * GJB >= gm.bp) return;
+    c128* M = gm.M + (int64_t)K * GJB * gm.bp + K * GJB;
+    const int j = threadIdx.x & 63, r0 = threadIdx.x >> 6, lane = j;
+    c128 A[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int i = r0 + 4 * q;
+        A[q] = j < GJB ? M[(int64_t)i * gm.bp + j] : mk(j - GJB == i ? 1.0 : 0.0, 0.0);
     }
-    __syncthreads();
     for (int k = 0; k < GJB; ++k) {
-        if (tid == 0) {
-            int p = k;
-            double best = cabs2(A[k][k]);
-            for (int i = k + 1; i < GJB; ++i) {
-                const double a = cabs2(A[i][k]);
-                if (a > best) { best = a; p = i; }
+        const int s = k & 1;
+        if (j == k) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) col[s][r0 + 4 * q] = A[q];
+        }
+        __syncthreads();
+        // pivot row: the largest |column entry| from row k on, the lowest on ties
+        double best = -1.0;
+        int p = k;
+        if (lane < GJB && lane >= k) { best = cabs2(col[s][lane]); p = lane; }
+        for (int off = 16; off > 0; off >>= 1) {
+            const double ob = __shfl_xor(best, off, 64);
+            const int op = __shfl_xor(p, off, 64);
+            if (ob > best || (ob == best && op < p)) { best = ob; p = op; }
+        }
+        best = __shfl(best, 0, 64);
+        p = __shfl(p, 0, 64);
+        if (!(best > 0.0)) {             // uniform: every wavefront found the same pivot
+            *bad = 1;
+            return;
+        }
+        if ((p & 3) == r0 || (k & 3) == r0) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (r0 + 4 * q == p) rowp[s][j] = A[q];
+                if (r0 + 4 * q == k) rowk[s][j] = A[q];
             }
-            if (!(best > 0.0)) { *bad = 1; p = -1; }
-            piv = p;
         }
         __syncthreads();
-        const int p = piv;
-        if (p < 0) return;   // uniform: every thread read the same flag
-        if (p != k && tid < 2 * GJB) {
-            const c128 t = A[k][tid];
-            A[k][tid] = A[p][tid];
-            A[p][tid] = t;
+        const c128 pr = cdiv(mk(1.0, 0.0), col[s][p]) * rowp[s][j];   // the new row k
+        const c128 rk = rowk[s][j], ck = col[s][k];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = r0 + 4 * q;
+            if (i == k) A[q] = pr;
+            else if (i == p) A[q] = rk - ck * pr;
+            else A[q] = A[q] - col[s][i] * pr;
         }
-        __syncthreads();
-        const c128 inv = cdiv(mk(1.0, 0.0), A[k][k]);
-        __syncthreads();
-        if (tid < 2 * GJB) A[k][tid] = inv * A[k][tid];
-        if (tid < GJB) mult[tid] = tid == k ? mk(0.0, 0.0) : A[tid][k];
-        __syncthreads();
-        for (int e = tid; e < GJB * 2 * GJB; e += 256) {
-            const int i = e / (2 * GJB), j = e % (2 * GJB);
-            if (i != k) A[i][j] = A[i][j] - mult[i] * A[k][j];
-        }
-        __syncthreads();
     }
-    for (int e = tid; e < GJB * GJB; e += 256) {
-        const int i = e / GJB, j = e % GJB;
-        M[(int64_t)(k0 + i) * bp + k0 + j] = A[i][GJB + j];
+    if (j >= GJB) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) M[(int64_t)(r0 + 4 * q) * gm.bp + j - GJB] = A[q];
     }
 }
 
 // Row panel of pivot block K: A_Kj <- A_KK^-1 A_Kj for every column j
 // outside the block (64 columns per workgroup).
 __global__ void __launch_bounds__(256)
-k_gj_rowpanel(c128* __restrict__ M, int bp, int K) {
+k_gj_rowpanel(const GJMat* __restrict__ mats, int K) {
+    c128* __restrict__ M = mats[blockIdx.z].M;
+    const int bp = mats[blockIdx.z].bp;
+    if (K * GJB >= bp || (int)blockIdx.x * 64 >= bp) return;
     __shared__ c128 Dv[GJB][GJB];
     __shared__ c128 Pn[GJB][64];
     const int tid = threadIdx.x;
@@ -176,7 +201,10 @@ k_gj_rowpanel(c128* __restrict__ M, int bp, int K) {
 // already multiplied by A_KK^-1).  64 x 64 output tile per workgroup, each
 // thread 4 x 4 entries 16 apart.
 __global__ void __launch_bounds__(256)
-k_gj_update(c128* __restrict__ M, int bp, int K) {
+k_gj_update(const GJMat* __restrict__ mats, int K) {
+    c128* __restrict__ M = mats[blockIdx.z].M;
+    const int bp = mats[blockIdx.z].bp;
+    if (K * GJB >= bp || (int)blockIdx.x * 64 >= bp || (int)blockIdx.y * 64 >= bp) return;
     __shared__ c128 Ac[64][GJB + 1];
     __shared__ c128 Br[GJB][64];
     const int tid = threadIdx.x;
@@ -227,7 +255,10 @@ k_gj_update(c128* __restrict__ M, int bp, int K) {
 // Column panel of pivot block K: A_iK <- -A_iK A_KK^-1 for every row i
 // outside the block (64 rows per workgroup).
 __global__ void __launch_bounds__(256)
-k_gj_colpanel(c128* __restrict__ M, int bp, int K) {
+k_gj_colpanel(const GJMat* __restrict__ mats, int K) {
+    c128* __restrict__ M = mats[blockIdx.z].M;
+    const int bp = mats[blockIdx.z].bp;
+    if (K * GJB >= bp || (int)blockIdx.x * 64 >= bp) return;
     __shared__ c128 Dv[GJB][GJB];
     __shared__ c128 Pn[64][GJB + 1];
     const int tid = threadIdx.x;
@@ -248,42 +279,114 @@ k_gj_colpanel(c128* __restrict__ M, int bp, int K) {
     }
 }
 
-// Copy S_I^-1 (the leading b x b of M, row stride bp) into the first b
-// columns of F_I (row stride ld).
+// C = sgn * A B (+ C with acc), bp x bp matrices, one product per
+// blockIdx.z: the dense products of a level of the elimination.  A 64 x 64
+// tile per workgroup, 16 columns of A and rows of B staged in LDS per step,
+// on the FP64 matrix unit (v_mfma_f64_16x16x4: lane l holds A[l % 16][l / 16]
+// and B[l / 16][l % 16], result register i holds D[l / 16 + 4 i][l % 16]); a
+// complex product is four real ones on split re / im planes.  The planes'
+// pitch keeps a wavefront's four rows (or its 16 rows) on different banks.
+struct GJProd {
+    const c128* A;
+    const c128* B;
+    c128* C;
+    double sgn;
+    int acc;
+};
+typedef double gj_f64x4 __attribute__((ext_vector_type(4)));
+constexpr int GJP_KC = 16;
 __global__ void __launch_bounds__(256)
-k_bt_store_inv(const c128* __restrict__ M, int bp, int b, c128* __restrict__ F, int ld) {
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    const int row = blockIdx.y;
-    if (col >= b || row >= b) return;
-    F[(int64_t)row * ld + col] = M[(int64_t)row * bp + col];
+k_gj_product(const GJProd* __restrict__ prods, int bp) {
+    __shared__ double Ar[64][GJP_KC + 1], Ai[64][GJP_KC + 1];
+    __shared__ double Br[GJP_KC][64 + 4], Bi[GJP_KC][64 + 4];
+    const GJProd pd = prods[blockIdx.z];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    const int lr = lane & 15, lk = lane >> 4;
+    gj_f64x4 cr[2][2], ci[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            cr[a][b] = gj_f64x4{0.0, 0.0, 0.0, 0.0};
+            ci[a][b] = gj_f64x4{0.0, 0.0, 0.0, 0.0};
+        }
+    for (int k0 = 0; k0 < bp; k0 += GJP_KC) {   // bp is a multiple of 32
+        c128 va[4], vb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = tid + 256 * u;
+            const int ia = i0 + e / GJP_KC, jb = j0 + e % 64;
+            va[u] = ia < bp ? pd.A[(int64_t)ia * bp + k0 + e % GJP_KC] : mk(0.0, 0.0);
+            vb[u] = jb < bp ? pd.B[(int64_t)(k0 + e / 64) * bp + jb] : mk(0.0, 0.0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = tid + 256 * u;
+            Ar[e / GJP_KC][e % GJP_KC] = va[u].re;
+            Ai[e / GJP_KC][e % GJP_KC] = va[u].im;
+            Br[e / 64][e % 64] = vb[u].re;
+            Bi[e / 64][e % 64] = vb[u].im;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < GJP_KC; kk += 4) {
+            double xr[2], xi[2], yr[2], yi[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                xr[a] = Ar[wi + 16 * a + lr][kk + lk];
+                xi[a] = Ai[wi + 16 * a + lr][kk + lk];
+                yr[a] = Br[kk + lk][wj + 16 * a + lr];
+                yi[a] = Bi[kk + lk][wj + 16 * a + lr];
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    cr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[a], yr[b], cr[a][b], 0, 0, 0);
+                    ci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[a], yi[b], ci[a][b], 0, 0, 0);
+                    cr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xi[a], yi[b], cr[a][b], 0, 0, 0);
+                    ci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[a], yr[b], ci[a][b], 0, 0, 0);
+                }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + wi + 16 * a + lk + 4 * q, j = j0 + wj + 16 * b + lr;
+                if (i >= bp || j >= bp) continue;
+                c128* p = pd.C + (int64_t)i * bp + j;
+                const c128 v = mk(pd.sgn * cr[a][b][q], pd.sgn * ci[a][b][q]);
+                *p = pd.acc ? *p + v : v;
+            }
 }
 
-// out[i][j] = -sum_r S_I^-1[i][r] X[r][j] for j in group J = I + dir, X =
-// L_I (dir -1) or U_I (dir +1): X[r][j] is the coefficient of point j in
-// row r, so r = j - o for each stencil offset o that lands in group I.
-// M holds S_I^-1 (row stride bp); out has row stride ld.
+// Copy the leading rows x cols of src (row stride lds) to dst (row stride
+// ldd); one copy per blockIdx.z.
+struct BTCopy {
+    const c128* src;
+    c128* dst;
+    int rows, cols, lds, ldd;
+};
 __global__ void __launch_bounds__(256)
-k_bt_couple(BTPart pt, const c128* __restrict__ st, int I, int dir, const c128* __restrict__ M, int bp,
-            c128* __restrict__ out, int ld) {
-    const int J = I + dir;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    const int bJ = pt.bsize(J), bI = pt.bsize(I);
-    if (j >= bJ || i >= bI) return;
-    int cj[3];
-    pt.coords(J, j, cj);
-    const int64_t N = pt.d.np();
-    const c128* Si = M + (int64_t)i * bp;
-    c128 acc = mk(0.0, 0.0);
-    for (int oz = -pt.w.w[2]; oz <= pt.w.w[2]; ++oz)
-    for (int oy = -pt.w.w[1]; oy <= pt.w.w[1]; ++oy)
-    for (int ox = -pt.w.w[0]; ox <= pt.w.w[0]; ++ox) {
-        int cr[3] = {cj[0] - ox, cj[1] - oy, cj[2] - oz};
-        if (!pt.inside(cr) || pt.group(cr) != I) continue;
-        const int64_t pr = pt.point(cr);
-        acc = acc + Si[pt.local(cr)] * st[(int64_t)pt.offset_index(ox, oy, oz) * N + pr];
-    }
-    out[(int64_t)i * ld + j] = mk(-acc.re, -acc.im);
+k_bt_store_inv(const BTCopy* __restrict__ copies) {
+    const BTCopy cp = copies[blockIdx.z];
+    const int col = blockIdx.x * blockDim.x + threadIdx.x;
+    const int row = blockIdx.y;
+    if (col < cp.cols && row < cp.rows) cp.dst[(int64_t)row * cp.ldd + col] = cp.src[(int64_t)row * cp.lds + col];
+}
+
+// Identity, the start of a padded dense matrix.
+__global__ void __launch_bounds__(256)
+k_gj_identity(c128* __restrict__ M, int bp) {
+    const int col = blockIdx.x * blockDim.x + threadIdx.x;
+    const int row = blockIdx.y;
+    if (col < bp) M[(int64_t)row * bp + col] = mk(row == col ? 1.0 : 0.0, 0.0);
 }
 
 // y = X x with an FP64 stencil (the setup's accuracy check).
@@ -312,47 +415,88 @@ k_stencil_f64(Dims d, Widths w, const c128* __restrict__ st, const c128* __restr
 // solve
 
 constexpr int BT_MAXS = 4;
-
-// Block-tridiagonal solve of X x = f over the groups I of a partition,
-// with S_I the Schur complements, L_I / U_I the couplings to groups I - 1 /
-// I + 1, F_I = [S_I^-1 | -S_I^-1 L_I] and B_I = -S_I^-1 U_I:
-//   forward  y_I = S_I^-1 f_I + (-S_I^-1 L_I) y_{I-1}
-//   back     x_I = y_I + B_I x_{I+1}.
-// The first term of the forward sweep does not depend on the sweep, so one
-// launch computes it for every group (k_bt_fpart); the sweeps then add, one
-// group step per launch, a matrix-vector product with the neighbour
-// group's vector in place (k_bt_chain).  Products and sums in FP64.
-
-// Both are matrix-vector products whose vector a group of rows shares: one
-// row per wavefront, four per workgroup.  Per chunk of columns each
-// wavefront first issues all loads of its row's entries, the workgroup
-// stages the vector's chunk (every right-hand side, FP64) in LDS, and each
-// lane sums its columns in a fixed order; a butterfly over the wavefront's
-// lanes completes the row.  The arithmetic of a right-hand side does not
-// depend on the others in the chunk.
-// columns per lane and chunk (the staged chunk holds 40 KB at most)
-template <int RB>
-constexpr int bt_na() { return RB >= 8 ? 5 : 10; }
 constexpr int BT_RW = 4;                // rows per workgroup, one per wavefront
 
-template <int RB>
-__device__ __forceinline__ void bt_wave_sum(double (&ar)[RB], double (&ai)[RB]) {
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        for (int off = 32; off > 0; off >>= 1) {
-            ar[r] += __shfl_xor(ar[r], off, 64);
-            ai[r] += __shfl_xor(ai[r], off, 64);
-        }
-}
+// The rows of one group in one launch: a rows x (n[0] + n[1] + n[2]) matrix,
+// row-major at mats + mat, times entries of up to three vectors.  Vectors
+// are in elimination order; off and out index them.
+struct BTTask {
+    int64_t mat;
+    int rows;
+    int n[3], off[3];
+    int out;
+};
 
-// Accumulate this wavefront's row A (nc entries; null: no row) times the
-// staged vectors, chunk by chunk; stage(c0, w, xs) writes columns c0 ..
-// c0 + w - 1 of every right-hand side into xs[r * CW + cc], CW = 64 NA.
-template <int RB, class Stage>
-__device__ __forceinline__ void bt_rows(const c128* __restrict__ A, int nc, c128* xs, Stage stage,
-                                        double (&ar)[RB], double (&ai)[RB]) {
+// One launch over up to BT_MAXS blocks.  Per slot: its tasks in this launch,
+// the permutation from elimination order to the level's points, the right-
+// hand side (the level's f on the first level of the elimination, y after),
+// the eliminated right-hand side y and the solution x (FP64, elimination
+// order, N entries per right-hand side), and the level's vector e.
+template <class T>
+struct BTRun {
+    int ns;
+    int nrhs;
+    const BTTask* tasks[BT_MAXS];
+    int ntasks[BT_MAXS];
+    int first[BT_MAXS];
+    const c128* mats[BT_MAXS];
+    const int* perm[BT_MAXS];
+    int N[BT_MAXS];
+    c128* y[BT_MAXS];
+    c128* x[BT_MAXS];
+    const cplx<T>* f[BT_MAXS];
+    int64_t vf[BT_MAXS];
+    cplx<T>* e[BT_MAXS];
+    int64_t ve[BT_MAXS];
+};
+
+// Down (BACK false): y_K = f_K + G_l f_e1 + G_r f_e2 (a kept group without
+// removed neighbours has no columns: y_K = f_K).  Up (BACK true): x_e =
+// S_e^-1 f_e - S_e^-1 L_e x_l - S_e^-1 U_e x_r, written to x and, in the
+// level's layout and precision, to e; also the dense rest (one vector).
+//
+// Bound by the matrix entries, each read once per chunk of right-hand sides:
+// one row per wavefront, four per workgroup, whose vector chunk (every
+// right-hand side, FP64) is staged in LDS while the row's loads are in
+// flight.  Each lane sums its columns in a fixed order, a butterfly adds the
+// lanes; a right-hand side's arithmetic does not depend on the others.
+// Columns per lane and chunk: the staged chunk holds 40 KB at most.
+// Grid (row blocks of the largest group, tasks x slots (slot fastest),
+// chunks of RB right-hand sides).
+template <int RB>
+constexpr int bt_na() { return RB >= 8 ? 5 : 10; }
+
+template <class T, int RB, bool BACK>
+__global__ void __launch_bounds__(256)
+k_bt_rows(BTRun<T> a) {
     constexpr int NA = bt_na<RB>(), CW = 64 * NA;
-    const int lane = threadIdx.x & 63;
+    __shared__ c128 xs[RB * CW];
+    const int s = blockIdx.y % a.ns, t = blockIdx.y / a.ns;
+    if (t >= a.ntasks[s]) return;
+    const BTTask tk = a.tasks[s][t];
+    const int row0 = blockIdx.x * BT_RW;
+    if (row0 >= tk.rows) return;
+    const int row = row0 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r0 = blockIdx.z * RB;
+    const int cnt = min(RB, a.nrhs - r0);
+    const int N = a.N[s];
+    const bool first = a.first[s] != 0;
+    const int* __restrict__ perm = a.perm[s];
+    const cplx<T>* f = a.f[s] + (int64_t)r0 * a.vf[s];
+    c128* y = a.y[s] + (int64_t)r0 * N;
+    c128* x = a.x[s] + (int64_t)r0 * N;
+    const int64_t vf = a.vf[s];
+    const int n0 = tk.n[0], n01 = n0 + tk.n[1], nc = n01 + tk.n[2];
+    const c128* A = row < tk.rows ? a.mats[s] + tk.mat + (int64_t)row * nc : nullptr;
+    // this lane's result: right-hand side r0 + lane of the wavefront's row
+    const bool wr = row < tk.rows && lane < cnt;
+    const int po = (wr && (BACK || first)) ? perm[tk.out + row] : 0;
+    c128 add = mk(0.0, 0.0);
+    if (!BACK && wr) {
+        if (first) add = ccast<double>(f[lane * vf + po]);
+        else add = y[(int64_t)lane * N + tk.out + row];
+    }
+    double ar[RB], ai[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) { ar[r] = 0.0; ai[r] = 0.0; }
     for (int c0 = 0; c0 < nc; c0 += CW) {
@@ -363,7 +507,24 @@ __device__ __forceinline__ void bt_rows(const c128* __restrict__ A, int nc, c128
             const int c = lane + 64 * u;
             mv[u] = (A && c < w) ? A[c0 + c] : mk(0.0, 0.0);
         }
-        stage(c0, w, xs);
+        if (c0 > 0) __syncthreads();          // the previous chunk is consumed
+        for (int cc = threadIdx.x; cc < w; cc += 256) {
+            const int c = c0 + cc;
+            const int q = c < n0 ? tk.off[0] + c : (c < n01 ? tk.off[1] + c - n0 : tk.off[2] + c - n01);
+            // down: every vector is the right-hand side; up: the first one
+            // is, the neighbours' entries come from the solution
+            const bool rhs = !BACK || c < n0;
+            if (rhs && first) {
+                const int pq = perm[q];
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    xs[r * CW + cc] = r < cnt ? ccast<double>(f[r * vf + pq]) : mk(0.0, 0.0);
+            } else {
+                const c128* v = rhs ? y : x;
+#pragma unroll
+                for (int r = 0; r < RB; ++r) xs[r * CW + cc] = r < cnt ? v[(int64_t)r * N + q] : mk(0.0, 0.0);
+            }
+        }
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
@@ -371,145 +532,32 @@ __device__ __forceinline__ void bt_rows(const c128* __restrict__ A, int nc, c128
             if (c < w) {
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
-                    const c128 x = xs[r * CW + c];
-                    ar[r] += mv[u].re * x.re - mv[u].im * x.im;
-                    ai[r] += mv[u].re * x.im + mv[u].im * x.re;
+                    const c128 v = xs[r * CW + c];
+                    ar[r] = fmat(-mv[u].im, v.im, fmat(mv[u].re, v.re, ar[r]));
+                    ai[r] = fmat(mv[u].im, v.re, fmat(mv[u].re, v.im, ai[r]));
                 }
             }
         }
-        if (c0 + CW < nc) __syncthreads();   // the next chunk reuses xs
     }
-    bt_wave_sum<RB>(ar, ai);
-}
-
-// Every group's S_I^-1 f_I.  Per slot: N points, groups of b0 rows (the
-// last may be shorter), nb groups, F_I at mats + offF[I] with rows of b_I +
-// b_{I-1} entries, the point permutation in group order, the FP64 work
-// vector y (stride N per right-hand side) and f in the level's layout.
-template <class T>
-struct BTAll {
-    int ns;
-    int nrhs;
-    int N[BT_MAXS], b0[BT_MAXS], nb[BT_MAXS];
-    const c128* mats[BT_MAXS];
-    const int64_t* offF[BT_MAXS];   // device array, one entry per group
-    const int* perm[BT_MAXS];
-    c128* y[BT_MAXS];
-    const cplx<T>* f[BT_MAXS];
-    int64_t vf[BT_MAXS];
-};
-
-// Grid (row blocks of BT_RW of the largest group, groups x slots (slot
-// fastest), chunks of RB right-hand sides).
-template <class T, int RB>
-__global__ void __launch_bounds__(256)
-k_bt_fpart(BTAll<T> a) {
-    constexpr int CW = 64 * bt_na<RB>();
-    __shared__ c128 xs[RB * CW];
-    const int s = blockIdx.y % a.ns, I = blockIdx.y / a.ns;
-    if (I >= a.nb[s]) return;
-    const int N = a.N[s], b0 = a.b0[s];
-    const int b = min(b0, N - I * b0), bprev = I > 0 ? b0 : 0;
-    const int row0 = blockIdx.x * BT_RW;
-    if (row0 >= b) return;
-    const int row = row0 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const c128* A = row < b ? a.mats[s] + a.offF[s][I] + (int64_t)row * (b + bprev) : nullptr;
-    const int* perm = a.perm[s] + (int64_t)I * b0;
-    const int r0 = blockIdx.z * RB;
-    const int cnt = min(RB, a.nrhs - r0);
-    const int64_t vf = a.vf[s];
-    const cplx<T>* f = a.f[s] + (int64_t)r0 * vf;
-    auto stage = [&](int c0, int w, c128* x) {
-        constexpr int K = (CW + 255) / 256;
-        int pc[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int cc = threadIdx.x + 256 * k;
-            pc[k] = cc < w ? perm[c0 + cc] : 0;
+    for (int r = 0; r < RB; ++r)
+        for (int off = 32; off > 0; off >>= 1) {
+            ar[r] += __shfl_xor(ar[r], off, 64);
+            ai[r] += __shfl_xor(ai[r], off, 64);
         }
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int cc = threadIdx.x + 256 * k;
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                if (cc < w) {
-                    const cplx<T> v = r < cnt ? f[r * vf + pc[k]] : czero<T>();
-                    x[r * CW + cc] = mk(double(v.re), double(v.im));
-                }
-        }
-    };
-    double ar[RB], ai[RB];
-    bt_rows<RB>(A, b, xs, stage, ar, ai);
-    if (row < b) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            if (lane == r && r < cnt) a.y[s][(int64_t)(r0 + r) * N + (int64_t)I * b0 + row] = mk(ar[r], ai[r]);
-    }
-}
-
-// One group step of a sweep for up to BT_MAXS blocks.  Per slot: the rows b
-// of the group's matrix (the coupling columns -S_I^-1 L_I of F_I, or B_I),
-// its row stride lda, the columns bo (the neighbour group's size), the
-// group's entries of the point permutation, the work vector at this group
-// (y) and at the neighbour group (yo), stride ldy per right-hand side, and
-// (back sweep) the level's vector e in the multigrid precision.
-template <class T>
-struct BTStep {
-    int ns;
-    int nrhs;
-    const c128* mat[BT_MAXS];
-    int b[BT_MAXS], bo[BT_MAXS], lda[BT_MAXS];
-    const int* perm[BT_MAXS];
-    c128* y[BT_MAXS];
-    const c128* yo[BT_MAXS];
-    int64_t ldy[BT_MAXS];
-    cplx<T>* e[BT_MAXS];
-    int64_t ve[BT_MAXS];
-};
-
-// y_I += M yo, in place; the back sweep also writes e = x_I in the level's
-// layout and precision.  Grid (row blocks of BT_RW, slots, chunks of RB
-// right-hand sides).
-template <class T, int RB, bool BACK>
-__global__ void __launch_bounds__(256)
-k_bt_chain(BTStep<T> a) {
-    constexpr int CW = 64 * bt_na<RB>();
-    __shared__ c128 xs[RB * CW];
-    const int s = blockIdx.y;
-    if (s >= a.ns) return;
-    const int b = a.b[s], bo = a.bo[s];
-    const int row0 = blockIdx.x * BT_RW;
-    if (row0 >= b) return;
-    const int row = row0 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int r0 = blockIdx.z * RB;
-    const int cnt = min(RB, a.nrhs - r0);
-    const int64_t ldy = a.ldy[s];
-    // this lane's entry of y (lane r: right-hand side r0 + r), loaded early
-    const bool wr = row < b && lane < cnt;
-    c128* yp = a.y[s] + (wr ? (int64_t)(r0 + lane) * ldy + row : 0);
-    const c128 yv = wr ? *yp : mk(0.0, 0.0);
-    const c128* A = row < b ? a.mat[s] + (int64_t)row * a.lda[s] : nullptr;
-    const c128* xo = a.yo[s] + (int64_t)r0 * ldy;
-    auto stage = [&](int c0, int w, c128* x) {
-        constexpr int K = (CW + 255) / 256;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int cc = threadIdx.x + 256 * k;
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                if (cc < w) x[r * CW + cc] = r < cnt ? xo[r * ldy + c0 + cc] : mk(0.0, 0.0);
-        }
-    };
-    double ar[RB], ai[RB];
-    bt_rows<RB>(A, bo, xs, stage, ar, ai);
     if (!wr) return;
     double sr = 0.0, si = 0.0;
 #pragma unroll
     for (int r = 0; r < RB; ++r)
         if (lane == r) { sr = ar[r]; si = ai[r]; }
-    const c128 x = mk(yv.re + sr, yv.im + si);
-    *yp = x;
-    if (BACK) a.e[s][(int64_t)(r0 + lane) * a.ve[s] + a.perm[s][row]] = mk<T>(T(x.re), T(x.im));
+    const c128 v = mk(add.re + sr, add.im + si);
+    const int64_t o = (int64_t)lane * N + tk.out + row;
+    if (BACK) {
+        x[o] = v;
+        a.e[s][(int64_t)(r0 + lane) * a.ve[s] + po] = mk<T>(T(v.re), T(v.im));
+    } else {
+        y[o] = v;
+    }
 }
 
 }  // namespace eh

@@ -81,18 +81,22 @@ k_galerkin(Dims df, Widths wf, const c128* __restrict__ cf, Dims dc, Widths wc, 
     for (int t = 0; t < ncs; ++t) cc[t * npc + q] = acc[t];
 }
 
-// Dense augmented matrix [A | I] (N x 2N, row-major) from a stencil.
-__global__ void k_dense_from_stencil(Dims d, Widths w, const c128* __restrict__ st,
-                                     c128* __restrict__ M) {
+// Dense matrix of a stencil, row-major with row stride ld: with augment
+// [A | I] (N x 2N, cleared here), else A into a matrix that holds the
+// identity (its own diagonal is overwritten, the padding stays).
+__global__ void k_dense_from_stencil(Dims d, Widths w, const c128* __restrict__ st, c128* __restrict__ M, int64_t ld,
+                                     int augment) {
     const int64_t N = d.np();
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N) return;
     const int i = (int)(q % d.g[0]);
     const int j = (int)((q / d.g[0]) % d.g[1]);
     const int k = (int)(q / ((int64_t)d.g[0] * d.g[1]));
-    c128* row = M + q * 2 * N;
-    for (int64_t c = 0; c < 2 * N; ++c) row[c] = mk(0.0, 0.0);
-    row[N + q] = mk(1.0, 0.0);
+    c128* row = M + q * ld;
+    if (augment) {
+        for (int64_t c = 0; c < 2 * N; ++c) row[c] = mk(0.0, 0.0);
+        row[N + q] = mk(1.0, 0.0);
+    }
     const int NX = 2 * w.w[0] + 1, NY = 2 * w.w[1] + 1;
     for (int oz = -w.w[2]; oz <= w.w[2]; ++oz)
     for (int oy = -w.w[1]; oy <= w.w[1]; ++oy)

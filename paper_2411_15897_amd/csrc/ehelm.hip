@@ -103,16 +103,25 @@ struct Level {
     int nstored() const { return half ? (w.nst() + 1) / 2 : w.nst(); }
 };
 
-// Block-tridiagonal factors of a coarsest level (eh_coarse_kernels.h).
+// Factors of a coarsest level eliminated group by group in levels
+// (eh_coarse_kernels.h).
 struct BTData {
-    BTPart pt{};
-    std::vector<int64_t> goff;   // first entry of each group in the group order (nb + 1)
-    std::vector<int64_t> offF;   // F_I = [S_I^-1 | -S_I^-1 L_I] in mats
-    std::vector<int64_t> offB;   // B_I = -S_I^-1 U_I in mats
-    int64_t* offF_d = nullptr;   // offF on the device
+    // one level of the elimination: its tasks down (kept groups) and back up
+    // (removed groups) in `tasks`, their largest row count, the entries of
+    // their matrices and the vector entries read and written
+    struct Lev {
+        int f0 = 0, nf = 0, fmax = 0;
+        int b0 = 0, nb = 0, bmax = 0;
+        double fmat = 0, fvec = 0, bmat = 0, bvec = 0;
+    };
+    int64_t N = 0;
+    std::vector<Lev> lev;
+    int tail = 0;                // the dense rest's task
+    int ntail = 0;               // its rows
+    BTTask* tasks = nullptr;     // on the device
     c128* mats = nullptr;
-    int* perm = nullptr;         // group order -> point index (N)
-    c128* y = nullptr;           // FP64 work vector, nrhs_cap * N
+    int* perm = nullptr;         // elimination order -> point index (N)
+    c128* y = nullptr;           // FP64 work vectors (right-hand side, solution), 2 * nrhs_cap * N
 };
 
 struct Block {
@@ -528,15 +537,116 @@ std::vector<c128> fine_stencil(const eh_ctx* c, const Block& B, const std::vecto
     return st;
 }
 
-// Coarsest solve by an explicit dense inverse: Gauss-Jordan with partial
-// pivoting (FP64) on [X | I], applied later as a matrix-vector product.
-void build_dense(eh_ctx* c, Block& B, c128* prev, const Widths& wprev, const Dims& dc) {
+// Scratch of the coarsest factorisation: n x n FP64 matrices handed out and
+// taken back, and a buffer for the descriptors of a batched launch.  (The
+// set-up runs on the null stream; a copy of new descriptors waits for the
+// launches that read the old ones.)
+struct GJScratch {
+    eh_ctx* c;
+    size_t elems;
+    std::vector<c128*> all, free_;
+    void* desc = nullptr;
+    size_t desc_cap = 0;
+    int* bad = nullptr;
+    GJScratch(eh_ctx* c_, size_t elems_) : c(c_), elems(elems_) {
+        bad = c->alloc<int>(1);
+        HIPCHK(hipMemset(bad, 0, sizeof(int)));
+    }
+    ~GJScratch() {
+        for (c128* p : all) c->release(p);
+        c->release(desc);
+        c->release(bad);
+    }
+    c128* get() {
+        if (free_.empty()) {
+            all.push_back(c->alloc<c128>(elems));
+            free_.push_back(all.back());
+        }
+        c128* p = free_.back();
+        free_.pop_back();
+        return p;
+    }
+    void put(c128*& p) {
+        if (p) free_.push_back(p);
+        p = nullptr;
+    }
+    template <class D>
+    const D* upload(const std::vector<D>& v) {
+        const size_t bytes = v.size() * sizeof(D);
+        if (bytes > desc_cap) {
+            c->release(desc);
+            desc = nullptr;
+            desc = c->alloc<char>(2 * bytes);
+            desc_cap = 2 * bytes;
+        }
+        HIPCHK(hipMemcpy(desc, v.data(), bytes, hipMemcpyHostToDevice));
+        return (const D*)desc;
+    }
+    bool zero_pivot() {
+        int h = 0;
+        HIPCHK(hipMemcpy(&h, bad, sizeof(int), hipMemcpyDeviceToHost));
+        return h != 0;
+    }
+};
+
+// In-place inverses of several padded matrices, side by side.
+void gj_invert(GJScratch& g, const std::vector<GJMat>& mats) {
+    if (mats.empty()) return;
+    const GJMat* dm = g.upload(mats);
+    int bp = 0;
+    for (const GJMat& m : mats) bp = std::max(bp, m.bp);
+    const unsigned t64 = (unsigned)((bp + 63) / 64), nz = (unsigned)mats.size();
+    for (int K = 0; K < bp / GJB; ++K) {
+        hipLaunchKernelGGL(k_gj_diag, dim3(1, 1, nz), dim3(256), 0, 0, dm, K, g.bad);
+        hipLaunchKernelGGL(k_gj_rowpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
+        hipLaunchKernelGGL(k_gj_update, dim3(t64, t64, nz), dim3(256), 0, 0, dm, K);
+        hipLaunchKernelGGL(k_gj_colpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
+    }
+    HIPCHK(hipGetLastError());
+}
+
+inline int pad_gj(int64_t b) { return (int)((b + GJB - 1) / GJB * GJB); }
+
+// Relative residual of X x = f for a fixed f, x from `solve(df, dx)` (FP64
+// device vectors of the level), recomputed in FP64.
+template <class F>
+double coarse_residual(eh_ctx* c, const c128* st, const Widths& w, const Dims& d, F solve) {
+    const int64_t N = d.np();
+    std::vector<c128> hf((size_t)N), hr((size_t)N);
+    for (int64_t q = 0; q < N; ++q) hf[(size_t)q] = mk(std::sin(0.37 * (double)q + 0.1), std::cos(0.91 * (double)q));
+    c128* df = c->alloc<c128>((size_t)N);
+    c128* dx = c->alloc<c128>((size_t)N);
+    c128* dy = c->alloc<c128>((size_t)N);
+    HIPCHK(hipMemcpy(df, hf.data(), (size_t)N * sizeof(c128), hipMemcpyHostToDevice));
+    hipStream_t keep = c->s;
+    c->s = nullptr;
+    try {
+        solve(df, dx);
+    } catch (...) {
+        c->s = keep;
+        throw;
+    }
+    c->s = keep;
+    hipLaunchKernelGGL(k_stencil_f64, dim3(lin_grid(N, 256, 1 << 30)), dim3(256), 0, 0, d, w, st, dx, dy);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpy(hr.data(), dy, (size_t)N * sizeof(c128), hipMemcpyDeviceToHost));
+    double rn = 0.0, fn = 0.0;
+    for (int64_t q = 0; q < N; ++q) {
+        rn += cabs2(hr[(size_t)q] - hf[(size_t)q]);
+        fn += cabs2(hf[(size_t)q]);
+    }
+    c->release(df);
+    c->release(dx);
+    c->release(dy);
+    return std::sqrt(rn / fn);
+}
+
+// One block's dense inverse by Gauss-Jordan with partial pivoting over all
+// rows, a launch sequence per column.
+void dense_pivoted(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& dc) {
     const int64_t N = dc.np();
-    // the dense inverse costs 16 N^2 bytes and O(N^3) setup: keep N modest
-    if (N > kDenseMax)
-        throw ArgError{"coarsest grid too large for the dense direct solve (use the block-tridiagonal solve)"};
     c128* M = c->alloc<c128>((size_t)N * 2 * N);
-    hipLaunchKernelGGL(k_dense_from_stencil, dim3(lin_grid(N, 64, 1 << 30)), dim3(64), 0, 0, dc, wprev, prev, M);
+    hipLaunchKernelGGL(k_dense_from_stencil, dim3(lin_grid(N, 64, 1 << 30)), dim3(64), 0, 0, dc, w, st, M, 2 * N, 1);
     HIPCHK(hipGetLastError());
     int64_t* piv = c->alloc<int64_t>(1);
     c128* pval = c->alloc<c128>(1);
@@ -549,8 +659,6 @@ void build_dense(eh_ctx* c, Block& B, c128* prev, const Widths& wprev, const Dim
         hipLaunchKernelGGL(k_gj_eliminate, dim3(gcols, (unsigned)N), dim3(256), 0, 0, N, kk, M, mult);
     }
     HIPCHK(hipGetLastError());
-    B.Nc = N;
-    B.Ainv = c->alloc<c128>((size_t)N * N);
     hipLaunchKernelGGL(k_gj_extract, dim3(lin_grid(N * N, 256, 1 << 30)), dim3(256), 0, 0, N, M, B.Ainv);
     HIPCHK(hipGetLastError());
     HIPCHK(hipDeviceSynchronize());
@@ -560,18 +668,347 @@ void build_dense(eh_ctx* c, Block& B, c128* prev, const Widths& wprev, const Dim
     c->release(mult);
 }
 
+// x = X_c^-1 f by the block's dense inverse, one FP64 vector.
+void dense_apply_f64(eh_ctx* c, const Block& B, const c128* f, c128* x) {
+    DenseArgs da{};
+    da.ns = 1;
+    da.N[0] = (int)B.Nc;
+    da.Ainv[0] = B.Ainv;
+    GArgs<double> a{};
+    a.ns = 1;
+    a.f[0] = f;
+    a.out[0] = x;
+    a.vf[0] = a.vo[0] = B.Nc;
+    hipLaunchKernelGGL((k_gdense<double, 1>), dim3((unsigned)B.Nc, 1), dim3(256), 0, c->s, da, a);
+    HIPCHK(hipGetLastError());
+}
+
+// Coarsest solves by explicit dense inverses (FP64), applied later as
+// matrix-vector products: every block inverted side by side by blocked
+// Gauss-Jordan, which pivots inside its 32 x 32 pivot blocks.  512^2 with 5
+// levels (three blocks of 1024-1056 points): 65 ms of one-column steps on
+// the device before, see the figures at k_gj_diag.  The inverse is checked
+// by one solve; a block whose residual is not below kDenseCheck (the pivot
+// blocks met too small pivots) is inverted again with pivoting over all
+// rows.
+constexpr double kDenseCheck = 1e-11;
+void build_dense(eh_ctx* c, c128* const* st, const Widths* w) {
+    std::vector<GJMat> mats;
+    int bpmax = 0;
+    for (int b = 0; b <= c->dim; ++b) {
+        const int64_t N = c->blk[b].lev.back().d.np();
+        // the dense inverse costs 16 N^2 bytes and O(N^3) setup: keep N modest
+        if (N > kDenseMax)
+            throw ArgError{"coarsest grid too large for the dense direct solve (use the block-tridiagonal solve)"};
+        bpmax = std::max(bpmax, pad_gj(N));
+    }
+    bool again[4] = {false, false, false, false};
+    {
+        GJScratch g(c, (size_t)bpmax * bpmax);
+        for (int b = 0; b <= c->dim; ++b) {
+            const Dims d = c->blk[b].lev.back().d;
+            GJMat m{g.get(), pad_gj(d.np())};
+            hipLaunchKernelGGL(k_gj_identity, dim3((unsigned)((m.bp + 255) / 256), (unsigned)m.bp), dim3(256), 0, 0,
+                               m.M, m.bp);
+            hipLaunchKernelGGL(k_dense_from_stencil, dim3(lin_grid(d.np(), 64, 1 << 30)), dim3(64), 0, 0, d, w[b],
+                               st[b], m.M, (int64_t)m.bp, 0);
+            HIPCHK(hipGetLastError());
+            mats.push_back(m);
+        }
+        gj_invert(g, mats);
+        const bool zero = g.zero_pivot();
+        std::vector<BTCopy> cp;
+        int64_t Nmax = 1;
+        for (int b = 0; b <= c->dim; ++b) {
+            Block& B = c->blk[b];
+            const int64_t N = B.lev.back().d.np();
+            B.Nc = N;
+            B.Ainv = c->alloc<c128>((size_t)N * N);
+            cp.push_back({mats[b].M, B.Ainv, (int)N, (int)N, mats[b].bp, (int)N});
+            Nmax = std::max(Nmax, N);
+        }
+        hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((Nmax + 255) / 256), (unsigned)Nmax, (unsigned)cp.size()),
+                           dim3(256), 0, 0, g.upload(cp));
+        HIPCHK(hipGetLastError());
+        for (int b = 0; b <= c->dim; ++b) {
+            const Block& B = c->blk[b];
+            const double rel = zero ? 1.0
+                                    : coarse_residual(c, st[b], w[b], B.lev.back().d, [&](const c128* f, c128* x) {
+                                          dense_apply_f64(c, B, f, x);
+                                      });
+            again[b] = !(rel < kDenseCheck);
+        }
+    }
+    for (int b = 0; b <= c->dim; ++b)
+        if (again[b]) dense_pivoted(c, c->blk[b], st[b], w[b], c->blk[b].lev.back().d);
+}
 
 template <class T>
 void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const int64_t* vf, void* const* out,
               const int64_t* vo, int nrhs);
 
-// Coarsest solve by block-tridiagonal LU over groups of planes normal to the
-// axis that gives the smallest groups (eh_coarse_kernels.h): every group's
-// Schur complement is inverted by blocked Gauss-Jordan; the factors are
-// checked by solving one system and recomputing its residual in FP64.
-void build_bt(eh_ctx* c, Block& B, c128* st, const Widths& w, const Dims& d) {
+// Points left to the dense matrix that ends the elimination: one launch over
+// n^2 entries instead of two launches per further level.
+constexpr int64_t kBtTail = 1536;
+
+// Eliminate the groups of pt: with `nested` every other group per level,
+// until at most kBtTail points (or one group) are left; else one group per
+// level, the first of the chain.  Returns the relative residual of a solve
+// with the factors (1 after a zero pivot).
+double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nested) {
+    struct Elim { int e, l, r; int64_t mat; };
+    struct Keep { int k, e1, e2; int64_t mat; };
+    struct Plan { std::vector<Elim> el; std::vector<Keep> kp; };
     BTData& T = B.btd;
-    BTPart& pt = T.pt;
+    T = BTData{};
+    T.N = pt.d.np();
+    const int nb = pt.nb;
+    auto bs = [&](int I) -> int64_t { return I < 0 ? 0 : pt.bsize(I); };
+    // the schedule and the elimination order
+    std::vector<Plan> plan;
+    std::vector<int> active(nb), order;
+    for (int I = 0; I < nb; ++I) active[I] = I;
+    int64_t left = T.N, tot = 0;
+    while (active.size() > 1 && !(nested && left <= kBtTail)) {
+        Plan P;
+        std::vector<int> next;
+        const int na = (int)active.size();
+        auto gone = [&](int p) { return nested ? p % 2 == 0 : p == 0; };
+        auto at = [&](int p) { return p >= 0 && p < na ? active[p] : -1; };
+        for (int p = 0; p < na; ++p) {
+            const int I = active[p];
+            if (gone(p)) {
+                Elim e{I, at(p - 1), at(p + 1), tot};
+                tot += bs(I) * (bs(I) + bs(e.l) + bs(e.r));
+                P.el.push_back(e);
+                order.push_back(I);
+                left -= bs(I);
+            } else {
+                Keep k{I, gone(p - 1) ? at(p - 1) : -1, gone(p + 1) ? at(p + 1) : -1, tot};
+                tot += bs(I) * (bs(k.e1) + bs(k.e2));
+                // the first level also brings the untouched groups' f into y
+                if (k.e1 >= 0 || k.e2 >= 0 || plan.empty()) P.kp.push_back(k);
+                next.push_back(I);
+            }
+        }
+        plan.push_back(P);
+        active.swap(next);
+    }
+    const int64_t mtail = tot;
+    tot += left * left;
+    order.insert(order.end(), active.begin(), active.end());
+    std::vector<int64_t> voff(nb, 0);
+    std::vector<int> perm((size_t)T.N);
+    {
+        int64_t o = 0;
+        for (int I : order) {
+            voff[I] = o;
+            for (int m = 0; m < pt.bsize(I); ++m) {
+                int cc[3];
+                pt.coords(I, m, cc);
+                perm[(size_t)o++] = (int)pt.point(cc);
+            }
+        }
+    }
+    // tasks
+    std::vector<BTTask> tasks;
+    auto vo = [&](int I) { return I < 0 ? 0 : (int)voff[I]; };
+    for (const Plan& P : plan) {
+        BTData::Lev L;
+        L.f0 = (int)tasks.size();
+        for (const Keep& k : P.kp) {
+            BTTask t{k.mat, (int)bs(k.k), {(int)bs(k.e1), (int)bs(k.e2), 0}, {vo(k.e1), vo(k.e2), 0}, vo(k.k)};
+            tasks.push_back(t);
+            L.fmax = std::max(L.fmax, t.rows);
+            L.fmat += (double)t.rows * (t.n[0] + t.n[1]);
+            L.fvec += 2.0 * t.rows + t.n[0] + t.n[1];
+        }
+        L.nf = (int)tasks.size() - L.f0;
+        L.b0 = (int)tasks.size();
+        for (const Elim& e : P.el) {
+            BTTask t{e.mat, (int)bs(e.e), {(int)bs(e.e), (int)bs(e.l), (int)bs(e.r)}, {vo(e.e), vo(e.l), vo(e.r)},
+                     vo(e.e)};
+            tasks.push_back(t);
+            L.bmax = std::max(L.bmax, t.rows);
+            L.bmat += (double)t.rows * (t.n[0] + t.n[1] + t.n[2]);
+            L.bvec += 2.0 * t.rows + t.n[1] + t.n[2];
+        }
+        L.nb = (int)tasks.size() - L.b0;
+        T.lev.push_back(L);
+    }
+    T.tail = (int)tasks.size();
+    T.ntail = (int)left;
+    tasks.push_back({mtail, (int)left, {(int)left, 0, 0}, {(int)(T.N - left), 0, 0}, (int)(T.N - left)});
+    T.mats = c->alloc<c128>((size_t)tot);
+    T.perm = c->alloc<int>((size_t)T.N);
+    T.tasks = c->alloc<BTTask>(tasks.size());
+    HIPCHK(hipMemcpy(T.perm, perm.data(), perm.size() * sizeof(int), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(T.tasks, tasks.data(), tasks.size() * sizeof(BTTask), hipMemcpyHostToDevice));
+    // the numbers
+    int64_t bmax = 1;
+    for (int I = 0; I < nb; ++I) bmax = std::max(bmax, bs(I));
+    const int bp = pad_gj(bmax);
+    bool zero = false;
+    {
+        GJScratch g(c, (size_t)bp * bp);
+        std::vector<c128*> D(nb, nullptr), L(nb, nullptr), U(nb, nullptr);
+        std::vector<BTBlock> ex;
+        auto expand = [&](std::vector<c128*>& X, int I, int dir) {
+            if (X[I]) return;
+            X[I] = g.get();
+            ex.push_back({X[I], I, dir});
+        };
+        auto run_expand = [&]() {
+            if (ex.empty()) return;
+            hipLaunchKernelGGL(k_bt_couple_dense, dim3((unsigned)((bp + 255) / 256), (unsigned)bp, (unsigned)ex.size()),
+                               dim3(256), 0, 0, pt, st, g.upload(ex), bp);
+            HIPCHK(hipGetLastError());
+            ex.clear();
+        };
+        auto run_products = [&](const std::vector<GJProd>& pr) {
+            if (pr.empty()) return;
+            const unsigned t64 = (unsigned)((bp + 63) / 64);
+            hipLaunchKernelGGL(k_gj_product, dim3(t64, t64, (unsigned)pr.size()), dim3(256), 0, 0, g.upload(pr), bp);
+            HIPCHK(hipGetLastError());
+        };
+        auto run_copies = [&](const std::vector<BTCopy>& cp) {
+            int rows = 1, cols = 1;
+            for (const BTCopy& k : cp) { rows = std::max(rows, k.rows); cols = std::max(cols, k.cols); }
+            if (cp.empty()) return;
+            hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((cols + 255) / 256), (unsigned)rows, (unsigned)cp.size()),
+                               dim3(256), 0, 0, g.upload(cp));
+            HIPCHK(hipGetLastError());
+        };
+        for (const Plan& P : plan) {
+            for (const Elim& e : P.el) {
+                expand(D, e.e, 0);
+                if (e.l >= 0) expand(L, e.e, -1);
+                if (e.r >= 0) expand(U, e.e, +1);
+            }
+            for (const Keep& k : P.kp) {
+                if (k.e1 < 0 && k.e2 < 0) continue;
+                expand(D, k.k, 0);
+                if (k.e1 >= 0) expand(L, k.k, -1);
+                if (k.e2 >= 0) expand(U, k.k, +1);
+            }
+            run_expand();
+            std::vector<GJMat> inv;
+            for (const Elim& e : P.el) inv.push_back({D[e.e], bp});
+            gj_invert(g, inv);
+            std::vector<GJProd> p1, p2, p3;
+            std::vector<BTCopy> cp;
+            std::vector<c128*> tmp;
+            auto fresh = [&]() { tmp.push_back(g.get()); return tmp.back(); };
+            for (const Elim& e : P.el) {
+                const int64_t b = bs(e.e), ld = b + bs(e.l) + bs(e.r);
+                c128* dst = T.mats + e.mat;
+                cp.push_back({D[e.e], dst, (int)b, (int)b, bp, (int)ld});
+                if (e.l >= 0) {
+                    c128* E = fresh();
+                    p1.push_back({D[e.e], L[e.e], E, -1.0, 0});
+                    cp.push_back({E, dst + b, (int)b, (int)bs(e.l), bp, (int)ld});
+                }
+                if (e.r >= 0) {
+                    c128* E = fresh();
+                    p1.push_back({D[e.e], U[e.e], E, -1.0, 0});
+                    cp.push_back({E, dst + b + bs(e.l), (int)b, (int)bs(e.r), bp, (int)ld});
+                }
+            }
+            std::vector<std::pair<c128**, c128*>> repl;    // couplings of kept groups to replace
+            for (const Keep& k : P.kp) {
+                const int64_t b = bs(k.k), ld = bs(k.e1) + bs(k.e2);
+                c128* dst = T.mats + k.mat;
+                if (k.e1 >= 0) {
+                    c128* G = fresh();
+                    p1.push_back({L[k.k], D[k.e1], G, -1.0, 0});
+                    cp.push_back({G, dst, (int)b, (int)bs(k.e1), bp, (int)ld});
+                    p2.push_back({G, U[k.e1], D[k.k], 1.0, 1});
+                    c128* nl = nullptr;
+                    if (L[k.e1]) {
+                        nl = g.get();
+                        p2.push_back({G, L[k.e1], nl, 1.0, 0});
+                    }
+                    repl.push_back({&L[k.k], nl});
+                }
+                if (k.e2 >= 0) {
+                    c128* G = fresh();
+                    p1.push_back({U[k.k], D[k.e2], G, -1.0, 0});
+                    cp.push_back({G, dst + bs(k.e1), (int)b, (int)bs(k.e2), bp, (int)ld});
+                    p3.push_back({G, L[k.e2], D[k.k], 1.0, 1});
+                    c128* nu = nullptr;
+                    if (U[k.e2]) {
+                        nu = g.get();
+                        p3.push_back({G, U[k.e2], nu, 1.0, 0});
+                    }
+                    repl.push_back({&U[k.k], nu});
+                }
+            }
+            run_products(p1);
+            run_products(p2);
+            run_products(p3);
+            run_copies(cp);
+            for (auto& r : repl) {
+                g.put(*r.first);
+                *r.first = r.second;
+            }
+            for (const Elim& e : P.el) { g.put(D[e.e]); g.put(L[e.e]); g.put(U[e.e]); }
+            for (c128*& t : tmp) g.put(t);
+        }
+        // the dense rest
+        for (size_t p = 0; p < active.size(); ++p) {
+            expand(D, active[p], 0);
+            if (p > 0) expand(L, active[p], -1);
+            if (p + 1 < active.size()) expand(U, active[p], +1);
+        }
+        run_expand();
+        const int bpt = pad_gj(left);
+        struct Tail {
+            eh_ctx* c;
+            c128* M;
+            ~Tail() { c->release(M); }
+        } tm{c, c->alloc<c128>((size_t)bpt * bpt)};
+        hipLaunchKernelGGL(k_gj_identity, dim3((unsigned)((bpt + 255) / 256), (unsigned)bpt), dim3(256), 0, 0, tm.M, bpt);
+        HIPCHK(hipGetLastError());
+        std::vector<BTCopy> cp;
+        int64_t r = 0;
+        for (size_t p = 0; p < active.size(); ++p) {
+            const int I = active[p];
+            const int64_t b = bs(I);
+            cp.push_back({D[I], tm.M + r * bpt + r, (int)b, (int)b, bp, bpt});
+            if (p > 0) {
+                const int64_t bl = bs(active[p - 1]);
+                cp.push_back({L[I], tm.M + r * bpt + r - bl, (int)b, (int)bl, bp, bpt});
+            }
+            if (p + 1 < active.size()) cp.push_back({U[I], tm.M + r * bpt + r + b, (int)b, (int)bs(active[p + 1]), bp, bpt});
+            r += b;
+        }
+        run_copies(cp);
+        gj_invert(g, {{tm.M, bpt}});
+        run_copies({{tm.M, T.mats + mtail, (int)left, (int)left, bpt, (int)left}});
+        zero = g.zero_pivot();
+    }
+    if (zero) return 1.0;
+    T.y = c->alloc<c128>((size_t)2 * T.N);
+    B.bt = true;
+    B.Nc = T.N;
+    return coarse_residual(c, st, pt.w, pt.d, [&](const c128* f, c128* x) {
+        const int kinds[1] = {B.kind};
+        const void* fp[1] = {f};
+        void* xp[1] = {x};
+        const int64_t vv[1] = {T.N};
+        bt_solve<double>(c, kinds, 1, fp, vv, xp, vv, 1);
+    });
+}
+
+// Coarsest solve by block elimination over groups of planes normal to the
+// axis that gives the smallest groups (eh_coarse_kernels.h); the factors are
+// checked by solving one system and recomputing its residual in FP64.
+// Elimination without pivoting between groups can meet a near-singular
+// Schur complement that another order avoids (or its larger factors may not
+// fit), so when the nested order fails the groups are eliminated one after
+// the other.
+void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& d) {
+    BTPart pt{};
     pt.d = d;
     pt.w = w;
     const int64_t N = d.np();
@@ -589,103 +1026,25 @@ void build_bt(eh_ctx* c, Block& B, c128* st, const Widths& w, const Dims& d) {
     pt.gsz = w.w[best];
     pt.nb = (d.g[best] + pt.gsz - 1) / pt.gsz;
     pt.P = (int)(N / d.g[best]);
-    const int nb = pt.nb;
-    T.goff.assign(nb + 1, 0);
-    T.offF.assign(nb, 0);
-    T.offB.assign(nb, 0);
-    int64_t tot = 0;
-    int bmax = 0;
-    for (int I = 0; I < nb; ++I) {
-        const int64_t b = pt.bsize(I);
-        T.goff[I + 1] = T.goff[I] + b;
-        T.offF[I] = tot;
-        tot += b * (b + pt.bsize(I - 1));
-        bmax = std::max(bmax, (int)b);
+    auto drop = [&]() {
+        BTData& T = B.btd;
+        c->release(T.mats);
+        c->release(T.perm);
+        c->release(T.tasks);
+        c->release(T.y);
+        T = BTData{};
+    };
+    double rel = 1.0;
+    try {
+        rel = bt_factor(c, B, st, pt, true);
+    } catch (const HipError& e) {
+        if (e.e != hipErrorOutOfMemory) throw;
+        (void)hipGetLastError();
     }
-    for (int I = 0; I < nb; ++I) {
-        T.offB[I] = tot;
-        tot += (int64_t)pt.bsize(I) * pt.bsize(I + 1);
+    if (!(rel < 1e-8)) {
+        drop();
+        rel = bt_factor(c, B, st, pt, false);
     }
-    T.mats = c->alloc<c128>((size_t)tot);
-    T.offF_d = c->alloc<int64_t>((size_t)nb);
-    HIPCHK(hipMemcpy(T.offF_d, T.offF.data(), (size_t)nb * sizeof(int64_t), hipMemcpyHostToDevice));
-    {
-        std::vector<int> perm((size_t)N);
-        for (int I = 0; I < nb; ++I)
-            for (int m = 0; m < pt.bsize(I); ++m) {
-                int cc[3];
-                pt.coords(I, m, cc);
-                perm[(size_t)(T.goff[I] + m)] = (int)pt.point(cc);
-            }
-        T.perm = c->alloc<int>((size_t)N);
-        HIPCHK(hipMemcpy(T.perm, perm.data(), (size_t)N * sizeof(int), hipMemcpyHostToDevice));
-    }
-    const int bpmax = (bmax + GJB - 1) / GJB * GJB;
-    c128* M = c->alloc<c128>((size_t)bpmax * bpmax);
-    int* bad = c->alloc<int>(1);
-    HIPCHK(hipMemset(bad, 0, sizeof(int)));
-    for (int I = 0; I < nb; ++I) {
-        const int b = pt.bsize(I), bprev = pt.bsize(I - 1), bnext = pt.bsize(I + 1);
-        const int bp = (b + GJB - 1) / GJB * GJB;
-        hipLaunchKernelGGL(k_bt_schur, dim3((unsigned)((bp + 255) / 256), (unsigned)bp), dim3(256), 0, 0, pt, st, I,
-                           I > 0 ? T.mats + T.offB[I - 1] : nullptr, M, bp);
-        const unsigned t64 = (unsigned)((bp + 63) / 64);
-        for (int K = 0; K < bp / GJB; ++K) {
-            hipLaunchKernelGGL(k_gj_diag, dim3(1), dim3(256), 0, 0, M, bp, K, bad);
-            hipLaunchKernelGGL(k_gj_rowpanel, dim3(t64), dim3(256), 0, 0, M, bp, K);
-            hipLaunchKernelGGL(k_gj_update, dim3(t64, t64), dim3(256), 0, 0, M, bp, K);
-            hipLaunchKernelGGL(k_gj_colpanel, dim3(t64), dim3(256), 0, 0, M, bp, K);
-        }
-        const int ldF = b + bprev;
-        hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((b + 255) / 256), (unsigned)b), dim3(256), 0, 0, M, bp, b,
-                           T.mats + T.offF[I], ldF);
-        if (I > 0)
-            hipLaunchKernelGGL(k_bt_couple, dim3((unsigned)((bprev + 255) / 256), (unsigned)b), dim3(256), 0, 0, pt,
-                               st, I, -1, M, bp, T.mats + T.offF[I] + b, ldF);
-        if (I < nb - 1)
-            hipLaunchKernelGGL(k_bt_couple, dim3((unsigned)((bnext + 255) / 256), (unsigned)b), dim3(256), 0, 0, pt,
-                               st, I, +1, M, bp, T.mats + T.offB[I], bnext);
-        HIPCHK(hipGetLastError());
-    }
-    HIPCHK(hipDeviceSynchronize());
-    int hbad = 0;
-    HIPCHK(hipMemcpy(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost));
-    c->release(M);
-    c->release(bad);
-    if (hbad) throw ArgError{"coarsest level: zero pivot in the block-tridiagonal factorisation"};
-    B.bt = true;
-    B.Nc = N;
-    // accuracy check: solve X x = f for a fixed f, recompute f - X x in FP64
-    std::vector<c128> hf((size_t)N), hr((size_t)N);
-    for (int64_t q = 0; q < N; ++q) hf[(size_t)q] = mk(std::sin(0.37 * (double)q + 0.1), std::cos(0.91 * (double)q));
-    c128* df = c->alloc<c128>((size_t)N);
-    c128* dx = c->alloc<c128>((size_t)N);
-    c128* dy = c->alloc<c128>((size_t)N);
-    T.y = c->alloc<c128>((size_t)N);
-    HIPCHK(hipMemcpy(df, hf.data(), (size_t)N * sizeof(c128), hipMemcpyHostToDevice));
-    {
-        hipStream_t keep = c->s;
-        c->s = nullptr;
-        const int kinds[1] = {B.kind};
-        const void* fp[1] = {df};
-        void* xp[1] = {dx};
-        const int64_t vv[1] = {N};
-        bt_solve<double>(c, kinds, 1, fp, vv, xp, vv, 1);
-        c->s = keep;
-    }
-    hipLaunchKernelGGL(k_stencil_f64, dim3(lin_grid(N, 256, 1 << 30)), dim3(256), 0, 0, d, w, st, dx, dy);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpy(hr.data(), dy, (size_t)N * sizeof(c128), hipMemcpyDeviceToHost));
-    double rn = 0.0, fn = 0.0;
-    for (int64_t q = 0; q < N; ++q) {
-        const c128 e = hr[(size_t)q] - hf[(size_t)q];
-        rn += cabs2(e);
-        fn += cabs2(hf[(size_t)q]);
-    }
-    c->release(df);
-    c->release(dx);
-    c->release(dy);
-    const double rel = std::sqrt(rn / fn);
     if (!(rel < 1e-8)) {
         char msg[160];
         std::snprintf(msg, sizeof msg, "coarsest level: block-tridiagonal factorisation inaccurate (relative "
@@ -694,8 +1053,9 @@ void build_bt(eh_ctx* c, Block& B, c128* st, const Widths& w, const Dims& d) {
     }
 }
 
-// Galerkin hierarchy (FP64 on the device) and coarsest inverse.
-void build_hierarchy(eh_ctx* c, Block& B, const std::vector<c128>& st0) {
+// Galerkin hierarchy (FP64 on the device); the coarsest operator's stencil
+// and widths are returned (the caller releases it).
+void build_hierarchy(eh_ctx* c, Block& B, const std::vector<c128>& st0, c128*& coarsest, Widths& wcoarsest) {
     const int L = (int)B.lev.size();
     const bool f32 = c->o.mg_precision == 32;
     c128* prev = c->alloc<c128>(st0.size());
@@ -766,10 +1126,9 @@ void build_hierarchy(eh_ctx* c, Block& B, const std::vector<c128>& st0) {
     HIPCHK(hipMemcpy(&ov, overflow, sizeof(int), hipMemcpyDeviceToHost));
     c->release(overflow);
     if (ov) throw ArgError{"internal: Galerkin stencil exceeded its width"};
-    const Level& Lc = B.lev[L - 1];
-    if (c->use_bt) build_bt(c, B, prev, wprev, Lc.d);
-    else build_dense(c, B, prev, wprev, Lc.d);
-    c->release(prev);
+    // the coarsest operator, inverted or factored with the other blocks'
+    coarsest = prev;
+    wcoarsest = wprev;
 }
 
 void ensure_mg_workspace(eh_ctx* c, int nrhs) {
@@ -788,7 +1147,7 @@ void ensure_mg_workspace(eh_ctx* c, int nrhs) {
         BTData& T = c->blk[b].btd;
         if (!c->blk[b].bt) continue;
         c->release(T.y);
-        T.y = c->alloc<c128>((size_t)T.pt.d.np() * nrhs);
+        T.y = c->alloc<c128>((size_t)2 * T.N * nrhs);
     }
     c->nrhs_cap = nrhs;
 }
@@ -1009,13 +1368,10 @@ template <class T>
 void gcycle(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, const int64_t* vf,
             void* const* out, const int64_t* vo, bool guess, int nrhs);
 
-// Coarsest solve e = X_c^-1 f for the blocks kinds[0..ns) by the block-
-// tridiagonal factors: every group's S_I^-1 f_I in one launch, then the
-// forward sweep over the groups adding -S_I^-1 L_I y_{I-1}, then the back
-// sweep adding B_I x_{I+1}, one launch per group step for all blocks of
-// the launch (a block with fewer groups idles in the last steps; the first
-// forward step has nothing to add).  Right-hand sides in chunks of up to 8
-// per workgroup (the steps of batches up to 4: one), each matrix row read
+// Coarsest solve e = X_c^-1 f for the blocks kinds[0..ns) with the factors
+// of bt_factor: one launch per level down, the dense rest, one per level
+// back up, for all blocks of the launch (a block with fewer levels idles in
+// the others).  Right-hand sides in chunks of up to 8, each matrix row read
 // once per chunk.
 template <class T>
 void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const int64_t* vf, void* const* out,
@@ -1024,99 +1380,64 @@ void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const i
     if (nrhs < 1) return;
     const int RB = nrhs >= 5 ? 8 : nrhs >= 3 ? 4 : nrhs;
     const unsigned chunks = (unsigned)((nrhs + RB - 1) / RB);
-    int maxnb = 0, maxb0 = 1;
-    BTAll<T> fa{};
-    fa.ns = ns;
-    fa.nrhs = nrhs;
-    double fby = 0.0;
+    BTRun<T> a{};
+    a.ns = ns;
+    a.nrhs = nrhs;
+    int nlev = 0;
     for (int s = 0; s < ns; ++s) {
         const BTData& bd = c->blk[kinds[s]].btd;
-        const BTPart& pt = bd.pt;
-        maxnb = std::max(maxnb, pt.nb);
-        fa.N[s] = (int)pt.d.np();
-        fa.b0[s] = pt.bsize(0);
-        fa.nb[s] = pt.nb;
-        fa.mats[s] = bd.mats;
-        fa.offF[s] = bd.offF_d;
-        fa.perm[s] = bd.perm;
-        fa.y[s] = bd.y;
-        fa.f[s] = (const cplx<T>*)f[s];
-        fa.vf[s] = vf[s];
-        maxb0 = std::max(maxb0, fa.b0[s]);
-        // algorithmic bytes: the S_I^-1 blocks once per chunk, f read, y written
-        for (int I = 0; I < pt.nb; ++I) fby += (double)pt.bsize(I) * pt.bsize(I) * sizeof(c128) * chunks;
-        fby += (double)fa.N[s] * nrhs * (sizeof(cplx<T>) + sizeof(c128));
+        nlev = std::max(nlev, (int)bd.lev.size());
+        a.mats[s] = bd.mats;
+        a.perm[s] = bd.perm;
+        a.N[s] = (int)bd.N;
+        a.y[s] = bd.y;
+        a.x[s] = bd.y + (int64_t)nrhs * bd.N;
+        a.f[s] = (const cplx<T>*)f[s];
+        a.vf[s] = vf[s];
+        a.e[s] = (cplx<T>*)out[s];
+        a.ve[s] = vo[s];
     }
-    {
-        Timed tm(c, KC_DENSE, fby);
-        const dim3 g((unsigned)((maxb0 + BT_RW - 1) / BT_RW), (unsigned)(maxnb * ns), chunks);
-        if (RB == 8) hipLaunchKernelGGL((k_bt_fpart<T, 8>), g, dim3(256), 0, c->s, fa);
-        else if (RB == 4) hipLaunchKernelGGL((k_bt_fpart<T, 4>), g, dim3(256), 0, c->s, fa);
-        else if (RB == 2) hipLaunchKernelGGL((k_bt_fpart<T, 2>), g, dim3(256), 0, c->s, fa);
-        else hipLaunchKernelGGL((k_bt_fpart<T, 1>), g, dim3(256), 0, c->s, fa);
-        HIPCHK(hipGetLastError());
-    }
-    // The sweep steps are latency-bound: up to 4 right-hand sides, one per
-    // workgroup (a shorter chain of work per workgroup, the rows re-read
-    // from the caches) beats reading the rows once for the batch (192^3 x 4:
-    // 111 -> 90 ms per solve).  Algorithmic bytes of one step: the matrix
-    // rows once per chunk of up to 8 right-hand sides, the neighbour's
-    // vector entries read, this group's read and written (and e written in
-    // the back sweep).
-    const int RBc = nrhs <= 4 ? 1 : RB;
-    const unsigned chunksc = (unsigned)((nrhs + RBc - 1) / RBc);
-    auto step_bytes = [&](bool fwd, const BTStep<T>& a) {
+    // level l down / up, or the dense rest (l < 0)
+    auto launch = [&](int l, bool back) {
+        int maxt = 0, maxr = 1;
         double by = 0.0;
         for (int s = 0; s < ns; ++s) {
-            const double b = a.b[s], bo = a.bo[s];
-            by += b * bo * sizeof(c128) * chunks;
-            by += nrhs * (bo * sizeof(c128) + b * (2.0 * sizeof(c128) + (fwd ? 0.0 : (double)sizeof(cplx<T>))));
+            const BTData& bd = c->blk[kinds[s]].btd;
+            a.tasks[s] = bd.tasks;
+            a.ntasks[s] = 0;
+            double mat = 0.0, vec = 0.0;
+            if (l < 0) {
+                a.tasks[s] += bd.tail;
+                a.ntasks[s] = 1;
+                a.first[s] = bd.lev.empty();
+                maxr = std::max(maxr, bd.ntail);
+                mat = (double)bd.ntail * bd.ntail;
+                vec = 2.0 * bd.ntail;
+            } else if (l < (int)bd.lev.size()) {
+                const BTData::Lev& L = bd.lev[l];
+                a.tasks[s] += back ? L.b0 : L.f0;
+                a.ntasks[s] = back ? L.nb : L.nf;
+                a.first[s] = l == 0;
+                maxr = std::max(maxr, back ? L.bmax : L.fmax);
+                mat = back ? L.bmat : L.fmat;
+                vec = back ? L.bvec : L.fvec;
+            }
+            maxt = std::max(maxt, a.ntasks[s]);
+            by += sizeof(c128) * (mat * chunks + vec * nrhs) + (back ? (double)sizeof(cplx<T>) * vec / 2 * nrhs : 0.0);
         }
-        return by;
-    };
-    auto launch = [&](bool fwd, const BTStep<T>& a, int maxb) {
-        Timed tm(c, KC_DENSE, step_bytes(fwd, a));
-        const dim3 g((unsigned)((std::max(maxb, 1) + BT_RW - 1) / BT_RW), (unsigned)ns, chunksc);
-#define EH_BT(RBV)                                                                          \
-    if (fwd) hipLaunchKernelGGL((k_bt_chain<T, RBV, false>), g, dim3(256), 0, c->s, a);     \
-    else hipLaunchKernelGGL((k_bt_chain<T, RBV, true>), g, dim3(256), 0, c->s, a);
-        if (RBc == 8) { EH_BT(8) } else if (RBc == 4) { EH_BT(4) } else if (RBc == 2) { EH_BT(2) } else { EH_BT(1) }
+        if (maxt == 0) return;
+        Timed tm(c, KC_DENSE, by);
+        const dim3 g((unsigned)((maxr + BT_RW - 1) / BT_RW), (unsigned)(maxt * ns), chunks);
+#define EH_BT(RBV)                                                                           \
+    if (back) hipLaunchKernelGGL((k_bt_rows<T, RBV, true>), g, dim3(256), 0, c->s, a);       \
+    else hipLaunchKernelGGL((k_bt_rows<T, RBV, false>), g, dim3(256), 0, c->s, a);
+        if (RB == 8) { EH_BT(8) } else if (RB == 4) { EH_BT(4) } else if (RB == 2) { EH_BT(2) } else { EH_BT(1) }
 #undef EH_BT
         HIPCHK(hipGetLastError());
     };
-    for (int pass = 0; pass < 2; ++pass) {
-        const bool fwd = pass == 0;
-        for (int k = fwd ? 1 : 0; k < maxnb; ++k) {
-            BTStep<T> a{};
-            a.ns = ns;
-            a.nrhs = nrhs;
-            int maxb = 0;
-            for (int s = 0; s < ns; ++s) {
-                const BTData& bd = c->blk[kinds[s]].btd;
-                const BTPart& pt = bd.pt;
-                a.ldy[s] = pt.d.np();
-                a.e[s] = (cplx<T>*)out[s];
-                a.ve[s] = vo[s];
-                const int I = fwd ? k : pt.nb - 1 - k;
-                if (k >= pt.nb) {
-                    a.b[s] = 0; a.bo[s] = 0; a.lda[s] = 0;
-                    a.mat[s] = bd.mats; a.perm[s] = bd.perm; a.y[s] = bd.y; a.yo[s] = bd.y;
-                    continue;
-                }
-                const int J = fwd ? I - 1 : I + 1;
-                a.b[s] = pt.bsize(I);
-                a.bo[s] = pt.bsize(J);
-                // forward: the coupling columns of F_I (after its b_I columns of S_I^-1)
-                a.lda[s] = fwd ? a.b[s] + a.bo[s] : a.bo[s];
-                a.mat[s] = bd.mats + (fwd ? bd.offF[I] + a.b[s] : bd.offB[I]);
-                a.perm[s] = bd.perm + bd.goff[I];
-                a.y[s] = bd.y + bd.goff[I];
-                a.yo[s] = bd.y + ((J >= 0 && J < pt.nb) ? bd.goff[J] : 0);
-                maxb = std::max(maxb, a.b[s]);
-            }
-            launch(fwd, a, maxb);
-        }
-    }
+    for (int l = 0; l < nlev; ++l) launch(l, false);
+    launch(-1, true);
+    for (int l = nlev - 1; l >= 0; --l) launch(l, true);
 }
 
 // The fused legs cover 2D V(1, nu2) cycles started from a zero guess.
@@ -2529,6 +2850,8 @@ eh_status eh_create(eh_ctx** out, int dim, const int64_t* n, const double* h, co
             upload_real<double>(c, (void**)&c->d_vs, tmp);
         }
         const bool f32 = o.mg_precision == 32;
+        c128* cst[4] = {nullptr, nullptr, nullptr, nullptr};   // coarsest stencils
+        Widths cw[4] = {};
         for (int b = 0; b <= dim; ++b) {
             Block& B = c->blk[b];
             B.kind = b;
@@ -2569,8 +2892,14 @@ eh_status eh_create(eh_ctx** out, int dim, const int64_t* n, const double* h, co
             if (f32) upload_cplx<float>(c, &B.fD, D);
             else upload_cplx<double>(c, &B.fD, D);
             const std::vector<c128> st0 = fine_stencil(c, B, w, D);
-            build_hierarchy(c, B, st0);
+            build_hierarchy(c, B, st0, cst[b], cw[b]);
         }
+        if (c->use_bt) {
+            for (int b = 0; b <= dim; ++b) build_bt(c, c->blk[b], cst[b], cw[b], c->blk[b].lev[o.levels - 1].d);
+        } else {
+            build_dense(c, cst, cw);
+        }
+        for (int b = 0; b <= dim; ++b) c->release(cst[b]);
         ensure_mg_workspace(c, 1);
         HIPCHK(hipDeviceSynchronize());
     } catch (const HipError& e) {

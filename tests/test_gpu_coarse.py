@@ -176,3 +176,55 @@ def test_batch_equals_single(nrhs):
         zk = gpu.apply_preconditioner(to_dev(r[k:k + 1])).cpu().numpy()[0]
         assert np.array_equal(zb[k], zk), k
     gpu.close()
+
+
+@pytest.mark.parametrize("n", [
+    (50, 41),        # 50 groups of 41: one level of the elimination, then 25 groups dense
+    (33, 97),        # odd group counts on two levels
+    (130, 17),       # long chain of narrow groups, the last one kept or removed
+    (200, 9),
+    (61, 64),        # 61 or 62 groups: the chain ends on a removed group
+    (13, 14, 15),    # 3D, groups of one plane of about 180
+])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 6])
+def test_elimination_levels(n, nrhs):
+    """Chains of groups whose elimination in levels ends differently (odd
+    and even counts, a last group without a right neighbour, a dense rest of
+    several groups) and every chunk width of the solve, against splu on the
+    fine blocks (one level, FP64, 1e-10 as above)."""
+    say("elimination levels", n, nrhs)
+    alpha = 0.3
+    gpu, s = make(n, seed=11, levels=1, alpha=alpha, mg_precision=64, coarse_solver="bt")
+    for b in range(s.dim + 1):
+        X = block_op(s, b, alpha).tocsc()
+        f = crand((nrhs, X.shape[0]), 70 + b)
+        e = gpu.block_cycle(b, to_dev(f)).cpu().numpy()
+        lu = spla.splu(X)
+        for k in range(nrhs):
+            assert rel(e[k], lu.solve(f[k])) <= 1e-10, (b, k)
+    gpu.close()
+
+
+def test_dense_inverse_with_small_pivot_blocks():
+    """The dense inverse's pivot blocks pivot only inside themselves.  A
+    medium whose constant velocities make the leading diagonal entries of
+    the unshifted, unattenuated operator vanish (the stiffness of the
+    pressure block's interior cells equals the mass term) is still inverted:
+    against splu, FP64, with the accuracy the set-up's check asks for
+    (1e-11) times the operator's conditioning taken from the oracle."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    n, h = (24, 20), (1.0, 1.0)
+    shape = tuple(reversed(n))
+    vp, vs, rho = np.full(shape, 2.0), np.full(shape, 1.0), np.ones(shape)
+    # H_p: (1 + mu / (lambda + mu)) * 4 = omega^2 rho / (lambda + mu)
+    omega = float(np.sqrt(4.0 * (1.0 + 1.0 / 3.0) * 3.0))
+    gpu = ElasticHelmholtz(n, h, vp, vs, rho, omega, levels=1, alpha=0.05, abc_width=0, abc_sides=0xF, gamma0=0.0,
+                           mg_precision=64, coarse_solver="dense")
+    s = ElasticSystem(n, h, vp, vs, rho, omega, 0, 0xF, gamma0=0.0)
+    for b in range(3):
+        X = block_op(s, b, 0.05).tocsc()
+        f = crand(X.shape[0], 90 + b)
+        e = gpu.block_cycle(b, to_dev(f)).cpu().numpy()
+        cond = np.linalg.cond(X.toarray())
+        assert rel(e, spla.splu(X).solve(f)) <= max(1e-10, 1e-11 * cond), b
+    gpu.close()
