@@ -38,25 +38,11 @@
 #pragma once
 
 #include "eh_common.h"
+#include "eh_launch.h"
 #include "eh_group_kernels.h"
 #include "eh_mg_kernels.h"
 
 namespace eh {
-
-// Tile configurations (x extent, y extent, threads): the down leg's tile
-// is in coarse points, the up leg's in fine points.  Large tiles amortise
-// the halo on big levels; small ones give the few-thousand-point levels
-// enough workgroups and keep every phase to about one round of loads per
-// thread.  The autotuner picks one per level and block group.  The phase
-// loops stay rolled: on small levels each compute unit runs a workgroup or
-// two, so the kernel's instruction fetch from a cold cache is part of its
-// latency, and unrolled code costs more there than it gains on big levels.
-struct FCfg {
-    int x, y, threads;
-};
-constexpr FCfg kFDown[] = {{32, 8, 256}, {32, 8, 512}, {16, 8, 256}, {7, 3, 128}};
-constexpr FCfg kFUp[] = {{64, 16, 1024}, {64, 8, 512}, {32, 8, 256}, {16, 8, 128}};
-constexpr int kFCfgs = 4;
 
 constexpr int FUSE_MAXW = 2;
 // LDS elements: down = staged u0 (support + halo) + residual of the support;

@@ -22,13 +22,10 @@
 #include "eh_krylov_kernels.h"
 #include "eh_mg_kernels.h"
 #include "eh_op_kernels.h"
-#include "eh_fine3_kernels.h"
-#include "eh_stencil3_kernels.h"
-#include "eh_transfer3_kernels.h"
 #include "eh_setup_kernels.h"
 #include "eh_grad_kernels.h"
 #include "eh_group_kernels.h"
-#include "eh_fused_kernels.h"
+#include "eh_launch.h"
 #include "eh_coarse_kernels.h"
 
 using namespace eh;
@@ -1190,66 +1187,6 @@ GArgs<T> gbase(eh_ctx* c, const int* kinds, int ns, int l, bool coarse_dims_for_
     return a;
 }
 
-// Right-hand sides per workgroup of a multigrid launch (fused leg or
-// per-sweep kernel) with `tiles` workgroups per slot: the whole batch while the tiles alone give kSplitWgs workgroups or
-// more (the operator in registers then serves every right-hand side);
-// below that the batch is split into chunks, up to one right-hand side per
-// workgroup, so that a small level runs its right-hand sides side by side
-// instead of one after the other.
-#ifndef EH_SPLIT_WGS
-#define EH_SPLIT_WGS 4096
-#endif
-constexpr int kSplitWgs = EH_SPLIT_WGS;
-inline int rhs_chunk(int tiles, int ns, int nrhs) {
-    const int64_t wgs = (int64_t)tiles * ns;
-    if (nrhs <= 1 || wgs >= kSplitWgs) return std::max(nrhs, 1);
-    const int nch = (int)std::min<int64_t>(nrhs, (kSplitWgs + wgs - 1) / wgs);
-    return (nrhs + nch - 1) / nch;
-}
-
-// Grid of a per-sweep kernel over the slots of a and the chunks of the
-// batch; rch receives the right-hand sides per workgroup.
-template <class T>
-dim3 ggrid(const GArgs<T>& a, const dim3& blk, int nrhs, int& rch) {
-    int gx = 1, gy = 1;
-    for (int s = 0; s < a.ns; ++s) {
-        gx = std::max(gx, (int)((a.d[s].g[0] + blk.x - 1) / blk.x));
-        gy = std::max(gy, (int)((a.d[s].g[1] + blk.y - 1) / blk.y));
-    }
-    rch = rhs_chunk(gx * gy * a.maxg2, a.ns, nrhs);
-    const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
-    return dim3((unsigned)gx, (unsigned)gy, (unsigned)(a.maxg2 * a.ns * nch));
-}
-
-// Restriction (grid = coarse level) or prolongation with correction (grid
-// = fine level) for the slots of t.
-template <class T>
-void launch_transfer(eh_ctx* c, const GArgs<T>& t, const dim3& blk, bool restrict_to_coarse, int nrhs) {
-    int rch = 1;
-    if (c->dim == 3) {
-        // the staged 3D transfers: tiles of 256 threads
-        if (restrict_to_coarse) {
-            const dim3 g = ggrid(t, dim3(RTX, RTY, 1), nrhs, rch);
-            if (t.mixed) hipLaunchKernelGGL((k_grestrict3_lds<T, true>), g, dim3(256), 0, c->s, t, nrhs, rch);
-            else hipLaunchKernelGGL((k_grestrict3_lds<T, false>), g, dim3(256), 0, c->s, t, nrhs, rch);
-        } else {
-            const dim3 g = ggrid(t, dim3(PTX, PTY, 1), nrhs, rch);
-            hipLaunchKernelGGL((k_gprolong3_lds<T>), g, dim3(256), 0, c->s, t, nrhs, rch);
-        }
-        HIPCHK(hipGetLastError());
-        return;
-    }
-    const dim3 g = ggrid(t, blk, nrhs, rch);
-    if (restrict_to_coarse) {
-        if (c->dim == 2) hipLaunchKernelGGL((k_gtransfer<T, 2, true>), g, blk, 0, c->s, t, nrhs, rch);
-        else hipLaunchKernelGGL((k_gtransfer<T, 3, true>), g, blk, 0, c->s, t, nrhs, rch);
-    } else {
-        if (c->dim == 2) hipLaunchKernelGGL((k_gtransfer<T, 2, false>), g, blk, 0, c->s, t, nrhs, rch);
-        else hipLaunchKernelGGL((k_gtransfer<T, 3, false>), g, blk, 0, c->s, t, nrhs, rch);
-    }
-    HIPCHK(hipGetLastError());
-}
-
 // real couplings stored per fine-level point: d edge weights (A_k), one
 // cell weight (H_p), or a pair per axis (H_p from A~_p)
 inline int fine_couplings(const eh_ctx* c, bool P) {
@@ -1282,75 +1219,8 @@ void gsweep(eh_ctx* c, GArgs<T>& a, int l, int mode, int nrhs) {
                           : (mode == 0 || mode == 4 || mode == 5 ? KC_FINE_FIRST
                                                                   : (mode == 1 ? KC_FINE_SWEEP : KC_FINE_RESID));
     Timed tm(c, cls, by);
-    if (l == 0 && c->dim == 3 && (mode == 1 || mode == 2 || mode == 5)) {
-        // the plane-staged kernel: FTX x FTY tiles of two planes, 256 threads
-        int gx = 1, gy = 1;
-        for (int s = 0; s < a.ns; ++s) {
-            gx = std::max(gx, (a.d[s].g[0] + FTX - 1) / FTX);
-            gy = std::max(gy, (a.d[s].g[1] + FTY - 1) / FTY);
-        }
-        const int nzb = (a.maxg2 + 1) / 2;   // plane pairs
-        const int rch = rhs_chunk(gx * gy * nzb, a.ns, nrhs);
-        const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
-        const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(nzb * a.ns * nch));
-#define EH_G3(KIND)                                                                                              \
-    if (mode == 1) hipLaunchKernelGGL((k_gfine3_lds<T, KIND, 1>), g, dim3(256), 0, c->s, a, nrhs, rch);          \
-    else if (mode == 2) hipLaunchKernelGGL((k_gfine3_lds<T, KIND, 2>), g, dim3(256), 0, c->s, a, nrhs, rch);     \
-    else hipLaunchKernelGGL((k_gfine3_lds<T, KIND, 5>), g, dim3(256), 0, c->s, a, nrhs, rch);
-        if (P && a.tilde) { EH_G3(2) } else if (P) { EH_G3(1) } else { EH_G3(0) }
-#undef EH_G3
-        HIPCHK(hipGetLastError());
-        return;
-    }
-    if (l > 0 && c->dim == 3 && a.mixed && (mode == 1 || mode == 2 || mode == 5)) {
-        // the plane-staged 27-point kernel: STX x STY tiles of 256 threads
-        const dim3 blk(STX, STY, 1);
-        int rch = 1;
-        const dim3 g = ggrid(a, blk, nrhs, rch);
-        if (mode == 1) hipLaunchKernelGGL((k_gstencil3_lds<T, 1>), g, dim3(256), 0, c->s, a, nrhs, rch);
-        else if (mode == 2) hipLaunchKernelGGL((k_gstencil3_lds<T, 2>), g, dim3(256), 0, c->s, a, nrhs, rch);
-        else hipLaunchKernelGGL((k_gstencil3_lds<T, 5>), g, dim3(256), 0, c->s, a, nrhs, rch);
-        HIPCHK(hipGetLastError());
-        return;
-    }
     const dim3 blk = shape_block(c, group_of(c, kind0), l, 0);
-    int rch = 1;
-    const dim3 g = ggrid(a, blk, nrhs, rch);
-    if (l == 0) {
-#define EH_GF(KIND, DIM, MODE) hipLaunchKernelGGL((k_gfine<T, KIND, DIM, MODE>), g, blk, 0, c->s, a, nrhs, rch)
-#define EH_GF_M(KIND, DIM)                      \
-    switch (mode) {                             \
-        case 0: EH_GF(KIND, DIM, 0); break;     \
-        case 1: EH_GF(KIND, DIM, 1); break;     \
-        case 2: EH_GF(KIND, DIM, 2); break;     \
-        case 3: EH_GF(KIND, DIM, 3); break;     \
-        case 4: EH_GF(KIND, DIM, 4); break;     \
-        default: EH_GF(KIND, DIM, 5); break;    \
-    }
-        if (c->dim == 2) {
-            if (P && a.tilde) { EH_GF_M(2, 2) } else if (P) { EH_GF_M(1, 2) } else { EH_GF_M(0, 2) }
-        } else {
-            if (P && a.tilde) { EH_GF_M(2, 3) } else if (P) { EH_GF_M(1, 3) } else { EH_GF_M(0, 3) }
-        }
-#undef EH_GF_M
-#undef EH_GF
-    } else {
-#define EH_GS(DIM, MODE)                                                                   \
-    if (a.mixed) hipLaunchKernelGGL((k_gstencil<T, DIM, MODE, true>), g, blk, 0, c->s, a, nrhs, rch);  \
-    else hipLaunchKernelGGL((k_gstencil<T, DIM, MODE, false>), g, blk, 0, c->s, a, nrhs, rch)
-#define EH_GS_M(DIM)                        \
-    switch (mode) {                         \
-        case 0: EH_GS(DIM, 0); break;       \
-        case 1: EH_GS(DIM, 1); break;       \
-        case 2: EH_GS(DIM, 2); break;       \
-        case 3: EH_GS(DIM, 3); break;       \
-        case 4: EH_GS(DIM, 4); break;       \
-        default: EH_GS(DIM, 5); break;      \
-    }
-        if (c->dim == 2) { EH_GS_M(2) } else { EH_GS_M(3) }
-#undef EH_GS_M
-#undef EH_GS
-    }
+    launch_sweep<T>(c->s, c->dim, a, l, mode, blk, nrhs);
     HIPCHK(hipGetLastError());
 }
 
@@ -1451,63 +1321,6 @@ inline bool fused_cycle(const eh_ctx* c, bool guess) {
 // f_{l+1} = R (f - X w D^-1 f), the cycle on level l+1, then
 // out = S^nu2 (w D^-1 f + P e_{l+1}).
 
-// Fused down leg on level l with tile configuration cfg: a.d / a.dc = levels
-// l / l+1, a.f = f_l, a.out = f_{l+1}.
-template <class T>
-void launch_fdown(eh_ctx* c, const GArgs<T>& a, int l, int cfg, int nrhs) {
-    const FCfg k = kFDown[cfg];
-    int gx = 1, gy = 1;
-    for (int s = 0; s < a.ns; ++s) {
-        gx = std::max(gx, (a.dc[s].g[0] + k.x - 1) / k.x);
-        gy = std::max(gy, (a.dc[s].g[1] + k.y - 1) / k.y);
-    }
-    const int rch = rhs_chunk(gx * gy, a.ns, nrhs);
-    const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
-    const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(a.ns * nch)), blk((unsigned)k.threads);
-#define EH_LFD(CF)                                                                               \
-    if (l == 0) hipLaunchKernelGGL((k_fdown<T, true, CF>), g, blk, 0, c->s, a, nrhs, rch);       \
-    else hipLaunchKernelGGL((k_fdown<T, false, CF>), g, blk, 0, c->s, a, nrhs, rch);
-    switch (cfg) {
-        case 0: EH_LFD(0) break;
-        case 1: EH_LFD(1) break;
-        case 2: EH_LFD(2) break;
-        default: EH_LFD(3) break;
-    }
-#undef EH_LFD
-    HIPCHK(hipGetLastError());
-}
-
-// Fused up leg on level l: a.f = f_l, a.u = e_{l+1}, a.out = e_l.
-template <class T>
-void launch_fup(eh_ctx* c, const GArgs<T>& a, int l, int cfg, int nrhs) {
-    const FCfg k = kFUp[cfg];
-    int gx = 1, gy = 1;
-    for (int s = 0; s < a.ns; ++s) {
-        gx = std::max(gx, (a.d[s].g[0] + k.x - 1) / k.x);
-        gy = std::max(gy, (a.d[s].g[1] + k.y - 1) / k.y);
-    }
-    const int rch = rhs_chunk(gx * gy, a.ns, nrhs);
-    const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
-    const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(a.ns * nch)), blk((unsigned)k.threads);
-    const bool two = c->o.nu_post == 2;
-#define EH_LFU(CF)                                                                                    \
-    if (l == 0) {                                                                                     \
-        if (two) hipLaunchKernelGGL((k_fup<T, true, 2, CF>), g, blk, 0, c->s, a, nrhs, rch);          \
-        else hipLaunchKernelGGL((k_fup<T, true, 1, CF>), g, blk, 0, c->s, a, nrhs, rch);              \
-    } else {                                                                                          \
-        if (two) hipLaunchKernelGGL((k_fup<T, false, 2, CF>), g, blk, 0, c->s, a, nrhs, rch);         \
-        else hipLaunchKernelGGL((k_fup<T, false, 1, CF>), g, blk, 0, c->s, a, nrhs, rch);             \
-    }
-    switch (cfg) {
-        case 0: EH_LFU(0) break;
-        case 1: EH_LFU(1) break;
-        case 2: EH_LFU(2) break;
-        default: EH_LFU(3) break;
-    }
-#undef EH_LFU
-    HIPCHK(hipGetLastError());
-}
-
 template <class T>
 void fused_level(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, const int64_t* vf,
                  void* const* out, const int64_t* vo, int nrhs) {
@@ -1538,7 +1351,8 @@ void fused_level(eh_ctx* c, const int* kinds, int ns, int l, const void* const* 
             a.vo[s] = vcv[s];
         }
         Timed tm(c, l == 0 ? KC_FINE_DOWN : KC_COARSE_DOWN, cbytes + nrhs * vdown);
-        launch_fdown<T>(c, a, l, c->fcfg[grp][lt][0], nrhs);
+        launch_fdown<T>(c->s, a, l, c->fcfg[grp][lt][0], nrhs);
+        HIPCHK(hipGetLastError());
     }
     gcycle<T>(c, kinds, ns, l + 1, cf, vcv, ce, vcv, false, nrhs);
     {
@@ -1551,7 +1365,8 @@ void fused_level(eh_ctx* c, const int* kinds, int ns, int l, const void* const* 
             a.vo[s] = vo[s];
         }
         Timed tm(c, l == 0 ? KC_FINE_UP : KC_COARSE_UP, cbytes + nrhs * vup);
-        launch_fup<T>(c, a, l, c->fcfg[grp][lt][1], nrhs);
+        launch_fup<T>(c->s, c->o.nu_post, a, l, c->fcfg[grp][lt][1], nrhs);
+        HIPCHK(hipGetLastError());
     }
 }
 
@@ -1714,7 +1529,7 @@ void gcycle(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, co
         }
         Timed tm(c, KC_RESTRICT, by);
         const dim3 blk = shape_block(c, group_of(c, kinds[0]), l, 1);
-        launch_transfer<T>(c, t, blk, true, nrhs);
+        launch_transfer<T>(c->s, c->dim, t, blk, true, nrhs);
         HIPCHK(hipGetLastError());
     }
     // W: two calls on level l+1, except when it is the coarsest level, whose
@@ -1734,7 +1549,7 @@ void gcycle(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, co
         }
         Timed tm(c, KC_PROLONG, by);
         const dim3 blk = shape_block(c, group_of(c, kinds[0]), l, 2);
-        launch_transfer<T>(c, t, blk, false, nrhs);
+        launch_transfer<T>(c->s, c->dim, t, blk, false, nrhs);
         HIPCHK(hipGetLastError());
     }
     for (int t = 0; t < nu2; ++t) sweep(1, t == nu2 - 1);
@@ -1901,15 +1716,16 @@ void maybe_autotune(eh_ctx* c, int nrhs) {
                     a.f[s] = (const cplx<T>*)Lv.f; a.vf[s] = Lv.d.np();
                     a.out[s] = (cplx<T>*)Cv.f; a.vo[s] = Cv.d.np();
                 }
-                c->fcfg[g][l][0] = pick_cfg(c, [&](int cf) { launch_fdown<T>(c, a, l, cf, nrhs); });
+                c->fcfg[g][l][0] = pick_cfg(c, [&](int cf) { launch_fdown<T>(c->s, a, l, cf, nrhs); });
                 for (int s = 0; s < ns; ++s) {
                     Level& Lv = c->blk[kinds[s]].lev[l];
                     Level& Cv = c->blk[kinds[s]].lev[l + 1];
                     a.u[s] = (const cplx<T>*)Cv.e; a.vu[s] = Cv.d.np();
                     a.out[s] = (cplx<T>*)Lv.u; a.vo[s] = Lv.d.np();
                 }
-                c->fcfg[g][l][1] = pick_cfg(c, [&](int cf) { launch_fup<T>(c, a, l, cf, nrhs); });
+                c->fcfg[g][l][1] = pick_cfg(c, [&](int cf) { launch_fup<T>(c->s, c->o.nu_post, a, l, cf, nrhs); });
             }
+            HIPCHK(hipGetLastError());
             continue;
         }
         for (int l = 0; l < L; ++l) {
@@ -1950,11 +1766,11 @@ void maybe_autotune(eh_ctx* c, int nrhs) {
                 pt.out[s] = (cplx<T>*)Lv.u; pt.vo[s] = Lv.d.np();
             }
             c->shape[g][l][1] = pick_shape(c, [&](const dim3& blk) {
-                launch_transfer<T>(c, rt, blk, true, nrhs);
+                launch_transfer<T>(c->s, c->dim, rt, blk, true, nrhs);
                 HIPCHK(hipGetLastError());
             });
             c->shape[g][l][2] = pick_shape(c, [&](const dim3& blk) {
-                launch_transfer<T>(c, pt, blk, false, nrhs);
+                launch_transfer<T>(c->s, c->dim, pt, blk, false, nrhs);
                 HIPCHK(hipGetLastError());
             });
         }
