@@ -222,6 +222,8 @@ struct eh_ctx {
     int64_t tmpT_elems = 0;
     double* misfit_part = nullptr; // eh_misfit's per-source partial sums (grown as needed)
     int misfit_cap = 0;
+    double* grad_part = nullptr;   // eh_gradient's sums per chunk of right-hand sides (grown as needed)
+    int64_t grad_cap = 0;
     std::vector<void*> allocs;
     std::string err;
     bool broken = false;

@@ -166,3 +166,35 @@ def test_gradient_full_size_512_finite_differences():
         say(f"  direction {t}: fd {fd:.10e} adjoint {an:.10e} rel err {err:.2e}")
         assert err <= 1e-5
     say(f"  worst relative error over 10 directions: {worst:.2e}")
+
+
+@pytest.mark.parametrize("n,nrhs", [
+    ((32, 8), 1),        # one whole tile of the gradient kernel
+    ((34, 10), 3),       # two columns and two rows beyond it
+    ((2, 2), 2),         # smaller than a tile, every mean at the boundary
+    ((66, 18), 40),      # few tiles: the right-hand sides split over workgroups, a ragged last chunk
+    ((130, 258), 5),     # many tiles
+    ((6, 10, 8), 3),     # 3D
+])
+def test_gradient_kernel_matches_oracle(n, nrhs):
+    """eh_gradient for random fields u, w against the oracle's per-cell sums
+    dH/dm at the edges of the kernel's tiles (FP64 sums of up to 40 terms:
+    1e-12 relative)."""
+    from oracle.elastic import ElasticSystem
+    from oracle.fwi import chain_to_velocities, dH_terms
+    from paper_2411_15897_amd import ElasticHelmholtz
+    rng = np.random.default_rng(3)
+    shape, h = tuple(reversed(n)), tuple(1.0 + 0.25 * a for a in range(len(n)))
+    vp = rng.uniform(2.0, 3.0, shape)
+    vs, rho = vp * rng.uniform(0.4, 0.6, shape), rng.uniform(1.0, 2.0, shape)
+    s = ElasticHelmholtz(n, h, vp, vs, rho, 0.6, levels=1, alpha=0.3, abc_width=2)
+    sys_ = ElasticSystem(n, h, vp, vs, rho, 0.6, 2, W.abc_all_but_top(len(n)))
+    u = rng.standard_normal((nrhs, s.ndof)) + 1j * rng.standard_normal((nrhs, s.ndof))
+    w = rng.standard_normal((nrhs, s.ndof)) + 1j * rng.standard_normal((nrhs, s.ndof))
+    got = s.gradient(torch.from_numpy(u).cuda(), torch.from_numpy(w).cuda())
+    T_mu, T_lm, T_rho = dH_terms(sys_, np.conj(w), u)
+    ref = chain_to_velocities(-T_mu.real, -T_lm.real, -T_rho.real, vp, vs, rho)
+    for a, o in zip(got, ref):
+        err = np.linalg.norm(a.cpu().numpy() - o) / np.linalg.norm(o)
+        assert err <= 1e-12, (n, nrhs, err)
+    s.close()
