@@ -397,7 +397,7 @@ k_gtransfer(GArgs<T> a, int nrhs, int rch) {
 }
 
 // ---------------------------------------------------------------------------
-// coarsest level: e = Ainv f per slot (one workgroup per row)
+// coarsest level: e = Ainv f per slot
 
 struct DenseArgs {
     int ns;
@@ -405,65 +405,100 @@ struct DenseArgs {
     const c128* Ainv[GMAX];
 };
 
+// Sum each of V values over the wavefront's 64 lanes.  While more than one
+// value is left, a step sends half of them to the partner lane and keeps the
+// other half, so V values take V - 1 + log2(64 / V) exchanges instead of
+// 6 V; a value's sum is the same tree whatever V is.  Returns the index of
+// the value whose sum ends in v[0] of this lane (lanes that differ in bits
+// below 64 / V hold the same one).
+template <int V, int OFF = 32, int H = V / 2>
+__device__ __forceinline__ int wave_sums(double (&v)[V]) {
+    if constexpr (OFF == 0) {
+        return 0;
+    } else if constexpr (H >= 1) {
+        const bool up = (threadIdx.x & OFF) != 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const double hi = v[i + H], lo = v[i];
+            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, OFF, 64);
+        }
+        return (up ? H : 0) + wave_sums<V, OFF / 2, H / 2>(v);
+    } else {
+        v[0] += __shfl_xor(v[0], OFF, 64);
+        return wave_sums<V, OFF / 2, 0>(v);
+    }
+}
+
+// Two rows per workgroup (one for a single right-hand side, where more
+// workgroups hide the latency of the reads), whose 256 threads take the
+// columns 256 apart (a row segment of 4 KB per load); the right-hand sides
+// of a chunk share the rows' entries, the rows share the vectors' (read
+// through L1).  With ~4 columns per thread the sums over the lanes weighed
+// more than the products, hence wave_sums.  N = 1056, two blocks: 16
+// right-hand sides 55 us in two launches with one row per workgroup and a
+// butterfly per value, 23 us so; three right-hand sides at N = 1690 38 us in
+// two launches (2 + 1), 20 us in one chunk of four.
+// Grid (row groups of the largest block, slots, chunks of RB right-hand sides).
+template <int RB>
+constexpr int gd_rows() { return RB == 1 ? 1 : 2; }
 template <class T, int RB>
 __global__ void __launch_bounds__(256)
-k_gdense(DenseArgs da, GArgs<T> a) {
-    // one row per workgroup: its 256 threads take the columns 256 apart
-    // (four row segments of 4 KB in flight per round), so even one block's
-    // ~1000 rows keep 16 wavefronts per compute unit reading the matrix
+k_gdense(DenseArgs da, GArgs<T> a, int nrhs) {
+    constexpr int GD_R = gd_rows<RB>(), V = 2 * RB * GD_R;
+    __shared__ double part[4][V];
     const int slot = blockIdx.y;
-    if (slot >= da.ns) return;
     const int N = da.N[slot];
-    const int row = blockIdx.x;
-    if (row >= N) return;
+    const int row0 = blockIdx.x * GD_R;
+    if (row0 >= N) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const c128* A = da.Ainv[slot] + (int64_t)row * N;
-    const cplx<T>* f = a.f[slot];
-    cplx<T>* e = a.out[slot];
-    const int64_t vf = a.vf[slot], ve = a.vo[slot];
-    double accr[RB], acci[RB];
+    const int r0 = blockIdx.z * RB;
+    const int cnt = min(RB, nrhs - r0);
+    const c128* __restrict__ A0 = da.Ainv[slot] + (int64_t)row0 * N;
+    const int64_t rstep = row0 + 1 < N ? N : 0;      // a missing second row repeats the first
+    const int64_t vf = a.vf[slot];
+    const cplx<T>* __restrict__ f = a.f[slot] + r0 * vf;
+    // value (row q, right-hand side r, part c) at (q * RB + r) * 2 + c
+    double acc[V];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) { accr[r] = 0.0; acci[r] = 0.0; }
-    constexpr int U = 4;
-    int c = threadIdx.x;
-    for (; c + 256 * (U - 1) < N; c += 256 * U) {
-        c128 av[U];
+    for (int i = 0; i < V; ++i) acc[i] = 0.0;
+    constexpr int U = RB >= 4 ? 2 : 4;               // columns in flight per thread
+    for (int c = threadIdx.x; c < N; c += 256 * U) {
+        c128 av[GD_R][U];
+        cplx<T> fv[RB][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) av[u] = A[c + 256 * u];
+        for (int u = 0; u < U; ++u) {
+            const int cc = c + 256 * u < N ? c + 256 * u : c;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+            for (int q = 0; q < GD_R; ++q) av[q][u] = A0[q * rstep + cc];
 #pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const cplx<T> fv = f[r * vf + c + 256 * u];
-                accr[r] += av[u].re * double(fv.re) - av[u].im * double(fv.im);
-                acci[r] += av[u].re * double(fv.im) + av[u].im * double(fv.re);
+            for (int r = 0; r < RB; ++r) fv[r][u] = f[(r < cnt ? r : 0) * vf + cc];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c + 256 * u < N) {
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    const double xr = double(fv[r][u].re), xi = double(fv[r][u].im);
+#pragma unroll
+                    for (int q = 0; q < GD_R; ++q) {
+                        const int i = (q * RB + r) * 2;
+                        acc[i] = fmat(-av[q][u].im, xi, fmat(av[q][u].re, xr, acc[i]));
+                        acc[i + 1] = fmat(av[q][u].im, xr, fmat(av[q][u].re, xi, acc[i + 1]));
+                    }
+                }
             }
-    }
-    for (; c < N; c += 256) {
-        const c128 av = A[c];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const cplx<T> fv = f[r * vf + c];
-            accr[r] += av.re * double(fv.re) - av.im * double(fv.im);
-            acci[r] += av.re * double(fv.im) + av.im * double(fv.re);
         }
     }
-    // fixed-order reduction: within each wavefront, then over the four
-    __shared__ double sr[4][RB], si[4][RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        for (int off = 32; off > 0; off >>= 1) {
-            accr[r] += __shfl_xor(accr[r], off, 64);
-            acci[r] += __shfl_xor(acci[r], off, 64);
-        }
-        if (lane == 0) { sr[wave][r] = accr[r]; si[wave][r] = acci[r]; }
-    }
+    const int idx = wave_sums<V>(acc);
+    if ((lane & (64 / V - 1)) == 0) part[wave][idx] = acc[0];
     __syncthreads();
-    if (threadIdx.x < RB) {
-        const int r = threadIdx.x;
-        const double re = (sr[0][r] + sr[1][r]) + (sr[2][r] + sr[3][r]);
-        const double im = (si[0][r] + si[1][r]) + (si[2][r] + si[3][r]);
-        e[r * ve + row] = mk<T>(T(re), T(im));
+    if (threadIdx.x < RB * GD_R) {
+        const int t = threadIdx.x, q = t / RB, r = t % RB;
+        if (r >= cnt || row0 + q >= N) return;
+        const double re = (part[0][2 * t] + part[1][2 * t]) + (part[2][2 * t] + part[3][2 * t]);
+        const double im =
+            (part[0][2 * t + 1] + part[1][2 * t + 1]) + (part[2][2 * t + 1] + part[3][2 * t + 1]);
+        a.out[slot][(r0 + r) * a.vo[slot] + row0 + q] = mk<T>(T(re), T(im));
     }
 }
 

@@ -678,7 +678,7 @@ void dense_apply_f64(eh_ctx* c, const Block& B, const c128* f, c128* x) {
     a.f[0] = f;
     a.out[0] = x;
     a.vf[0] = a.vo[0] = B.Nc;
-    hipLaunchKernelGGL((k_gdense<double, 1>), dim3((unsigned)B.Nc, 1), dim3(256), 0, c->s, da, a);
+    hipLaunchKernelGGL((k_gdense<double, 1>), dim3((unsigned)B.Nc, 1), dim3(256), 0, c->s, da, a, 1);
     HIPCHK(hipGetLastError());
 }
 
@@ -1397,30 +1397,27 @@ void gcycle(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, co
             da.Ainv[s] = B.Ainv;
             Nmax = std::max(Nmax, da.N[s]);
         }
-        int r = 0;
-        while (r < nrhs) {
-            // one timed launch per chunk: the inverse once, the chunk's vectors
-            const int rb = nrhs - r >= 8 ? 8 : nrhs - r >= 4 ? 4 : nrhs - r >= 2 ? 2 : 1;
-            double by = 0.0;
-            for (int s = 0; s < ns; ++s) {
-                const double N = (double)c->blk[kinds[s]].Nc;
-                by += N * N * sizeof(c128) + 2.0 * N * rb * sizeof(cplx<T>);
-            }
-            Timed tm(c, KC_DENSE, by);
-            for (int s = 0; s < ns; ++s) {
-                a.f[s] = (const cplx<T>*)f[s] + (int64_t)r * vf[s];
-                a.out[s] = (cplx<T>*)out[s] + (int64_t)r * vo[s];
-                a.vf[s] = vf[s];
-                a.vo[s] = vo[s];
-            }
-            const dim3 g((unsigned)Nmax, (unsigned)ns);        // one row per workgroup
-            const int left = nrhs - r;
-            if (left >= 8) { hipLaunchKernelGGL((k_gdense<T, 8>), g, dim3(256), 0, c->s, da, a); r += 8; }
-            else if (left >= 4) { hipLaunchKernelGGL((k_gdense<T, 4>), g, dim3(256), 0, c->s, da, a); r += 4; }
-            else if (left >= 2) { hipLaunchKernelGGL((k_gdense<T, 2>), g, dim3(256), 0, c->s, da, a); r += 2; }
-            else { hipLaunchKernelGGL((k_gdense<T, 1>), g, dim3(256), 0, c->s, da, a); r += 1; }
-            HIPCHK(hipGetLastError());
+        // one launch: chunks of up to 8 right-hand sides, the inverse read
+        // once per chunk
+        const int rb = nrhs >= 5 ? 8 : nrhs >= 3 ? 4 : nrhs;
+        const int chunks = (nrhs + rb - 1) / rb;
+        double by = 0.0;
+        for (int s = 0; s < ns; ++s) {
+            const double N = (double)c->blk[kinds[s]].Nc;
+            by += chunks * N * N * sizeof(c128) + 2.0 * N * nrhs * sizeof(cplx<T>);
+            a.f[s] = (const cplx<T>*)f[s];
+            a.out[s] = (cplx<T>*)out[s];
+            a.vf[s] = vf[s];
+            a.vo[s] = vo[s];
         }
+        Timed tm(c, KC_DENSE, by);
+        const int rows = rb == 1 ? gd_rows<1>() : gd_rows<8>();
+        const dim3 g((unsigned)((Nmax + rows - 1) / rows), (unsigned)ns, (unsigned)chunks);
+        if (rb == 8) hipLaunchKernelGGL((k_gdense<T, 8>), g, dim3(256), 0, c->s, da, a, nrhs);
+        else if (rb == 4) hipLaunchKernelGGL((k_gdense<T, 4>), g, dim3(256), 0, c->s, da, a, nrhs);
+        else if (rb == 2) hipLaunchKernelGGL((k_gdense<T, 2>), g, dim3(256), 0, c->s, da, a, nrhs);
+        else hipLaunchKernelGGL((k_gdense<T, 1>), g, dim3(256), 0, c->s, da, a, nrhs);
+        HIPCHK(hipGetLastError());
         return;
     }
     const int nu1 = c->o.nu_pre, nu2 = c->o.nu_post;
