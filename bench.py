@@ -283,7 +283,7 @@ def pmc_summary(fetch_csv, write_csv, kernel, workload, config=None):
 # Each solve's first cycle start, and nothing else in a benchmark run, takes
 # the norm of b with the Gram-Schmidt kernel's mode 3: its dispatches mark
 # where the solves begin in a trace or a counter run.
-SOLVE_MARK = "eh::k_gs<3>"
+SOLVE_MARK = "eh::k_gs<3"
 
 
 def trace_summary(trace_csv, solves):

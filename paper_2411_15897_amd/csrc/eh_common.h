@@ -73,4 +73,28 @@ struct Widths {
     __host__ __device__ int nst() const { return (2 * w[0] + 1) * (2 * w[1] + 1) * (2 * w[2] + 1); }
 };
 
+// Sum each of V values over the wavefront's 64 lanes.  While more than one
+// value is left, a step sends half of them to the partner lane and keeps the
+// other half, so V values take V - 1 + log2(64 / V) exchanges instead of
+// 6 V; a value's sum is the same tree whatever V is.  Returns the index of
+// the value whose sum ends in v[0] of this lane (lanes that differ in bits
+// below 64 / V hold the same one).
+template <int V, int OFF = 32, int H = V / 2>
+__device__ __forceinline__ int wave_sums(double (&v)[V]) {
+    if constexpr (OFF == 0) {
+        return 0;
+    } else if constexpr (H >= 1) {
+        const bool up = (threadIdx.x & OFF) != 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const double hi = v[i + H], lo = v[i];
+            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, OFF, 64);
+        }
+        return (up ? H : 0) + wave_sums<V, OFF / 2, H / 2>(v);
+    } else {
+        v[0] += __shfl_xor(v[0], OFF, 64);
+        return wave_sums<V, OFF / 2, 0>(v);
+    }
+}
+
 }  // namespace eh

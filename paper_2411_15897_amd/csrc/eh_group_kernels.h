@@ -405,30 +405,6 @@ struct DenseArgs {
     const c128* Ainv[GMAX];
 };
 
-// Sum each of V values over the wavefront's 64 lanes.  While more than one
-// value is left, a step sends half of them to the partner lane and keeps the
-// other half, so V values take V - 1 + log2(64 / V) exchanges instead of
-// 6 V; a value's sum is the same tree whatever V is.  Returns the index of
-// the value whose sum ends in v[0] of this lane (lanes that differ in bits
-// below 64 / V hold the same one).
-template <int V, int OFF = 32, int H = V / 2>
-__device__ __forceinline__ int wave_sums(double (&v)[V]) {
-    if constexpr (OFF == 0) {
-        return 0;
-    } else if constexpr (H >= 1) {
-        const bool up = (threadIdx.x & OFF) != 0;
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const double hi = v[i + H], lo = v[i];
-            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, OFF, 64);
-        }
-        return (up ? H : 0) + wave_sums<V, OFF / 2, H / 2>(v);
-    } else {
-        v[0] += __shfl_xor(v[0], OFF, 64);
-        return wave_sums<V, OFF / 2, 0>(v);
-    }
-}
-
 // Two rows per workgroup (one for a single right-hand side, where more
 // workgroups hide the latency of the reads), whose 256 threads take the
 // columns 256 apart (a row segment of 4 KB per load); the right-hand sides

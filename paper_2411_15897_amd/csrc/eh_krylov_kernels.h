@@ -19,11 +19,19 @@ constexpr int KRY_MAXM = 32;   // columns handled by one pass
 // MODE 3: partial[0] = sum |w|^2
 // MODE 4: partial[i] = sum conj(V_i) w and partial[m + i] = sum conj(V_i) V_{m-1}
 //         (projections of w and the newest column of the Gram matrix V^H V)
-// grid: (nblk, nrhs); block b owns the KRY_E * 256 entries starting at
-// b * KRY_E * 256 (each thread KRY_E of them, 256 apart: coalesced).
+// grid: (nblk, nrhs); block b owns the E * 256 entries starting at
+// b * E * 256 (each thread E of them, 256 apart: coalesced).
 // partial layout [r][i][blk] (i < m, or 1 for norms); coef layout [r][i].
+// E entries per thread: KRY_E, or 1 on vectors so short that KRY_E would
+// leave most compute units idle (then the update's columns are loaded four
+// at a time instead).  The choice depends on n alone (kry_entries).
 constexpr int KRY_E = 4;
-template <int MODE>
+constexpr int64_t KRY_SHORT = 256 * KRY_E * KRY_THREADS;   // entries that give 256 workgroups
+__host__ __device__ constexpr int kry_entries(int64_t n) { return n < KRY_SHORT ? 1 : KRY_E; }
+__host__ __device__ constexpr int kry_blocks(int64_t n) {
+    return n < 1 ? 1 : (int)((n + kry_entries(n) * KRY_THREADS - 1) / (kry_entries(n) * KRY_THREADS));
+}
+template <int MODE, int E>
 __global__ void __launch_bounds__(KRY_THREADS)
 k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
      const c128* __restrict__ coef, c128* __restrict__ partial, c128* wout) {
@@ -31,27 +39,41 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
     const int r = blockIdx.y;
     const int nblk = gridDim.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * (KRY_E * KRY_THREADS) + threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (E * KRY_THREADS) + threadIdx.x;
     const c128* wr = w + (int64_t)r * n;
-    c128 wv[KRY_E];
+    c128 wv[E];
 #pragma unroll
-    for (int e = 0; e < KRY_E; ++e) {
+    for (int e = 0; e < E; ++e) {
         const int64_t p = base + e * KRY_THREADS;
         wv[e] = p < n ? wr[p] : mk(0.0, 0.0);
     }
     if (MODE == 1 || MODE == 2) {
-        for (int t = 0; t < m; ++t) {
+        constexpr int UT = E == 1 ? 4 : 1;         // columns in flight
+        int t = 0;
+        if (UT > 1) {
+            for (; t + UT <= m; t += UT) {
+                c128 vt[UT], cf[UT];
+#pragma unroll
+                for (int q = 0; q < UT; ++q) {
+                    cf[q] = coef[r * m + t + q];
+                    vt[q] = base < n ? V[((int64_t)(t + q) * nrhs + r) * n + base] : mk(0.0, 0.0);
+                }
+#pragma unroll
+                for (int q = 0; q < UT; ++q) wv[0] = wv[0] - cf[q] * vt[q];
+            }
+        }
+        for (; t < m; ++t) {
             const c128 cf = coef[r * m + t];
             const c128* Vt = V + ((int64_t)t * nrhs + r) * n;
 #pragma unroll
-            for (int e = 0; e < KRY_E; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const int64_t p = base + e * KRY_THREADS;
                 if (p < n) wv[e] = wv[e] - cf * Vt[p];
             }
         }
         c128* wo = wout + (int64_t)r * n;
 #pragma unroll
-        for (int e = 0; e < KRY_E; ++e) {
+        for (int e = 0; e < E; ++e) {
             const int64_t p = base + e * KRY_THREADS;
             if (p < n) wo[p] = wv[e];
         }
@@ -59,10 +81,10 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
     int mm = 1;
     if (MODE == 4) {
         mm = 2 * m;
-        c128 vl[KRY_E];
+        c128 vl[E];
         const c128* Vl = V + ((int64_t)(m - 1) * nrhs + r) * n;
 #pragma unroll
-        for (int e = 0; e < KRY_E; ++e) {
+        for (int e = 0; e < E; ++e) {
             const int64_t p = base + e * KRY_THREADS;
             vl[e] = p < n ? Vl[p] : mk(0.0, 0.0);
         }
@@ -70,7 +92,7 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
             const c128* Vt = V + ((int64_t)t * nrhs + r) * n;
             double ar = 0.0, ai = 0.0, gr = 0.0, gi = 0.0;
 #pragma unroll
-            for (int e = 0; e < KRY_E; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const int64_t p = base + e * KRY_THREADS;
                 if (p < n) {
                     const c128 v = t == m - 1 ? vl[e] : Vt[p];   // the newest column is in registers
@@ -97,7 +119,7 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
             const c128* Vt = V + ((int64_t)t * nrhs + r) * n;
             double ar = 0.0, ai = 0.0;
 #pragma unroll
-            for (int e = 0; e < KRY_E; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const int64_t p = base + e * KRY_THREADS;
                 if (p < n) {
                     const c128 v = Vt[p];
@@ -114,7 +136,7 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
     } else {
         double a = 0.0;
 #pragma unroll
-        for (int e = 0; e < KRY_E; ++e) a += wv[e].re * wv[e].re + wv[e].im * wv[e].im;
+        for (int e = 0; e < E; ++e) a += wv[e].re * wv[e].re + wv[e].im * wv[e].im;
         for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
         if (lane == 0) { lre[wave][0] = a; lim[wave][0] = 0.0; }
     }
@@ -293,18 +315,43 @@ k_arn_start(ArnState s, const c128* __restrict__ nrm, int first, double tol, Arn
 // [a_0..a_j, b_0..b_j]).  With h1_i = sv_i a_i and the Gram column
 // G_ij = sv_i sv_j b_i of the normalised basis, the reorthogonalised column
 // is hcol = h1 + V^H (w - V h1) = 2 h1 - G h1, and the update weight on the
-// stored column i is coef_i = sv_i hcol_i.  One block per RHS.
-__global__ void __launch_bounds__(64)
-k_arn_coef(ArnState s, int j, const c128* __restrict__ d1, c128* __restrict__ coef) {
-    __shared__ c128 h1[KRY_MAXM], gj[KRY_MAXM];
+// stored column i is coef_i = sv_i hcol_i.  One block per RHS; G is gathered
+// into LDS with every load in flight at once.  With nblk > 0 the pass's
+// partial sums of nblk workgroups ([r][2J][nblk]) are added up here instead
+// of by a launch of their own: up to ARN_FOLD workgroups, two loads per lane,
+// the 2J sums dealt to 16 wavefronts.  (64^2 solve, up to 20 columns: 8.1 us
+// per step in two launches before.)
+constexpr int ARN_FOLD = 128;
+constexpr int ARN_THREADS = 1024;
+__global__ void __launch_bounds__(ARN_THREADS)
+k_arn_coef(ArnState s, int j, const c128* __restrict__ d1, int nblk, c128* __restrict__ coef) {
+    __shared__ c128 h1[KRY_MAXM], gj[KRY_MAXM], dots[2 * KRY_MAXM];
+    __shared__ c128 G[KRY_MAXM][KRY_MAXM + 1];           // columns 0..j-1 as stored: G[q][i], i <= q
     const int r = blockIdx.x, i = threadIdx.x, J = j + 1, m = s.m;
     const double* sv = s.sv + r * (m + 1);
-    const c128* dr = d1 + (int64_t)r * 2 * J;
     c128* gram = s.gram + (int64_t)r * m * m;
+    for (int e = threadIdx.x; e < j * j; e += ARN_THREADS) {
+        const int q = e / j, k = e - q * j;
+        if (k <= q) G[q][k] = gram[(int64_t)q * m + k];
+    }
+    if (nblk > 0) {
+        const int lane = threadIdx.x & 63;
+        for (int e = threadIdx.x >> 6; e < 2 * J; e += ARN_THREADS / 64) {
+            const c128* pr = d1 + ((int64_t)r * 2 * J + e) * nblk;
+            const c128 a = lane < nblk ? pr[lane] : mk(0.0, 0.0);
+            const c128 b = lane + 64 < nblk ? pr[lane + 64] : mk(0.0, 0.0);
+            double v[2] = {a.re + b.re, a.im + b.im};
+            const int idx = wave_sums<2>(v);
+            if ((lane & 31) == 0) ((double*)&dots[e])[idx] = v[0];
+        }
+    } else if (i < 2 * J) {
+        dots[i] = d1[(int64_t)r * 2 * J + i];
+    }
+    __syncthreads();
     if (i < J) {
         const double si = sv[i];
-        h1[i] = si * dr[i];
-        gj[i] = (si * sv[j]) * dr[J + i];
+        h1[i] = si * dots[i];
+        gj[i] = (si * sv[j]) * dots[J + i];
         gram[(int64_t)j * m + i] = gj[i];
     }
     __syncthreads();
@@ -312,8 +359,8 @@ k_arn_coef(ArnState s, int j, const c128* __restrict__ d1, c128* __restrict__ co
         c128 gh = czero<double>();
         for (int q = 0; q < J; ++q) {
             c128 gi;   // G_iq: stored by column q (q >= i) or as conj of column i
-            if (q >= i) gi = (q == j) ? gj[i] : gram[(int64_t)q * m + i];
-            else gi = (i == j) ? cconj(gj[q]) : cconj(gram[(int64_t)i * m + q]);
+            if (q >= i) gi = (q == j) ? gj[i] : G[q][i];
+            else gi = (i == j) ? cconj(gj[q]) : cconj(G[i][q]);
             gh = gh + gi * h1[q];
         }
         const c128 hc = 2.0 * h1[i] - gh;
@@ -325,42 +372,68 @@ k_arn_coef(ArnState s, int j, const c128* __restrict__ d1, c128* __restrict__ co
 // Hessenberg column of step j: the earlier rotations, a new rotation that
 // zeroes the subdiagonal hn = ||w - V hcol|| (nrm[r] = hn^2), the residual
 // estimate, and the convergence / breakdown test.  The new column's scale
-// is 1/hn while the RHS stays active, 0 after.  One thread per RHS.
+// is 1/hn while the RHS stays active, 0 after.  One wavefront per RHS: lane
+// i holds entry i of the column and rotation i, the chain of rotations
+// passes its running entry along in registers (through memory it took 5 us
+// for 20 columns).  With nblk > 0 the norm's partial sums ([r][nblk], at
+// most NRM_FOLD) are added up here.
+constexpr int NRM_FOLD = 512;
+__device__ __forceinline__ double lane_get(double v, int l) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
 __global__ void __launch_bounds__(64)
-k_arn_givens(ArnState s, int j, const c128* __restrict__ nrm, ArnStatus* out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= s.nrhs) return;
+k_arn_givens(ArnState s, int j, const c128* __restrict__ nrm, int nblk, ArnStatus* out) {
+    const int r = blockIdx.x, lane = threadIdx.x;
     const int m = s.m;
     double* sv = s.sv + r * (m + 1);
-    ArnStatus st;
-    st.rel = -1.0;
-    st.done = s.done[r];
     if (!s.act[r]) {
-        sv[j + 1] = 0.0;
-        st.est = s.est[r];
-        st.active = 0;
-        st.its = s.its[r];
-        st.bad = 0;
-        out[r] = st;
+        if (lane == 0) {
+            ArnStatus st;
+            st.rel = -1.0;
+            st.done = s.done[r];
+            sv[j + 1] = 0.0;
+            st.est = s.est[r];
+            st.active = 0;
+            st.its = s.its[r];
+            st.bad = 0;
+            out[r] = st;
+        }
         return;
     }
-    const double hn = sqrt(fmax(nrm[r].re, 0.0));
-    c128* col = s.R + ((int64_t)r * m + j) * (m + 1);
+    double n2;
+    if (nblk > 0) {
+        double a = 0.0;
+#pragma unroll
+        for (int q = 0; q < NRM_FOLD / 64; ++q) {
+            const int b = lane + 64 * q;
+            a += b < nblk ? nrm[(int64_t)r * nblk + b].re : 0.0;
+        }
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+        n2 = a;
+    } else {
+        n2 = nrm[r].re;
+    }
+    const c128 h = lane <= j ? s.hcol[r * m + lane] : mk(0.0, 0.0);
+    const double ci_ = lane < j ? s.cs[r * m + lane] : 0.0;
+    const c128 si_ = lane < j ? s.sn[r * m + lane] : mk(0.0, 0.0);
+    c128* g = s.g + r * (m + 1);
+    const c128 gj = g[j];
+    const double hn = sqrt(fmax(n2, 0.0));
     double w0 = hn * hn;
-    for (int i = 0; i <= j; ++i) {
-        col[i] = s.hcol[r * m + i];
-        w0 += cabs2(col[i]);
+    c128 a = mk(lane_get(h.re, 0), lane_get(h.im, 0));   // the running entry
+    w0 += cabs2(a);
+    c128 mine = mk(0.0, 0.0);                            // entry `lane` of the rotated column
+    for (int i = 0; i < j; ++i) {
+        const c128 b = mk(lane_get(h.re, i + 1), lane_get(h.im, i + 1));
+        w0 += cabs2(b);
+        const double ci = lane_get(ci_, i);
+        const c128 si = mk(lane_get(si_.re, i), lane_get(si_.im, i));
+        const c128 t = ci * a + si * b;
+        if (lane == i) mine = t;
+        a = ci * b - cconj(si) * a;
     }
     w0 = sqrt(w0);
-    col[j + 1] = mk(hn, 0.0);
-    for (int i = 0; i < j; ++i) {
-        const double ci = s.cs[r * m + i];
-        const c128 si = s.sn[r * m + i];
-        const c128 a = col[i], b = col[i + 1];
-        col[i] = ci * a + si * b;
-        col[i + 1] = ci * b - cconj(si) * a;
-    }
-    const c128 a = col[j];
     const double aa = sqrt(cabs2(a));
     const double nu = sqrt(cabs2(a) + hn * hn);
     double ci;
@@ -372,23 +445,28 @@ k_arn_givens(ArnState s, int j, const c128* __restrict__ nrm, ArnStatus* out) {
         ci = aa / nu;
         si = (hn / (nu * aa)) * a;
     }
+    if (lane == j) mine = ci * a + si * mk(hn, 0.0);
+    c128* col = s.R + ((int64_t)r * m + j) * (m + 1);
+    if (lane <= j + 1) col[lane] = lane <= j ? mine : czero<double>();
+    if (lane != 0) return;
     s.cs[r * m + j] = ci;
     s.sn[r * m + j] = si;
-    col[j] = ci * a + si * col[j + 1];
-    col[j + 1] = czero<double>();
-    c128* g = s.g + r * (m + 1);
-    g[j + 1] = -1.0 * (cconj(si) * g[j]);
-    g[j] = ci * g[j];
+    const c128 gn = -1.0 * (cconj(si) * gj);
+    g[j + 1] = gn;
+    g[j] = ci * gj;
     s.jr[r] = j + 1;
     const int its = s.its[r] + 1;
     s.its[r] = its;
-    const double est = sqrt(cabs2(g[j + 1])) / s.bnorm[r];
+    const double est = sqrt(cabs2(gn)) / s.bnorm[r];
     s.est[r] = est;
     const int bad = !isfinite(est);
     const bool brk = hn <= 1e-14 * w0;
     const int act = !(est < s.tol[0] || brk || bad);
     s.act[r] = act;
     sv[j + 1] = act ? 1.0 / hn : 0.0;
+    ArnStatus st;
+    st.rel = -1.0;
+    st.done = s.done[r];
     st.est = est;
     st.active = act;
     st.its = its;
@@ -423,19 +501,26 @@ k_arn_compact(ArnState s, const int* __restrict__ map, int k) {
 }
 
 // End of a cycle: y = R^{-1} g over the jr[r] columns built (back
-// substitution on the rotated Hessenberg matrix).  One thread per RHS.
+// substitution on the rotated Hessenberg matrix).  One wavefront per RHS:
+// lane i holds g_i, and each y_q found is taken off the lanes above it, the
+// next column's loads in flight (23 us for 20 columns with one thread per
+// RHS).
 __global__ void __launch_bounds__(64)
 k_arn_solve(ArnState s) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= s.nrhs) return;
+    const int r = blockIdx.x, lane = threadIdx.x;
     const int m = s.m, jj = s.jr[r];
     const c128* R = s.R + (int64_t)r * m * (m + 1);
-    c128* y = s.y + r * m;
-    for (int i = jj - 1; i >= 0; --i) {
-        c128 acc = s.g[r * (m + 1) + i];
-        for (int q = i + 1; q < jj; ++q) acc = acc - R[(int64_t)q * (m + 1) + i] * y[q];
-        y[i] = cdiv(acc, R[(int64_t)i * (m + 1) + i]);
+    c128 acc = lane < jj ? s.g[r * (m + 1) + lane] : mk(0.0, 0.0);
+    c128 y = mk(0.0, 0.0);
+    c128 col = lane < jj ? R[(int64_t)(jj - 1) * (m + 1) + lane] : mk(0.0, 0.0);
+    for (int q = jj - 1; q >= 0; --q) {
+        const c128 cur = col;
+        if (q > 0) col = lane < q ? R[(int64_t)(q - 1) * (m + 1) + lane] : mk(0.0, 0.0);
+        const c128 yq = cdiv(mk(lane_get(acc.re, q), lane_get(acc.im, q)), mk(lane_get(cur.re, q), lane_get(cur.im, q)));
+        if (lane == q) y = yq;
+        else if (lane < q) acc = acc - cur * yq;
     }
+    if (lane < jj) s.y[r * m + lane] = y;
 }
 
 }  // namespace eh

@@ -86,12 +86,17 @@ struct OpArgs {
 // conj(V_t) . w and conj(V_t) . V_{J-1} over the workgroup's degrees of
 // freedom (each thread's faces and cell, then the wavefront butterfly, then
 // the four wavefronts in a fixed order), so w need not be read back for
-// them.  Partials [r][2J][workgroup]; k_reduce_partials adds them in a fixed
-// order.
+// them.  Partials [r][2J][workgroup]; k_reduce_partials (or k_arn_coef) adds
+// them in a fixed order.  On a grid of few tiles the columns are dealt to
+// several workgroups per tile, each forming w for itself (the first writes
+// it): one workgroup's columns follow one after the other.
 struct DotArgs {
     const c128* V;       // basis: column t of RHS r at V + t * vstep + r * (the output stride)
     int64_t vstep;
     int J;               // columns 0 .. J-1 (J <= KRY_MAXM)
+    int jc;              // columns per workgroup: chunk q of the columns goes to the workgroups
+                         // gridDim.z = q * (chunks of the batch) + chunk of the batch
+    int rchunks;         // chunks of the batch
     c128* partial;
 };
 
@@ -100,11 +105,14 @@ constexpr int OP_MAXJ = 32;
 
 // The DOTS epilogue for right-hand side r: the thread's NE degrees of
 // freedom (has[e], at index at[e] within a vector) with w values yk[e];
-// writes the workgroup's partials for columns t < J at workgroup index blk
-// of nt.  Called by every thread of the workgroup (two barriers).
+// writes the workgroup's partials for columns t0 <= t < t1 at workgroup
+// index blk of nt.  Called by every thread of the workgroup (two barriers).
+// Two columns at a time: their loads are in flight together and their eight
+// sums over the lanes take 10 exchanges (wave_sums) instead of 48.
 template <int NE>
 __device__ __forceinline__ void gs_first_pass(const DotArgs& da, int r, int64_t vs, const bool* has,
-                                              const int64_t* at, const c128* yk, int64_t blk, int64_t nt) {
+                                              const int64_t* at, const c128* yk, int64_t blk, int64_t nt, int t0,
+                                              int t1) {
     __shared__ double red[4][4 * OP_MAXJ];
     const int tid = threadIdx.x;
     const int J = da.J;
@@ -113,33 +121,38 @@ __device__ __forceinline__ void gs_first_pass(const DotArgs& da, int r, int64_t 
     c128 vl[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) vl[e] = has[e] ? Vl[at[e]] : mk(0.0, 0.0);
-    for (int t = 0; t < J; ++t) {
-        const c128* Vt = da.V + (int64_t)t * da.vstep + r * vs;
-        double ar = 0.0, ai = 0.0, gr = 0.0, gi = 0.0;
+    for (int t = t0; t < t1; t += 2) {
+        c128 v[2][NE];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const c128 v = t == J - 1 ? vl[e] : (has[e] ? Vt[at[e]] : mk(0.0, 0.0));
-            ar += v.re * yk[e].re + v.im * yk[e].im;
-            ai += v.re * yk[e].im - v.im * yk[e].re;
-            gr += v.re * vl[e].re + v.im * vl[e].im;
-            gi += v.re * vl[e].im - v.im * vl[e].re;
+        for (int q = 0; q < 2; ++q) {
+            const c128* Vt = da.V + (int64_t)(t + q) * da.vstep + r * vs;
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+                v[q][e] = t + q >= J - 1 ? vl[e] : (has[e] ? Vt[at[e]] : mk(0.0, 0.0));   // the newest is in registers
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            ar += __shfl_xor(ar, off, 64);
-            ai += __shfl_xor(ai, off, 64);
-            gr += __shfl_xor(gr, off, 64);
-            gi += __shfl_xor(gi, off, 64);
+        // (a second column past t1 is summed but not kept)
+        double sum[8];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            double ar = 0.0, ai = 0.0, gr = 0.0, gi = 0.0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                ar += v[q][e].re * yk[e].re + v[q][e].im * yk[e].im;
+                ai += v[q][e].re * yk[e].im - v[q][e].im * yk[e].re;
+                gr += v[q][e].re * vl[e].re + v[q][e].im * vl[e].im;
+                gi += v[q][e].re * vl[e].im - v[q][e].im * vl[e].re;
+            }
+            sum[4 * q] = ar;
+            sum[4 * q + 1] = ai;
+            sum[4 * q + 2] = gr;
+            sum[4 * q + 3] = gi;
         }
-        if (lane == 0) {
-            red[wave][4 * t] = ar;
-            red[wave][4 * t + 1] = ai;
-            red[wave][4 * t + 2] = gr;
-            red[wave][4 * t + 3] = gi;
-        }
+        const int idx = wave_sums<8>(sum);
+        if ((lane & 7) == 0 && t + idx / 4 < t1) red[wave][4 * t + idx] = sum[0];
     }
     __syncthreads();
-    if (tid < 2 * J) {
-        const int t = tid % J, g = tid / J;   // g = 0: conj(V_t) w, 1: conj(V_t) V_{J-1}
+    if (tid < 2 * (t1 - t0)) {
+        const int t = t0 + tid % (t1 - t0), g = tid / (t1 - t0);   // g = 0: conj(V_t) w, 1: conj(V_t) V_{J-1}
         const int q = 4 * t + 2 * g;
         const double sr = (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
         const double si = (red[0][q + 1] + red[1][q + 1]) + (red[2][q + 1] + red[3][q + 1]);
@@ -160,7 +173,9 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
     const int tx = tid % OTX, ty = tid / OTX;
     const int x0 = blockIdx.x * OTX, y0 = blockIdx.y * OTY;
     const int i = x0 + tx, j = y0 + ty;
-    const int rlo = blockIdx.z * rch, rhi = min(nrhs, rlo + rch);
+    const int zc = DOTS ? blockIdx.z % da.rchunks : blockIdx.z;   // chunk of the batch
+    const int t0 = DOTS ? blockIdx.z / da.rchunks * da.jc : 0;     // first column of this workgroup
+    const int rlo = zc * rch, rhi = min(nrhs, rlo + rch);
     const int n0 = o.dc.g[0], n1 = o.dc.g[1];
     const bool inx = i <= n0 && j <= n1;
     // staged entries of this thread: field offset + index, or -1 (zero)
@@ -247,7 +262,7 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
                 yv = ra.b[r * vs_out + o.off[a] + fp[a]] - yv;
                 rr += yv.re * yv.re + yv.im * yv.im;
             }
-            y[r * vs_out + o.off[a] + fp[a]] = yv;
+            if (!DOTS || t0 == 0) y[r * vs_out + o.off[a] + fp[a]] = yv;
             yk[a] = yv;
         }
         if (cell) {
@@ -256,7 +271,7 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
                 yv = ra.b[r * vs_out + o.off[2] + pc] - yv;
                 rr += yv.re * yv.re + yv.im * yv.im;
             }
-            y[r * vs_out + o.off[2] + pc] = yv;
+            if (!DOTS || t0 == 0) y[r * vs_out + o.off[2] + pc] = yv;
             yk[2] = yv;
         }
         if (RES) res_partial(ra, r, 0, rr);
@@ -264,7 +279,8 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
             const bool has[3] = {face[0], face[1], cell};
             const int64_t at[3] = {o.off[0] + fp[0], o.off[1] + fp[1], o.off[2] + pc};
             const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-            gs_first_pass<3>(da, r, vs_out, has, at, yk, blk, (int64_t)gridDim.x * gridDim.y);
+            gs_first_pass<3>(da, r, vs_out, has, at, yk, blk, (int64_t)gridDim.x * gridDim.y, t0,
+                             min(da.J, t0 + da.jc));
         }
     }
 }

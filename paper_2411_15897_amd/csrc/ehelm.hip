@@ -1837,11 +1837,17 @@ void apply_H(eh_ctx* c, const void* x, int64_t vx, c128* y, int64_t vy, int nrhs
 // column t of RHS r at V + t * vstep + r * ndof.  2D only: in 3D the plane
 // kernel with the pass folded in measured slower than the two launches
 // (192^3 x 4: 486 against 461 ms per solve for operator and Krylov work),
-// so there, and for more columns than the launch handles, it returns false
-// (nothing launched).
+// so there, and for more columns than the launch handles, it returns -1
+// (nothing launched).  At most ARN_FOLD workgroups leave their partial sums
+// in c->partial and their number is returned, else 0.
+//
+// Up to kDotWgs workgroups the columns are spread over workgroups, two or
+// more per workgroup: the 64^2 grid has 34 tiles and up to 20 columns (12 us
+// with one workgroup per tile).
 template <class Tin>
-bool apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int64_t vstep, int J, c128* d1) {
-    if (c->dim != 2 || J > OP_MAXJ) return false;
+int apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int64_t vstep, int J, c128* d1) {
+    if (c->dim != 2 || J > OP_MAXJ) return -1;
+    constexpr int kDotWgs = 512;
     double coefb = 8.0 * c->ncell;
     for (int k = 0; k < c->dim; ++k) coefb += (double)c->fsize[k] * (8.0 * c->dim + 16.0);
     Timed tm(c, KC_OPERATOR,
@@ -1860,15 +1866,20 @@ bool apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, in
     o.C = c->C;
     const dim3 g = op_grid(c);
     const int rch = rhs_chunk((int)(g.x * g.y * g.z), 1, nrhs);
-    const dim3 gc(g.x, g.y, g.z * (unsigned)((std::max(nrhs, 1) + rch - 1) / rch));
-    DotArgs da{V, vstep, J, c->partial};
+    const int rchunks = (std::max(nrhs, 1) + rch - 1) / rch;
+    const int wgs = (int)(g.x * g.y) * rchunks;
+    const int cmax = std::max(1, std::min((J + 1) / 2, kDotWgs / wgs));
+    const int jc = (J + cmax - 1) / cmax;
+    const dim3 gc(g.x, g.y, (unsigned)(rchunks * ((J + jc - 1) / jc)));
+    DotArgs da{V, vstep, J, jc, rchunks, c->partial};
     hipLaunchKernelGGL((k_op2_lds<Tin, false, true>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)z, w, nrhs,
                        c->ndof, c->ndof, ResArgs{}, rch, da);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce_partials, dim3(2 * J, nrhs), dim3(256), 0, c->s, (int)(g.x * g.y * g.z), 2 * J,
-                       nrhs, c->partial, d1);
+    const int nblk = (int)(g.x * g.y);
+    if (nblk <= ARN_FOLD) return nblk;
+    hipLaunchKernelGGL(k_reduce_partials, dim3(2 * J, nrhs), dim3(256), 0, c->s, nblk, 2 * J, nrhs, c->partial, d1);
     HIPCHK(hipGetLastError());
-    return true;
+    return 0;
 }
 
 // r = b - H x for nrhs complex128 vectors of stride ndof, and nrm[q] =
@@ -1995,7 +2006,9 @@ void ensure_krylov(eh_ctx* c, int nrhs, int m) {
     c->V = c->alloc<c128>((size_t)(m + 1) * nrhs * c->ndof);
     c->Z = c->alloc<char>((size_t)m * nrhs * c->ndof * c->csize());
     c->W = c->alloc<c128>((size_t)nrhs * c->ndof);
-    c->kry_nblk = (int)std::max<int64_t>(1, (c->ndof + KRY_E * KRY_THREADS - 1) / (KRY_E * KRY_THREADS));
+    // (a single block's vectors are shorter than ndof, but may take the
+    // short-vector form with more workgroups)
+    c->kry_nblk = std::max(kry_blocks(c->ndof), kry_blocks(std::min<int64_t>(c->ndof, KRY_SHORT - 1)));
     // Gram-Schmidt partials: the k_gs blocks, or the operator workgroups
     // where the 2D operator launch does the first pass
     c->partial = c->alloc<c128>((size_t)std::max(c->kry_nblk, op_blocks(c)) * nrhs * 2 * (m + 1));
@@ -2048,19 +2061,27 @@ void ensure_krylov(eh_ctx* c, int nrhs, int m) {
 }
 
 // Gram-Schmidt pass over columns [0, m): MODE as in k_gs.  coef/out are
-// device arrays [nrhs][m] (out: [nrhs][1] for norms).
+// device arrays [nrhs][m] (out: [nrhs][1] for norms).  When the pass has at
+// most `fold` workgroups its partial sums stay in c->partial for the next
+// kernel to add up, and their number is returned; else out gets the sums (0).
 template <int MODE>
-void gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w, const c128* coef, c128* out,
-             c128* wout = nullptr) {
-    const int nblk = (int)std::max<int64_t>(1, (n + KRY_E * KRY_THREADS - 1) / (KRY_E * KRY_THREADS));
+int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w, const c128* coef, c128* out,
+            c128* wout = nullptr, int fold = 0) {
+    const int nblk = kry_blocks(n);
     const double vecs = (MODE == 0 || MODE == 4) ? m + 1 : (MODE == 3 ? 1 : m + 2);
     Timed tm(c, KC_KRYLOV, vecs * nrhs * n * sizeof(c128));
-    hipLaunchKernelGGL((k_gs<MODE>), dim3(nblk, nrhs), dim3(KRY_THREADS), 0, c->s, n, m, nrhs, V, w,
-                       coef, c->partial, wout);
+    if (kry_entries(n) == 1)
+        hipLaunchKernelGGL((k_gs<MODE, 1>), dim3(nblk, nrhs), dim3(KRY_THREADS), 0, c->s, n, m, nrhs, V, w, coef,
+                           c->partial, wout);
+    else
+        hipLaunchKernelGGL((k_gs<MODE, KRY_E>), dim3(nblk, nrhs), dim3(KRY_THREADS), 0, c->s, n, m, nrhs, V, w, coef,
+                           c->partial, wout);
     HIPCHK(hipGetLastError());
+    if (nblk <= fold) return nblk;
     const int mm = (MODE == 0 || MODE == 1) ? m : (MODE == 4 ? 2 * m : 1);
     hipLaunchKernelGGL(k_reduce_partials, dim3(mm, nrhs), dim3(256), 0, c->s, nblk, mm, nrhs, c->partial, out);
     HIPCHK(hipGetLastError());
+    return 0;
 }
 
 // Flexible GMRES(m) with right preconditioning, x_0 = 0.  Every Arnoldi
@@ -2078,8 +2099,10 @@ void gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w
 //   op_z(z_j, W, nb)          W = X z_j for a preconditioned vector (multigrid precision)
 //   op_zd(z_j, W, nb, V, vstep, J, d1)
 //                             the same and the first Gram-Schmidt pass over
-//                             columns 0..J-1 into d1 from the same launch, or
-//                             false where the problem does not provide it
+//                             columns 0..J-1 from the same launch: 0 with the
+//                             sums in d1, the number of workgroups whose
+//                             partial sums are in c->partial, or -1 where the
+//                             problem does not provide it
 //   prec(v, sv, z_j, nb)      z_j = M (sv[q * (m+1)] v) per right-hand side q
 //   op_res(x, b, r, nrm, nb)  r = b - X x and nrm = |r|^2 in one pass, or false
 //                             where the problem does not provide it
@@ -2223,15 +2246,17 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec
             cplx<T>* Zj = Z + (int64_t)j * vstep;
             auto body = [&]() {
                 prec(Vj, S.sv + j, Zj, nb);
-                if (!op_zd(Zj, c->W, nb, c->V, vstep, j + 1, d1)) {
+                int fold = op_zd(Zj, c->W, nb, c->V, vstep, j + 1, d1);
+                if (fold < 0) {
                     op_z(Zj, c->W, nb);
-                    gs_pass<4>(c, n, j + 1, nb, c->V, c->W, nullptr, d1);
+                    fold = gs_pass<4>(c, n, j + 1, nb, c->V, c->W, nullptr, d1, nullptr, ARN_FOLD);
                 }
-                hipLaunchKernelGGL(k_arn_coef, dim3(nb), dim3(64), 0, c->s, S, j, (const c128*)d1, d2);
+                hipLaunchKernelGGL(k_arn_coef, dim3(nb), dim3(ARN_THREADS), 0, c->s, S, j,
+                                   (const c128*)(fold > 0 ? c->partial : d1), fold, d2);
                 HIPCHK(hipGetLastError());
-                gs_pass<2>(c, n, j + 1, nb, c->V, c->W, d2, d3, Vj + vstep);
-                hipLaunchKernelGGL(k_arn_givens, dim3(rgrid), dim3(64), 0, c->s, S, j, (const c128*)d3,
-                                   ds + (size_t)j * nrhs);
+                fold = gs_pass<2>(c, n, j + 1, nb, c->V, c->W, d2, d3, Vj + vstep, NRM_FOLD);
+                hipLaunchKernelGGL(k_arn_givens, dim3(nb), dim3(64), 0, c->s, S, j,
+                                   (const c128*)(fold > 0 ? c->partial : d3), fold, ds + (size_t)j * nrhs);
                 HIPCHK(hipGetLastError());
             };
             if (graphs && c->timer_mask == 0) {
@@ -2287,7 +2312,7 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec
             }
         }
         // x += Z y with y = R^-1 g of this cycle
-        hipLaunchKernelGGL(k_arn_solve, dim3(rgrid), dim3(64), 0, c->s, S);
+        hipLaunchKernelGGL(k_arn_solve, dim3(nb), dim3(64), 0, c->s, S);
         HIPCHK(hipGetLastError());
         {
             Timed tm(c, KC_KRYLOV, (double)nb * n * (2 * sizeof(c128) + steps * sizeof(cplx<T>)));
@@ -2383,7 +2408,7 @@ eh_status block_solve_impl(eh_ctx* c, int block, const c128* f, c128* x, int nrh
         gcycle<T>(c, kinds, 1, 0, fa, vf, out, vf, false, nb);
     };
     auto no_res = [](const c128*, const c128*, c128*, c128*, int) { return false; };
-    auto no_zd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, c128*) { return false; };
+    auto no_zd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, c128*) { return -1; };
     return fgmres_core<T>(c, n, op_x, op_z, no_zd, prec, false, f, x, nrhs, tol, maxit, info, no_res);
 }
 

@@ -1,0 +1,64 @@
+"""The Arnoldi step at the edges of its launch rules (needs an MI355X).
+
+Short vectors take one entry per thread and their columns four at a time;
+grids of few tiles deal the basis columns of the first Gram-Schmidt pass to
+several workgroups; few workgroups leave their partial sums to the
+coefficient and rotation kernels.  Each of these changes with the grid, the
+restart length and the batch, so solves on grids to both sides of every
+threshold are checked against the oracle's operator.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle.elastic import apply_H_stencil, medium_arrays
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_15897_amd import _native
+    _native.lib()
+
+
+@pytest.mark.parametrize("n,levels", [
+    ((16, 12), 1),          # one tile in x, four in y
+    ((64, 64), 3),          # 34 tiles: sums folded, columns over 10 workgroups
+    ((120, 168), 3),        # 86 tiles: folded, the norm's 238 sums too
+    ((136, 256), 3),        # 195 tiles: the first pass reduced by its own launch
+    ((288, 296), 4),        # the longest vectors still short, norm reduced by its own launch
+    ((304, 296), 4),        # the shortest of the others
+    ((12, 10, 8), 1),       # 3D: the pass is a launch of its own
+])
+@pytest.mark.parametrize("restart", [1, 2, 5, 32])
+def test_restart_lengths(n, levels, restart):
+    """Three sources, alone and batched: the true residual recomputed by the
+    oracle is below the tolerance, the Arnoldi estimate of the last step
+    equals it to 1e-10 (FP64 sums), and the batch gives each source bitwise
+    what it gets alone."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    d, h = len(n), tuple(1.0 for _ in n)
+    rng = np.random.default_rng(2)
+    vp = rng.uniform(2.0, 2.6, tuple(reversed(n)))
+    vs, rho = 0.5 * vp, np.ones_like(vp)
+    omega = W.omega_for_ppw(vs, h, 12.0)
+    sides = W.ABC_ALL[d]
+    s = ElasticHelmholtz(n, h, vp, vs, rho, omega, levels=levels, alpha=0.4, mg_precision=64, restart=restart,
+                         abc_width=4, abc_sides=sides)
+    src = [(d - 1, tuple(n[a] // 2 + q - 1 if a < d - 1 else n[a] // 2 for a in range(d))) for q in range(3)]
+    b = W.point_source_rhs(n, h, src)
+    tol = 1e-6
+    x, info = s.solve(torch.from_numpy(b).cuda(), tol=tol, maxit=600)
+    mu, lm, mass = medium_arrays(n, h, vp, vs, rho, omega, 4, sides)
+    for q in range(3):
+        xq = x[q].cpu().numpy()
+        rr = np.linalg.norm(b[q] - apply_H_stencil(n, h, mu, lm, mass, omega, xq)) / np.linalg.norm(b[q])
+        assert info[q]["converged"] and rr < tol
+        assert abs(info[q]["relres_est"] - rr) <= 1e-10
+        x1, i1 = s.solve(torch.from_numpy(b[q:q + 1]).cuda(), tol=tol, maxit=600)
+        assert i1[0]["iters"] == info[q]["iters"] and np.array_equal(x1[0].cpu().numpy(), xq)
+    s.close()
