@@ -18,9 +18,15 @@ void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrh
     const int rch = rhs_chunk(gx * gy, a.ns, nrhs);
     const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
     const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(a.ns * nch)), blk((unsigned)k.threads);
+    const bool pb = a.kind[0] == 2;
 #define EH_LFD(CF)                                                                               \
-    if (l == 0) hipLaunchKernelGGL((k_fdown<T, true, CF>), g, blk, 0, stream, a, nrhs, rch);     \
-    else hipLaunchKernelGGL((k_fdown<T, false, CF>), g, blk, 0, stream, a, nrhs, rch);
+    if (l == 0) {                                                                                \
+        if (pb) hipLaunchKernelGGL((k_fdown<T, true, CF, true>), g, blk, 0, stream, a, nrhs, rch);    \
+        else hipLaunchKernelGGL((k_fdown<T, true, CF, false>), g, blk, 0, stream, a, nrhs, rch);      \
+    } else {                                                                                     \
+        if (pb) hipLaunchKernelGGL((k_fdown<T, false, CF, true>), g, blk, 0, stream, a, nrhs, rch);   \
+        else hipLaunchKernelGGL((k_fdown<T, false, CF, false>), g, blk, 0, stream, a, nrhs, rch);     \
+    }
     switch (cfg) {
         case 0: EH_LFD(0) break;
         case 1: EH_LFD(1) break;
@@ -46,13 +52,15 @@ void launch_fup(hipStream_t stream, int nu_post, const GArgs<T>& a, int l, int c
     const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
     const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(a.ns * nch)), blk((unsigned)k.threads);
     const bool two = nu_post == 2;
-#define EH_LFU(CF)                                                                                    \
-    if (l == 0) {                                                                                     \
-        if (two) hipLaunchKernelGGL((k_fup<T, true, 2, CF>), g, blk, 0, stream, a, nrhs, rch);        \
-        else hipLaunchKernelGGL((k_fup<T, true, 1, CF>), g, blk, 0, stream, a, nrhs, rch);            \
-    } else {                                                                                          \
-        if (two) hipLaunchKernelGGL((k_fup<T, false, 2, CF>), g, blk, 0, stream, a, nrhs, rch);       \
-        else hipLaunchKernelGGL((k_fup<T, false, 1, CF>), g, blk, 0, stream, a, nrhs, rch);           \
+    const bool pb = a.kind[0] == 2;
+#define EH_LFU1(CF, FI, NU)                                                                            \
+    if (pb) hipLaunchKernelGGL((k_fup<T, FI, NU, CF, true>), g, blk, 0, stream, a, nrhs, rch);         \
+    else hipLaunchKernelGGL((k_fup<T, FI, NU, CF, false>), g, blk, 0, stream, a, nrhs, rch);
+#define EH_LFU(CF)                                                                                     \
+    if (l == 0) {                                                                                      \
+        if (two) { EH_LFU1(CF, true, 2) } else { EH_LFU1(CF, true, 1) }                                \
+    } else {                                                                                           \
+        if (two) { EH_LFU1(CF, false, 2) } else { EH_LFU1(CF, false, 1) }                              \
     }
     switch (cfg) {
         case 0: EH_LFU(0) break;
@@ -61,6 +69,7 @@ void launch_fup(hipStream_t stream, int nu_post, const GArgs<T>& a, int l, int c
         default: EH_LFU(3) break;
     }
 #undef EH_LFU
+#undef EH_LFU1
 }
 
 template void launch_fup<EH_T>(hipStream_t, int, const GArgs<EH_T>&, int, int, int);
