@@ -9,7 +9,6 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
-#include <complex>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -321,219 +320,62 @@ struct Timed {
 };
 
 // ---------------------------------------------------------------------------
-// setup on the host (FP64)
+// setup
 
-struct HostMedium {
-    std::vector<double> mu, lm, rho, gamma;
-    std::vector<std::complex<double>> m;   // rho (1 - i gamma/w), unshifted
-};
-
-int64_t cidx(const eh_ctx* c, int i, int j, int k) {
-    return ((int64_t)k * c->n[1] + j) * c->n[0] + i;
-}
-
-// gamma = gamma0 + w * sum_a l_a^2, l_a = max(0, W - d_a)/W, d_a the distance
-// (cells, centre to side) to the nearest absorbing side along axis a
-// (Section 4: a layer of gradually increasing attenuation).
-double abc_gamma(const eh_ctx* c, int i, int j, int k) {
-    const int idx[3] = {i, j, k};
-    double g = c->o.gamma0;
-    const int W = c->o.abc_width;
-    if (W <= 0) return g;
-    for (int a = 0; a < c->dim; ++a) {
-        double d = 1e300;
-        if (c->o.abc_sides & (1u << (2 * a))) d = std::min(d, idx[a] + 0.5);
-        if (c->o.abc_sides & (1u << (2 * a + 1))) d = std::min(d, c->n[a] - idx[a] - 0.5);
-        const double l = std::max(0.0, W - d) / W;
-        g += c->omega * l * l;
+MediumArgs medium_args(const eh_ctx* c) {
+    MediumArgs a{};
+    a.dim = c->dim;
+    for (int x = 0; x < 3; ++x) {
+        a.n[x] = (int)c->n[x];
+        a.h[x] = c->h[x];
     }
-    return g;
+    a.omega = c->omega;
+    a.gamma0 = c->o.gamma0;
+    a.abc_width = c->o.abc_width;
+    a.abc_sides = c->o.abc_sides;
+    return a;
 }
 
-// Mean of mu over the existing cells around the location whose nodal axes
-// are `nodal` (bit mask) at location index (li, lj, lk).
-double mu_mean(const eh_ctx* c, const HostMedium& M, int nodal, int li, int lj, int lk) {
-    const int L[3] = {li, lj, lk};
-    int lo[3], hi[3];
-    for (int a = 0; a < 3; ++a) {
-        if (a < c->dim && (nodal & (1 << a))) { lo[a] = L[a] - 1; hi[a] = L[a]; }
-        else { lo[a] = L[a]; hi[a] = L[a]; }
-    }
-    double s = 0.0;
-    int cnt = 0;
-    for (int z = lo[2]; z <= hi[2]; ++z)
-        for (int y = lo[1]; y <= hi[1]; ++y)
-            for (int x = lo[0]; x <= hi[0]; ++x) {
-                if (x < 0 || y < 0 || z < 0 || x >= c->n[0] || y >= c->n[1] || z >= c->n[2]) continue;
-                s += M.mu[cidx(c, x, y, z)];
-                ++cnt;
-            }
-    return s / cnt;
+double* upload_cells(eh_ctx* c, const double* v) {
+    double* p = c->alloc<double>((size_t)c->ncell);
+    HIPCHK(hipMemcpy(p, v, (size_t)c->ncell * sizeof(double), hipMemcpyHostToDevice));
+    return p;
 }
 
-// Fine-level acoustic block A_k on the k-faces: couplings w_a (between a
-// face and its +e_a neighbour) and the diagonal, from grad_h^T A_e(mu) grad_h
-// - w^2 A_f(m) (eq. mixed-discretized); alpha shifts the mass (eq. shift).
-void build_Ak(const eh_ctx* c, const HostMedium& M, int kb, double alpha,
-              std::vector<double> w[3], std::vector<std::complex<double>>& D) {
-    const Dims& d = c->dface[kb];
-    const int64_t np = d.np();
-    for (int a = 0; a < c->dim; ++a) w[a].assign(np, 0.0);
-    D.assign(np, 0.0);
-    const double om2 = c->omega * c->omega;
-    for (int z = 0; z < d.g[2]; ++z)
-        for (int y = 0; y < d.g[1]; ++y)
-            for (int x = 0; x < d.g[0]; ++x) {
-                const int64_t p = ((int64_t)z * d.g[1] + y) * d.g[0] + x;
-                const int P[3] = {x, y, z};
-                double stiff = 0.0;
-                for (int a = 0; a < c->dim; ++a) {
-                    const double ih2 = 1.0 / (c->h[a] * c->h[a]);
-                    if (a == kb) {
-                        // derivative along the nodal axis lands on cells P[a]-1 and P[a]
-                        int q[3] = {x, y, z};
-                        if (P[a] < c->n[a]) {
-                            const double m = M.mu[cidx(c, q[0], q[1], q[2])] * ih2;
-                            w[a][p] = m;
-                            stiff += m;
-                        }
-                        if (P[a] >= 1) {
-                            q[a] = P[a] - 1;
-                            stiff += M.mu[cidx(c, q[0], q[1], q[2])] * ih2;
-                        }
-                    } else {
-                        // derivative along a cell-centred axis lands on edges at
-                        // node indices P[a] and P[a]+1 (zero ghost outside)
-                        const int nm = (1 << kb) | (1 << a);
-                        int q[3] = {x, y, z};
-                        const double m0 = mu_mean(c, M, nm, q[0], q[1], q[2]) * ih2;
-                        q[a] = P[a] + 1;
-                        const double m1 = mu_mean(c, M, nm, q[0], q[1], q[2]) * ih2;
-                        stiff += m0 + m1;
-                        if (P[a] + 1 < d.g[a]) w[a][p] = m1;
-                    }
-                }
-                // face mass: mean of the existing cells on both sides along kb
-                std::complex<double> mf = 0.0;
-                int cnt = 0;
-                for (int off = -1; off <= 0; ++off) {
-                    int q[3] = {x, y, z};
-                    q[kb] += off;
-                    if (q[kb] < 0 || q[kb] >= c->n[kb]) continue;
-                    const int64_t ci = cidx(c, q[0], q[1], q[2]);
-                    mf += M.rho[ci] * std::complex<double>(1.0, -(M.gamma[ci] / c->omega + alpha));
-                    ++cnt;
-                }
-                mf /= double(cnt);
-                D[p] = stiff - om2 * mf;
-            }
-}
-
-// Fine-level H_p on the cells: H_p = B B^T diag(w) - w^2 diag(m/(lambda+mu)),
-// w = (lambda + 2 mu)/(lambda + mu) (eqs. Ap, Hp); alpha shifts m.
-void build_Hp(const eh_ctx* c, const HostMedium& M, double alpha, std::vector<double>& w,
-              std::vector<std::complex<double>>& D) {
-    const int64_t nc = c->ncell;
-    w.assign(nc, 0.0);
-    D.assign(nc, 0.0);
-    double sum_ih2 = 0.0;
-    for (int a = 0; a < c->dim; ++a) sum_ih2 += 2.0 / (c->h[a] * c->h[a]);
-    const double om2 = c->omega * c->omega;
-    for (int64_t q = 0; q < nc; ++q) {
-        w[q] = 1.0 + M.mu[q] / M.lm[q];
-        const std::complex<double> ms = M.rho[q] * std::complex<double>(1.0, -(M.gamma[q] / c->omega + alpha));
-        D[q] = w[q] * sum_ih2 - om2 * ms / M.lm[q];
-    }
-}
-
+// Fine-level operator of a block on the device: the coefficients of H
+// (shear blocks), the shifted operator in the multigrid precision and, for
+// the Galerkin products, as an FP64 stencil (returned; the caller releases
+// it).
 template <class T>
-void upload_real(eh_ctx* c, void** dst, const std::vector<double>& v) {
-    std::vector<T> t(v.begin(), v.end());
-    T* p = c->alloc<T>(t.size());
-    HIPCHK(hipMemcpy(p, t.data(), t.size() * sizeof(T), hipMemcpyHostToDevice));
-    *dst = p;
-}
-
-template <class T>
-void upload_cplx(eh_ctx* c, void** dst, const std::vector<std::complex<double>>& v) {
-    std::vector<cplx<T>> t(v.size());
-    for (size_t q = 0; q < v.size(); ++q) t[q] = mk<T>(T(v[q].real()), T(v[q].imag()));
-    cplx<T>* p = c->alloc<cplx<T>>(t.size());
-    HIPCHK(hipMemcpy(p, t.data(), t.size() * sizeof(cplx<T>), hipMemcpyHostToDevice));
-    *dst = p;
-}
-
-// FP64 stencil (half widths 1) of a fine block for the Galerkin setup.
-// H_p with the Remark's A~_p = B A_f(mu) B^T - w^2 M_p in place of A_p:
-// H~_p = B B^T + A~_p C.  Across the face between cell c and its neighbour
-// nb along axis a the coupling is (1 + mu_f / (lambda+mu)_nb) / h_a^2, mu_f
-// the mean of the face's existing cells (a boundary face has one); the
-// diagonal collects (1 + mu_f / (lambda+mu)_c) / h_a^2 over the cell's
-// faces and the shifted mass / (lambda+mu)_c.  wpm[a] holds the pair
-// (coupling to c + e_a, to c - e_a) per cell.
-void build_Hp_tilde(const eh_ctx* c, const HostMedium& M, double alpha, std::vector<double> wpm[3],
-                    std::vector<std::complex<double>>& D) {
-    const Dims& d = c->dcell;
-    const int64_t nc = c->ncell;
-    const int64_t st[3] = {1, d.g[0], (int64_t)d.g[0] * d.g[1]};
-    for (int a = 0; a < c->dim; ++a) wpm[a].assign(2 * nc, 0.0);
-    D.assign(nc, 0.0);
-    const double om2 = c->omega * c->omega;
-    for (int64_t q = 0; q < nc; ++q) {
-        const int P[3] = {(int)(q % d.g[0]), (int)((q / d.g[0]) % d.g[1]), (int)(q / st[2])};
-        double diag = 0.0;
-        for (int a = 0; a < c->dim; ++a) {
-            const double ih2 = 1.0 / (c->h[a] * c->h[a]);
-            const bool hi = P[a] + 1 < d.g[a], lo = P[a] > 0;
-            const double mhi = hi ? 0.5 * (M.mu[q] + M.mu[q + st[a]]) : M.mu[q];
-            const double mlo = lo ? 0.5 * (M.mu[q] + M.mu[q - st[a]]) : M.mu[q];
-            if (hi) wpm[a][2 * q] = (1.0 + mhi / M.lm[q + st[a]]) * ih2;
-            if (lo) wpm[a][2 * q + 1] = (1.0 + mlo / M.lm[q - st[a]]) * ih2;
-            diag += (2.0 + (mlo + mhi) / M.lm[q]) * ih2;
-        }
-        const std::complex<double> ms = M.rho[q] * std::complex<double>(1.0, -(M.gamma[q] / c->omega + alpha));
-        D[q] = diag - om2 * ms / M.lm[q];
-    }
-}
-
-std::vector<c128> fine_stencil(const eh_ctx* c, const Block& B, const std::vector<double> w[3],
-                               const std::vector<std::complex<double>>& D) {
-    const bool tilde = B.kind == c->dim && c->o.ap_variant == 1;
-    const Dims& d = B.lev[0].d;
+c128* build_fine(eh_ctx* c, Block& B) {
+    const MediumArgs ma = medium_args(c);
+    const Dims d = B.lev[0].d;
     const int64_t np = d.np();
-    Widths wd{{1, 1, c->dim == 3 ? 1 : 0}};
-    const int nst = wd.nst();
-    std::vector<c128> st((size_t)nst * np, mk(0.0, 0.0));
-    const int NX = 3, NY = 3;
-    auto put = [&](int ox, int oy, int oz, int64_t p, double v) {
-        const int o = ((oz + wd.w[2]) * NY + (oy + 1)) * NX + (ox + 1);
-        st[(size_t)o * np + p] = mk(v, 0.0);
-    };
-    const int64_t stride[3] = {1, d.g[0], (int64_t)d.g[0] * d.g[1]};
-    for (int z = 0; z < d.g[2]; ++z)
-        for (int y = 0; y < d.g[1]; ++y)
-            for (int x = 0; x < d.g[0]; ++x) {
-                const int64_t p = ((int64_t)z * d.g[1] + y) * d.g[0] + x;
-                const int P[3] = {x, y, z};
-                const int o = ((0 + wd.w[2]) * NY + 1) * NX + 1;
-                st[(size_t)o * np + p] = mk(D[p].real(), D[p].imag());
-                for (int a = 0; a < c->dim; ++a) {
-                    int e[3] = {0, 0, 0};
-                    e[a] = 1;
-                    const double ih2 = 1.0 / (c->h[a] * c->h[a]);
-                    if (P[a] + 1 < d.g[a]) {
-                        const double v = tilde ? w[a][2 * p]
-                                               : (B.kind < c->dim) ? w[a][p] : w[0][p + stride[a]] * ih2;
-                        put(e[0], e[1], e[2], p, -v);
-                    }
-                    if (P[a] >= 1) {
-                        const double v = tilde ? w[a][2 * p + 1]
-                                               : (B.kind < c->dim) ? w[a][p - stride[a]] : w[0][p - stride[a]] * ih2;
-                        put(-e[0], -e[1], -e[2], p, -v);
-                    }
-                }
-            }
-    return st;
+    const bool P = B.kind == c->dim;
+    FineOut<T> out{};
+    const int nfw = P && c->o.ap_variant == 0 ? 1 : c->dim;
+    for (int a = 0; a < nfw; ++a) {
+        out.fw[a] = c->alloc<T>((size_t)np * (P && c->o.ap_variant == 1 ? 2 : 1));
+        B.fw[a] = out.fw[a];
+    }
+    out.fD = c->alloc<cplx<T>>((size_t)np);
+    B.fD = out.fD;
+    out.st = c->alloc<c128>((size_t)(c->dim == 3 ? 27 : 9) * np);
+    const dim3 g((unsigned)((np + 255) / 256)), blk(256);
+    if (!P) {
+        for (int a = 0; a < c->dim; ++a) out.w[a] = c->k1w[B.kind][a] = c->alloc<double>((size_t)np);
+        out.D = c->k1D[B.kind] = c->alloc<c128>((size_t)np);
+        hipLaunchKernelGGL((k_galerkin_shear<T>), g, blk, 0, 0, ma, B.kind, c->o.alpha, d, (const double*)c->mu,
+                           (const double*)c->d_rho, (const double*)c->d_gamma, out);
+    } else if (c->o.ap_variant == 1) {
+        hipLaunchKernelGGL((k_galerkin_pressure<T, true>), g, blk, 0, 0, ma, c->o.alpha, (const double*)c->mu,
+                           (const double*)c->d_lm, (const double*)c->d_rho, (const double*)c->d_gamma, out);
+    } else {
+        hipLaunchKernelGGL((k_galerkin_pressure<T, false>), g, blk, 0, 0, ma, c->o.alpha, (const double*)c->mu,
+                           (const double*)c->d_lm, (const double*)c->d_rho, (const double*)c->d_gamma, out);
+    }
+    HIPCHK(hipGetLastError());
+    return out.st;
 }
 
 // Scratch of the coarsest factorisation: n x n FP64 matrices handed out and
@@ -1052,13 +894,13 @@ void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& 
     }
 }
 
-// Galerkin hierarchy (FP64 on the device); the coarsest operator's stencil
-// and widths are returned (the caller releases it).
-void build_hierarchy(eh_ctx* c, Block& B, const std::vector<c128>& st0, c128*& coarsest, Widths& wcoarsest) {
+// Galerkin hierarchy (FP64 on the device) from the fine stencil st0, which is
+// released; the coarsest operator's stencil and widths are returned (the
+// caller releases it).
+void build_hierarchy(eh_ctx* c, Block& B, c128* st0, c128*& coarsest, Widths& wcoarsest) {
     const int L = (int)B.lev.size();
     const bool f32 = c->o.mg_precision == 32;
-    c128* prev = c->alloc<c128>(st0.size());
-    HIPCHK(hipMemcpy(prev, st0.data(), st0.size() * sizeof(c128), hipMemcpyHostToDevice));
+    c128* prev = st0;
     Widths wprev{{1, 1, c->dim == 3 ? 1 : 0}};
     int* overflow = c->alloc<int>(1);
     HIPCHK(hipMemset(overflow, 0, sizeof(int)));
@@ -2661,34 +2503,19 @@ eh_status eh_create(eh_ctx** out, int dim, const int64_t* n, const double* h, co
         c->fsize[dim] = ncell;
         c->ndof = acc + ncell;
         c->nblocks = dim + 1;
-        // medium
-        HostMedium M;
-        M.mu.resize(ncell); M.lm.resize(ncell); M.rho.resize(ncell); M.gamma.resize(ncell); M.m.resize(ncell);
-        for (int z = 0; z < c->n[2]; ++z)
-            for (int y = 0; y < c->n[1]; ++y)
-                for (int x = 0; x < c->n[0]; ++x) {
-                    const int64_t q = cidx(c, x, y, z);
-                    M.mu[q] = rho[q] * vs[q] * vs[q];
-                    M.lm[q] = rho[q] * (vp[q] * vp[q] - vs[q] * vs[q]);
-                    M.rho[q] = rho[q];
-                    M.gamma[q] = abc_gamma(c, x, y, z);
-                    M.m[q] = rho[q] * std::complex<double>(1.0, -M.gamma[q] / omega);
-                }
-        // FP64 arrays for H, the distributor and the gradient
-        {
-            std::vector<double> Cv(ncell);
-            for (int64_t q = 0; q < ncell; ++q) Cv[q] = 1.0 / M.lm[q];
-            upload_real<double>(c, (void**)&c->C, Cv);
-            upload_real<double>(c, (void**)&c->mu, M.mu);
-            upload_cplx<double>(c, (void**)&c->mcell, M.m);
-            upload_real<double>(c, (void**)&c->d_rho, M.rho);
-            upload_real<double>(c, (void**)&c->d_gamma, M.gamma);
-            upload_real<double>(c, (void**)&c->d_lm, M.lm);
-            std::vector<double> tmp(vp, vp + ncell);
-            upload_real<double>(c, (void**)&c->d_vp, tmp);
-            tmp.assign(vs, vs + ncell);
-            upload_real<double>(c, (void**)&c->d_vs, tmp);
-        }
+        // medium: cell arrays for H, the distributor and the gradient
+        c->d_vp = upload_cells(c, vp);
+        c->d_vs = upload_cells(c, vs);
+        c->d_rho = upload_cells(c, rho);
+        c->mu = c->alloc<double>((size_t)ncell);
+        c->d_lm = c->alloc<double>((size_t)ncell);
+        c->C = c->alloc<double>((size_t)ncell);
+        c->d_gamma = c->alloc<double>((size_t)ncell);
+        c->mcell = c->alloc<c128>((size_t)ncell);
+        hipLaunchKernelGGL(k_galerkin_medium, dim3((unsigned)((ncell + 255) / 256)), dim3(256), 0, 0, medium_args(c),
+                           (const double*)c->d_vp, (const double*)c->d_vs, (const double*)c->d_rho, c->mu, c->d_lm,
+                           c->C, c->d_gamma, c->mcell);
+        HIPCHK(hipGetLastError());
         const bool f32 = o.mg_precision == 32;
         c128* cst[4] = {nullptr, nullptr, nullptr, nullptr};   // coarsest stencils
         Widths cw[4] = {};
@@ -2706,32 +2533,7 @@ eh_status eh_create(eh_ctx** out, int dim, const int64_t* n, const double* h, co
                 B.lev[l].d = d;
                 B.lev[l].damp = o.damping[std::min(l, o.n_damping - 1)];
             }
-            std::vector<double> w[3];
-            std::vector<std::complex<double>> D, D0;
-            if (b < dim) {
-                build_Ak(c, M, b, o.alpha, w, D);
-                std::vector<double> w0[3];
-                build_Ak(c, M, b, 0.0, w0, D0);
-                for (int a = 0; a < dim; ++a) upload_real<double>(c, (void**)&c->k1w[b][a], w0[a]);
-                upload_cplx<double>(c, (void**)&c->k1D[b], D0);
-                for (int a = 0; a < dim; ++a) {
-                    if (f32) upload_real<float>(c, &B.fw[a], w[a]);
-                    else upload_real<double>(c, &B.fw[a], w[a]);
-                }
-            } else if (o.ap_variant == 1) {
-                build_Hp_tilde(c, M, o.alpha, w, D);
-                for (int a = 0; a < dim; ++a) {
-                    if (f32) upload_real<float>(c, &B.fw[a], w[a]);
-                    else upload_real<double>(c, &B.fw[a], w[a]);
-                }
-            } else {
-                build_Hp(c, M, o.alpha, w[0], D);
-                if (f32) upload_real<float>(c, &B.fw[0], w[0]);
-                else upload_real<double>(c, &B.fw[0], w[0]);
-            }
-            if (f32) upload_cplx<float>(c, &B.fD, D);
-            else upload_cplx<double>(c, &B.fD, D);
-            const std::vector<c128> st0 = fine_stencil(c, B, w, D);
+            c128* st0 = f32 ? build_fine<float>(c, B) : build_fine<double>(c, B);
             build_hierarchy(c, B, st0, cst[b], cw[b]);
         }
         if (c->use_bt) {
