@@ -714,12 +714,20 @@ __device__ __forceinline__ void up_body_coarse(const GArgs<T>& a, int slot, cplx
                 const int l = (rby + WY) * AX + (rbx + WX);
                 cplx<T> v = czero<T>();
                 if (ring && RING_LDS) {
-                    // the same PointOp code as every other point, fed from LDS
-                    PointOp<T, false, 0, WX, WY, HALF> wop;
+                    // the sum of PointOp::apply in its order, one stencil row
+                    // at a time: held all at once next to the own point's,
+                    // the ring point's coefficients set the kernel's registers
+                    cplx<T> xu = czero<T>();
+                    const cplx<T>* rc = RC + threadIdx.x;
+                    const cplx<T>* sr = A + l - WY * AX - WX;
+#pragma unroll 1
+                    for (int oy = 0; oy < 2 * WY + 1; ++oy) {
 #pragma unroll
-                    for (int o = 0; o < NST; ++o) wop.cf[o] = RC[o * RING + threadIdx.x];
-                    wop.sc = rsc;
-                    v = wop.template sweep<AX>(A, l, fring);
+                        for (int ox = 0; ox < 2 * WX + 1; ++ox) xu = cfma(rc[ox * RING], sr[ox], xu);
+                        rc += (2 * WX + 1) * RING;
+                        sr += AX;
+                    }
+                    v = cfma(rsc, fring - xu, A[l]);
                 } else if (ring) {
                     PointOp<T, false, 0, WX, WY, HALF> wop;
                     wop.load(a, slot, d, rgx, rgy, rp);
@@ -738,8 +746,14 @@ __device__ __forceinline__ void up_body_coarse(const GArgs<T>& a, int slot, cplx
     }
 }
 
+// Wavefronts per SIMD the up leg's registers leave room for: the shear
+// blocks' coarse legs come out two registers above the line of four.
+template <class T, bool FINE, int CFG, bool PB>
+constexpr int fup_waves() {
+    return !FINE && !PB && sizeof(T) == 4 && kFUp[CFG].threads <= 256 ? 4 : 1;
+}
 template <class T, bool FINE, int NU2, int CFG, bool PB>
-__global__ void __launch_bounds__(kFUp[CFG].threads)
+__global__ void __launch_bounds__(kFUp[CFG].threads, (fup_waves<T, FINE, CFG, PB>()))
 k_fup(GArgs<T> a, int nrhs, int rch) {
     constexpr int TX = kFUp[CFG].x, TY = kFUp[CFG].y, NT = kFUp[CFG].threads;
     // every stencil shape the block's coarse levels use: 5x5 and 3x3 (H_p),
