@@ -232,49 +232,43 @@ __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* 
             }
         }
     }
-    // Fine level: every global load of one right-hand side (the staged
-    // points and the support points' f) is issued together without branches
-    // (a point outside reads element 0 and is zeroed).
-    constexpr int NUF = FINE ? NU : 1, NRF = FINE ? NR : 1;
-    cplx<T> inu[NUF], inr[NRF], in_fr = czero<T>();
+    // One right-hand side's inputs (the staged points and, where one thread
+    // has one or its operators are held, the support points' f), loaded
+    // without branches (a point outside reads element 0 and is zeroed).  On
+    // coarse levels the next right-hand side's are in flight while this one
+    // is computed (level 1 of a 2048^2 batch of 8: 160 -> 123 us for the
+    // shear blocks, 128 -> 102 for H_p); the fine legs, bound by instruction
+    // issue with enough wavefronts to hide the loads, lose by it (the H_p leg
+    // at 1024^2 12 -> 17 us).
+    constexpr int NRF = HOLD ? NR : 1;
+    cplx<T> inu[NU], inr[NRF], in_fr = czero<T>();
     auto load_in = [&](int r) {
         const cplx<T>* __restrict__ f = a.f[slot] + r * a.vf[slot];
 #pragma unroll
-        for (int it = 0; it < NUF; ++it) inu[it] = f[up_[it] >= 0 ? up_[it] : 0];
+        for (int it = 0; it < NU; ++it) inu[it] = f[up_[it] >= 0 ? up_[it] : 0];
         if (HOLD) {
 #pragma unroll
             for (int it = 0; it < NRF; ++it) inr[it] = f[hp[it] >= 0 ? hp[it] : 0];
         }
-        in_fr = f[rin ? rp : 0];
+        if (ONE_R) in_fr = f[rin ? rp : 0];
     };
+    if (!FINE) load_in(r0);
     for (int r = r0; r < r1; ++r) {
         const cplx<T>* __restrict__ f = a.f[slot] + r * a.vf[slot];
-        cplx<T> fr;
+        if (FINE) load_in(r);
+        const cplx<T> fr = rin ? in_fr : czero<T>();
         cplx<T> fhold[NRF];
-        if constexpr (FINE) {
-            load_in(r);
-            fr = rin ? in_fr : czero<T>();
 #pragma unroll
-            for (int it = 0; it < NRF; ++it) fhold[it] = inr[it];
-            if (r > r0) lds_barrier();                  // LDS of the previous RHS consumed
+        for (int it = 0; it < NRF; ++it) fhold[it] = HOLD ? inr[it] : czero<T>();
+        if (r > r0) lds_barrier();                  // LDS of the previous RHS consumed
 #pragma unroll
-            for (int it = 0; it < NU; ++it) {
-                const int q = threadIdx.x + it * NT;
-                if (q >= UX * UY) break;
-                U[q] = up_[it] >= 0 ? usc[it] * inu[it] : czero<T>();
-            }
-            lds_barrier();
-        } else {
-            fr = rin ? f[rp] : czero<T>();
-            if (r > r0) lds_barrier();                  // LDS of the previous RHS consumed
-#pragma unroll
-            for (int it = 0; it < NU; ++it) {
-                const int q = threadIdx.x + it * NT;
-                if (q >= UX * UY) break;
-                U[q] = up_[it] >= 0 ? usc[it] * f[up_[it]] : czero<T>();
-            }
-            lds_barrier();
+        for (int it = 0; it < NU; ++it) {
+            const int q = threadIdx.x + it * NT;
+            if (q >= UX * UY) break;
+            U[q] = up_[it] >= 0 ? usc[it] * inu[it] : czero<T>();
         }
+        if (!FINE && r + 1 < r1) load_in(r + 1);
+        lds_barrier();
         if (ONE_R) {
             if ((int)threadIdx.x < RX * RY)
                 RR[threadIdx.x] =
