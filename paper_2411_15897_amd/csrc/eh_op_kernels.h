@@ -98,6 +98,7 @@ struct DotArgs {
                          // gridDim.z = q * (chunks of the batch) + chunk of the batch
     int rchunks;         // chunks of the batch
     c128* partial;
+    const c128* coef;    // second pass: [r][J]
 };
 
 constexpr int OTX = 64, OTY = 4;
@@ -160,10 +161,56 @@ __device__ __forceinline__ void gs_first_pass(const DotArgs& da, int r, int64_t 
     }
     __syncthreads();   // red is reused by the next right-hand side
 }
-template <class Tin, bool RES, bool DOTS = false>
+
+// The UPD epilogue for right-hand side r: the second Gram-Schmidt pass on the
+// w the launch has just formed, v = w - sum_t coef_t V_t over the thread's
+// degrees of freedom, two columns' loads in flight.  Returns the thread's
+// part of |v|^2.
+template <int NE>
+__device__ __forceinline__ double gs_update(const DotArgs& da, int r, int64_t vs, const bool* has, const int64_t* at,
+                                            c128* yk) {
+    const int J = da.J;
+    const c128* cf = da.coef + (int64_t)r * J;
+    for (int t = 0; t < J; t += 2) {
+        c128 v[2][NE];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const c128* Vt = da.V + (int64_t)(t + q < J ? t + q : t) * da.vstep + r * vs;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) v[q][e] = has[e] ? Vt[at[e]] : mk(0.0, 0.0);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (t + q >= J) break;
+            const c128 c = cf[t + q];
+#pragma unroll
+            for (int e = 0; e < NE; ++e) yk[e] = yk[e] - c * v[q][e];
+        }
+    }
+    double a = 0.0;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) a += has[e] ? yk[e].re * yk[e].re + yk[e].im * yk[e].im : 0.0;
+    return a;
+}
+
+// What a launch does with w = H x besides or instead of writing it:
+//   OP_APPLY  y = w
+//   OP_RES    y = b - w and partial sums of |y|^2
+//   OP_DOTS   y = w and the first Gram-Schmidt pass
+//   OP_DOTS_ONLY  the first Gram-Schmidt pass, w is not written
+//   OP_UPDATE y = w - sum_t coef_t V_t and partial sums of |y|^2 (the second
+//             Gram-Schmidt pass, w formed again from x)
+// A batch whose vectors are far larger than the caches takes the last two:
+// forming w again reads x (8 bytes per unknown in complex64) and the batch's
+// coefficients once more, where writing w and reading it back moves 32
+// (2048^2, 8 right-hand sides, FGMRES(4): the two passes 2893 -> 2517 us per
+// step; 512^2, 16: 335 -> 303 us).
+enum OpMode { OP_APPLY, OP_RES, OP_DOTS, OP_DOTS_ONLY, OP_UPDATE };
+template <class Tin, int MODE>
 __global__ void __launch_bounds__(256)
 k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int nrhs, int64_t vs_in, int64_t vs_out,
           ResArgs ra, int rch, DotArgs da = DotArgs{}) {
+    constexpr bool RES = MODE == OP_RES, DOTS = MODE == OP_DOTS || MODE == OP_DOTS_ONLY, UPD = MODE == OP_UPDATE;
     constexpr int UW = OTX + 2, UH = OTY + 2;        // u_a box: [x0-1, x0+OTX] x [y0-1, y0+OTY]
     constexpr int PW = OTX + 1, PH = OTY + 1;        // p box:   [x0-1, x0+OTX-1] x [y0-1, y0+OTY-1]
     constexpr int NU = UW * UH, NP = PW * PH, NS = 2 * NU + NP;
@@ -262,7 +309,7 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
                 yv = ra.b[r * vs_out + o.off[a] + fp[a]] - yv;
                 rr += yv.re * yv.re + yv.im * yv.im;
             }
-            if (!DOTS || t0 == 0) y[r * vs_out + o.off[a] + fp[a]] = yv;
+            if (MODE <= OP_RES || (MODE == OP_DOTS && t0 == 0)) y[r * vs_out + o.off[a] + fp[a]] = yv;
             yk[a] = yv;
         }
         if (cell) {
@@ -271,13 +318,19 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
                 yv = ra.b[r * vs_out + o.off[2] + pc] - yv;
                 rr += yv.re * yv.re + yv.im * yv.im;
             }
-            if (!DOTS || t0 == 0) y[r * vs_out + o.off[2] + pc] = yv;
+            if (MODE <= OP_RES || (MODE == OP_DOTS && t0 == 0)) y[r * vs_out + o.off[2] + pc] = yv;
             yk[2] = yv;
         }
-        if (RES) res_partial(ra, r, 0, rr);
+        const bool has[3] = {face[0], face[1], cell};
+        const int64_t at[3] = {o.off[0] + fp[0], o.off[1] + fp[1], o.off[2] + pc};
+        if (UPD) {
+            rr = gs_update<3>(da, r, vs_out, has, at, yk);
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (has[e]) y[r * vs_out + at[e]] = yk[e];
+        }
+        if (RES || UPD) res_partial(ra, r, 0, rr);
         if (DOTS) {
-            const bool has[3] = {face[0], face[1], cell};
-            const int64_t at[3] = {o.off[0] + fp[0], o.off[1] + fp[1], o.off[2] + pc};
             const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
             gs_first_pass<3>(da, r, vs_out, has, at, yk, blk, (int64_t)gridDim.x * gridDim.y, t0,
                              min(da.J, t0 + da.jc));

@@ -1638,8 +1638,7 @@ inline int op_blocks(const eh_ctx* c) {
     return (int)(g.x * g.y * g.z);
 }
 
-template <class Tin, bool RES>
-void launch_H(eh_ctx* c, const void* x, int64_t vx, c128* y, int64_t vy, int nrhs, ResArgs ra) {
+OpArgs op_args(const eh_ctx* c) {
     OpArgs o{};
     o.dc = c->dcell;
     for (int a = 0; a < 3; ++a) {
@@ -1652,12 +1651,18 @@ void launch_H(eh_ctx* c, const void* x, int64_t vx, c128* y, int64_t vy, int nrh
     }
     for (int a = 0; a < 4; ++a) o.off[a] = c->off[a];
     o.C = c->C;
+    return o;
+}
+
+template <class Tin, bool RES>
+void launch_H(eh_ctx* c, const void* x, int64_t vx, c128* y, int64_t vy, int nrhs, ResArgs ra) {
+    const OpArgs o = op_args(c);
     // a batch on a small grid is spread over chunks of right-hand sides in z
     const dim3 g = op_grid(c);
     const int rch = rhs_chunk((int)(g.x * g.y * g.z), 1, nrhs);
     const dim3 gc(g.x, g.y, g.z * (unsigned)((std::max(nrhs, 1) + rch - 1) / rch));
     if (c->dim == 2)
-        hipLaunchKernelGGL((k_op2_lds<Tin, RES>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)x, y, nrhs, vx, vy, ra,
+        hipLaunchKernelGGL((k_op2_lds<Tin, RES ? OP_RES : OP_APPLY>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)x, y, nrhs, vx, vy, ra,
                            rch);
     else
         hipLaunchKernelGGL((k_op3_lds<Tin, RES>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)x, y, nrhs, vx, vy, ra,
@@ -1686,6 +1691,8 @@ void apply_H(eh_ctx* c, const void* x, int64_t vx, c128* y, int64_t vy, int nrhs
 // Up to kDotWgs workgroups the columns are spread over workgroups, two or
 // more per workgroup: the 64^2 grid has 34 tiles and up to 20 columns (12 us
 // with one workgroup per tile).
+//
+// With w null the launch keeps w to itself (apply_H_update forms it again).
 template <class Tin>
 int apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int64_t vstep, int J, c128* d1) {
     if (c->dim != 2 || J > OP_MAXJ) return -1;
@@ -1693,19 +1700,8 @@ int apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int
     double coefb = 8.0 * c->ncell;
     for (int k = 0; k < c->dim; ++k) coefb += (double)c->fsize[k] * (8.0 * c->dim + 16.0);
     Timed tm(c, KC_OPERATOR,
-             coefb + (double)nrhs * c->ndof * (sizeof(cplx<Tin>) + sizeof(c128) + J * sizeof(c128)));
-    OpArgs o{};
-    o.dc = c->dcell;
-    for (int a = 0; a < 3; ++a) {
-        o.ih[a] = 1.0 / c->h[a];
-        if (a < c->dim) {
-            o.df[a] = c->dface[a];
-            for (int b = 0; b < 3; ++b) o.w[a][b] = c->k1w[a][b];
-            o.D[a] = c->k1D[a];
-        }
-    }
-    for (int a = 0; a < 4; ++a) o.off[a] = c->off[a];
-    o.C = c->C;
+             coefb + (double)nrhs * c->ndof * (sizeof(cplx<Tin>) + (w ? sizeof(c128) : 0) + J * sizeof(c128)));
+    const OpArgs o = op_args(c);
     const dim3 g = op_grid(c);
     const int rch = rhs_chunk((int)(g.x * g.y * g.z), 1, nrhs);
     const int rchunks = (std::max(nrhs, 1) + rch - 1) / rch;
@@ -1713,15 +1709,40 @@ int apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int
     const int cmax = std::max(1, std::min((J + 1) / 2, kDotWgs / wgs));
     const int jc = (J + cmax - 1) / cmax;
     const dim3 gc(g.x, g.y, (unsigned)(rchunks * ((J + jc - 1) / jc)));
-    DotArgs da{V, vstep, J, jc, rchunks, c->partial};
-    hipLaunchKernelGGL((k_op2_lds<Tin, false, true>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)z, w, nrhs,
-                       c->ndof, c->ndof, ResArgs{}, rch, da);
+    DotArgs da{V, vstep, J, jc, rchunks, c->partial, nullptr};
+    if (w)
+        hipLaunchKernelGGL((k_op2_lds<Tin, OP_DOTS>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)z, w, nrhs, c->ndof,
+                           c->ndof, ResArgs{}, rch, da);
+    else
+        hipLaunchKernelGGL((k_op2_lds<Tin, OP_DOTS_ONLY>), gc, dim3(256), 0, c->s, o, (const cplx<Tin>*)z,
+                           (c128*)nullptr, nrhs, c->ndof, c->ndof, ResArgs{}, rch, da);
     HIPCHK(hipGetLastError());
     const int nblk = (int)(g.x * g.y);
     if (nblk <= ARN_FOLD) return nblk;
     hipLaunchKernelGGL(k_reduce_partials, dim3(2 * J, nrhs), dim3(256), 0, c->s, nblk, 2 * J, nrhs, c->partial, d1);
     HIPCHK(hipGetLastError());
     return 0;
+}
+
+// v = H z - sum_t coef_t V_t and nrm = |v|^2 per right-hand side (2D): the
+// second Gram-Schmidt pass with H z formed again.
+template <class Tin>
+void apply_H_update(eh_ctx* c, const void* z, c128* v, int nrhs, const c128* V, int64_t vstep, int J, const c128* coef,
+                    c128* nrm) {
+    double coefb = 8.0 * c->ncell;
+    for (int k = 0; k < c->dim; ++k) coefb += (double)c->fsize[k] * (8.0 * c->dim + 16.0);
+    Timed tm(c, KC_OPERATOR, coefb + (double)nrhs * c->ndof * (sizeof(cplx<Tin>) + (J + 1) * sizeof(c128)));
+    const dim3 g = op_grid(c);
+    const int nblk = (int)(g.x * g.y);
+    const int rch = rhs_chunk(nblk, 1, nrhs);
+    const dim3 gc(g.x, g.y, (unsigned)((std::max(nrhs, 1) + rch - 1) / rch));
+    const ResArgs ra{nullptr, c->res_partial, nblk, 0};
+    const DotArgs da{V, vstep, J, 0, 1, nullptr, coef};
+    hipLaunchKernelGGL((k_op2_lds<Tin, OP_UPDATE>), gc, dim3(256), 0, c->s, op_args(c), (const cplx<Tin>*)z, v, nrhs,
+                       c->ndof, c->ndof, ra, rch, da);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_reduce_partials, dim3(1, nrhs), dim3(256), 0, c->s, nblk, 1, nrhs, c->res_partial, nrm);
+    HIPCHK(hipGetLastError());
 }
 
 // r = b - H x for nrhs complex128 vectors of stride ndof, and nrm[q] =
@@ -1926,6 +1947,8 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
     return 0;
 }
 
+constexpr double kAgainBytes = 128.0 * 1024 * 1024;
+
 // Flexible GMRES(m) with right preconditioning, x_0 = 0.  Every Arnoldi
 // step -- z_j = M v_j, w = H z_j, CGS2 against the basis and the Hessenberg
 // update -- runs on the device (replayed from a HIP graph when enabled); the
@@ -1935,7 +1958,7 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
 // right-hand sides only: scale 0, no column counted).  A cycle start
 // computes r = b - H x in FP64, so the last start gives the true residual.
 //
-// The problem enters through four callbacks, each enqueueing on c->s for
+// The problem enters through callbacks, each enqueueing on c->s for
 // the nb right-hand sides currently in the batch:
 //   op_x(x, W, nb)            W = X x for an FP64 vector (cycle starts)
 //   op_z(z_j, W, nb)          W = X z_j for a preconditioned vector (multigrid precision)
@@ -1945,6 +1968,10 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
 //                             sums in d1, the number of workgroups whose
 //                             partial sums are in c->partial, or -1 where the
 //                             problem does not provide it
+//   op_upd(z_j, v, nb, V, vstep, J, coef, nrm)
+//                             v = X z_j - sum_t coef_t V_t and nrm = |v|^2,
+//                             after an op_zd without W (op_upd chosen by the
+//                             caller through `again`)
 //   prec(v, sv, z_j, nb)      z_j = M (sv[q * (m+1)] v) per right-hand side q
 //   op_res(x, b, r, nrm, nb)  r = b - X x and nrm = |r|^2 in one pass, or false
 //                             where the problem does not provide it
@@ -1959,9 +1986,10 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
 // x goes back to its place in the caller's x.  Every kernel's arithmetic per
 // right-hand side does not depend on the batch around it, so the results
 // and the counts are those of the full batch.
-template <class T, class OpX, class OpZ, class OpZD, class Prec, class OpRes>
-eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec prec, bool graphs, const c128* b,
-                      c128* x, int nrhs, double tol, int maxit, eh_info* info, OpRes op_res) {
+template <class T, class OpX, class OpZ, class OpZD, class OpUpd, class Prec, class OpRes>
+eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, OpUpd op_upd, Prec prec, bool graphs,
+                      const c128* b, c128* x, int nrhs, double tol, int maxit, eh_info* info, OpRes op_res,
+                      bool recompute) {
     const int m = c->o.restart;
     int nb = nrhs;                               // right-hand sides in the batch
     int64_t vstep = (int64_t)nb * n;             // distance between basis vectors
@@ -1974,6 +2002,11 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec
     c128* d2 = c->dsmall + (size_t)2 * nrhs * (m + 2);
     c128* d3 = c->dsmall + (size_t)4 * nrhs * (m + 2);
     unsigned rgrid = (unsigned)((nb + 63) / 64);
+    // w = X z_j is formed again for the second Gram-Schmidt pass instead of
+    // written and read back where its vectors pass through memory and several
+    // right-hand sides share the coefficients (decided by the call, so that a
+    // batch that shrinks keeps its arithmetic)
+    const bool again = recompute && nrhs >= 4 && (double)nrhs * (double)n * sizeof(c128) >= kAgainBytes;
     // predicted estimate below this multiple of tol: wait for the step
     constexpr double kNear = 3.0;
     HIPCHK(hipMemsetAsync(x, 0, (size_t)nrhs * n * sizeof(c128), c->s));
@@ -2088,7 +2121,7 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec
             cplx<T>* Zj = Z + (int64_t)j * vstep;
             auto body = [&]() {
                 prec(Vj, S.sv + j, Zj, nb);
-                int fold = op_zd(Zj, c->W, nb, c->V, vstep, j + 1, d1);
+                int fold = op_zd(Zj, again ? nullptr : c->W, nb, c->V, vstep, j + 1, d1);
                 if (fold < 0) {
                     op_z(Zj, c->W, nb);
                     fold = gs_pass<4>(c, n, j + 1, nb, c->V, c->W, nullptr, d1, nullptr, ARN_FOLD);
@@ -2096,7 +2129,12 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, Prec
                 hipLaunchKernelGGL(k_arn_coef, dim3(nb), dim3(ARN_THREADS), 0, c->s, S, j,
                                    (const c128*)(fold > 0 ? c->partial : d1), fold, d2);
                 HIPCHK(hipGetLastError());
-                fold = gs_pass<2>(c, n, j + 1, nb, c->V, c->W, d2, d3, Vj + vstep, NRM_FOLD);
+                if (again) {
+                    op_upd(Zj, Vj + vstep, nb, c->V, vstep, j + 1, d2, d3);
+                    fold = 0;
+                } else {
+                    fold = gs_pass<2>(c, n, j + 1, nb, c->V, c->W, d2, d3, Vj + vstep, NRM_FOLD);
+                }
                 hipLaunchKernelGGL(k_arn_givens, dim3(nb), dim3(64), 0, c->s, S, j,
                                    (const c128*)(fold > 0 ? c->partial : d3), fold, ds + (size_t)j * nrhs);
                 HIPCHK(hipGetLastError());
@@ -2203,7 +2241,11 @@ eh_status solve_impl(eh_ctx* c, const c128* b, c128* x, int nrhs, double tol, in
     auto op_zd = [&](const cplx<T>* z, c128* w, int nb, const c128* V, int64_t vstep, int J, c128* d1) {
         return apply_H_dots<T>(c, z, w, nb, V, vstep, J, d1);
     };
-    return fgmres_core<T>(c, n, op_x, op_z, op_zd, prec, c->o.graphs != 0, b, x, nrhs, tol, maxit, info, op_res);
+    auto op_upd = [&](const cplx<T>* z, c128* v, int nb, const c128* V, int64_t vstep, int J, const c128* coef,
+                      c128* nrm) { apply_H_update<T>(c, z, v, nb, V, vstep, J, coef, nrm); };
+    const bool again = c->dim == 2 && m <= OP_MAXJ;
+    return fgmres_core<T>(c, n, op_x, op_z, op_zd, op_upd, prec, c->o.graphs != 0, b, x, nrhs, tol, maxit, info, op_res,
+                          again);
 }
 
 eh_status fail(eh_ctx* c, eh_status st, const std::string& msg);
@@ -2251,7 +2293,8 @@ eh_status block_solve_impl(eh_ctx* c, int block, const c128* f, c128* x, int nrh
     };
     auto no_res = [](const c128*, const c128*, c128*, c128*, int) { return false; };
     auto no_zd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, c128*) { return -1; };
-    return fgmres_core<T>(c, n, op_x, op_z, no_zd, prec, false, f, x, nrhs, tol, maxit, info, no_res);
+    auto no_upd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, const c128*, c128*) {};
+    return fgmres_core<T>(c, n, op_x, op_z, no_zd, no_upd, prec, false, f, x, nrhs, tol, maxit, info, no_res, false);
 }
 
 void ensure_zbuf(eh_ctx* c) {

@@ -62,3 +62,32 @@ def test_restart_lengths(n, levels, restart):
         x1, i1 = s.solve(torch.from_numpy(b[q:q + 1]).cuda(), tol=tol, maxit=600)
         assert i1[0]["iters"] == info[q]["iters"] and np.array_equal(x1[0].cpu().numpy(), xq)
     s.close()
+
+
+@pytest.mark.parametrize("n,nsrc", [
+    ((848, 840), 4),        # vectors of the batch just above 128 MiB: H z formed twice
+    ((840, 832), 4),        # just below: H z written and read back
+    ((624, 600), 8),        # above, the batch split over workgroups
+])
+@pytest.mark.parametrize("restart", [2, 5])
+def test_second_pass_forms_the_vector_again(n, nsrc, restart):
+    """The second Gram-Schmidt pass on a large batch forms H z again instead
+    of reading it: true residuals recomputed by the oracle below the
+    tolerance and equal to the Arnoldi estimate to 1e-10, as above; finished
+    sources leave the batch on the way."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    h, levels = (1.0, 1.0), 4
+    vp, vs, rho = W.layered_medium(n, seed=5)
+    omega = W.omega_for_ppw(vs, h, 12.0)
+    sides = W.abc_all_but_top(2)
+    s = ElasticHelmholtz(n, h, vp, vs, rho, omega, levels=levels, alpha=0.5, restart=restart, abc_width=20,
+                         abc_sides=sides)
+    b = W.point_source_rhs(n, h, [(1, ((2 * q + 1) * n[0] // (2 * nsrc), 1)) for q in range(nsrc)])
+    x, info = s.solve(torch.from_numpy(b).cuda(), tol=1e-6, maxit=600)
+    mu, lm, mass = medium_arrays(n, h, vp, vs, rho, omega, 20, sides)
+    for q in range(nsrc):
+        rr = np.linalg.norm(b[q] - apply_H_stencil(n, h, mu, lm, mass, omega, x[q].cpu().numpy()))
+        rr /= np.linalg.norm(b[q])
+        assert info[q]["converged"] and rr < 1e-6
+        assert abs(info[q]["relres_est"] - rr) <= 1e-10
+    s.close()
