@@ -346,8 +346,10 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
 // of two LDS buffers, and loads the values one plane below and above that
 // the z-stencils, the z-face pressure difference and the divergence need
 // (u_a at k-1 and k+1 of the own faces, p at k-1 of the own cell) straight
-// from memory; the next right-hand side's loads are in flight while this
-// one is computed.  One barrier per right-hand side.
+// from memory; complex64 inputs have the next right-hand side's loads in
+// flight while this one is computed, one barrier per right-hand side.
+// Indices within a vector are 32 bits (2^32 unknowns of one vector would
+// need more than the card's memory for the operator alone).
 template <class Tin, bool RES>
 __global__ void __launch_bounds__(256)
 k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int nrhs, int64_t vs_in, int64_t vs_out,
@@ -356,7 +358,13 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
     constexpr int PW = OTX + 1, PH = OTY + 1;
     constexpr int NU = UW * UH, NP = PW * PH, NS = 3 * NU + NP;
     constexpr int NR = (NS + 255) / 256;
-    __shared__ cplx<Tin> lds[2][NS];
+    constexpr uint32_t kNone = 0xffffffffu;
+    // complex128 inputs: without the next right-hand side's loads in registers
+    // (and a second LDS buffer for them) three wavefronts per SIMD fit instead
+    // of two (168 x 120 x 104, two vectors: 227 -> 214 us); complex64 inputs
+    // keep three with them, and lose without (192^3: 677 -> 733 us)
+    constexpr bool AHEAD = sizeof(Tin) == 4;
+    __shared__ cplx<Tin> lds[AHEAD ? 2 : 1][NS];
     const int tid = threadIdx.x;
     const int tx = tid % OTX, ty = tid / OTX;
     const int x0 = blockIdx.x * OTX, y0 = blockIdx.y * OTY;
@@ -366,31 +374,31 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
     const int k = blockIdx.z % planes;
     const int rlo = (blockIdx.z / planes) * rch, rhi = min(nrhs, rlo + rch);
     const bool inx = i <= n0 && j <= n1;
-    int64_t sidx[NR];
+    uint32_t sidx[NR];
 #pragma unroll
     for (int it = 0; it < NR; ++it) {
         const int q = tid + it * 256;
-        int64_t v = -1;
+        uint32_t v = kNone;
         if (q < 3 * NU) {
             const int a = q / NU, e = q - a * NU;
             const int ey = e / UW, ex = e - ey * UW;
             const int gx = x0 - 1 + ex, gy = y0 - 1 + ey;
             const Dims& d = o.df[a];
             if (gx >= 0 && gx < d.g[0] && gy >= 0 && gy < d.g[1] && k < d.g[2])
-                v = o.off[a] + ((int64_t)k * d.g[1] + gy) * d.g[0] + gx;
+                v = (uint32_t)(o.off[a] + ((int64_t)k * d.g[1] + gy) * d.g[0] + gx);
         } else if (q < NS) {
             const int e = q - 3 * NU;
             const int ey = e / PW, ex = e - ey * PW;
             const int gx = x0 - 1 + ex, gy = y0 - 1 + ey;
             if (gx >= 0 && gx < n0 && gy >= 0 && gy < n1 && k < n2)
-                v = o.off[3] + ((int64_t)k * n1 + gy) * n0 + gx;
+                v = (uint32_t)(o.off[3] + ((int64_t)k * n1 + gy) * n0 + gx);
         }
         sidx[it] = v;
     }
     const int ci[3] = {i, j, k};
     const int nn[3] = {n0, n1, n2};
     bool face[3];
-    int64_t fp[3], fsz[3];
+    uint32_t fp[3], fsz[3];
     FineCoef<double, 0, 3> cf[3];
     c128 Dp[3];
     bool zm[3], zp[3];
@@ -401,8 +409,8 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
 #pragma unroll
         for (int b = 0; b < 3; ++b) if (b != a && ci[b] >= nn[b]) ok = false;
         face[a] = ok;
-        fsz[a] = (int64_t)d.g[0] * d.g[1];
-        fp[a] = k * fsz[a] + (int64_t)j * d.g[0] + i;
+        fsz[a] = (uint32_t)d.g[0] * d.g[1];
+        fp[a] = k * fsz[a] + (uint32_t)j * d.g[0] + i;
         zm[a] = ok && k > 0;
         zp[a] = ok && k + 1 < d.g[2];
         Dp[a] = mk(0.0, 0.0);
@@ -414,8 +422,8 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
         }
     }
     const bool cell = inx && i < n0 && j < n1 && k < n2;
-    const int64_t csz = (int64_t)n0 * n1;
-    const int64_t pc = k * csz + (int64_t)j * n0 + i;
+    const uint32_t csz = (uint32_t)n0 * n1;
+    const uint32_t pc = k * csz + (uint32_t)j * n0 + i;
     const bool pzm = face[2] && k > 0;     // p in the cell below the own z-face
     const double Cp = cell ? o.C[pc] : 0.0;
     const int lu = (ty + 1) * UW + (tx + 1);
@@ -425,22 +433,30 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
     auto load_in = [&](int r) {
         const cplx<Tin>* xr = x + r * vs_in;
 #pragma unroll
-        for (int it = 0; it < NR; ++it) vin[it] = xr[sidx[it] >= 0 ? sidx[it] : 0];
+        for (int it = 0; it < NR; ++it) vin[it] = xr[sidx[it] != kNone ? sidx[it] : 0u];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const cplx<Tin>* ur = xr + o.off[a];
-            vzm[a] = ur[zm[a] ? fp[a] - fsz[a] : 0];
-            vzp[a] = ur[zp[a] ? fp[a] + fsz[a] : 0];
+            vzm[a] = ur[zm[a] ? fp[a] - fsz[a] : 0u];
+            vzp[a] = ur[zp[a] ? fp[a] + fsz[a] : 0u];
         }
         vpm = xr[o.off[3] + (pzm ? pc - csz : 0)];
     };
-    load_in(rlo);
+    if (AHEAD) load_in(rlo);
     for (int r = rlo; r < rhi; ++r) {
-        cplx<Tin>* S = lds[(r - rlo) & 1];
+        cplx<Tin>* S = lds[AHEAD ? (r - rlo) & 1 : 0];
+        if (!AHEAD) {
+            load_in(r);
+            if (r > rlo) {                     // the last right-hand side's readers are done
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            }
+        }
 #pragma unroll
         for (int it = 0; it < NR; ++it) {
             const int q = tid + it * 256;
-            if (q < NS) S[q] = sidx[it] >= 0 ? vin[it] : cplx<Tin>{Tin(0), Tin(0)};
+            if (q < NS) S[q] = sidx[it] != kNone ? vin[it] : cplx<Tin>{Tin(0), Tin(0)};
         }
         c128 um2[3], up2[3];
 #pragma unroll
@@ -449,7 +465,7 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
             up2[a] = zp[a] ? ccast<double>(vzp[a]) : mk(0.0, 0.0);
         }
         const c128 pm2 = pzm ? ccast<double>(vpm) : mk(0.0, 0.0);
-        if (r + 1 < rhi) load_in(r + 1);
+        if (AHEAD && r + 1 < rhi) load_in(r + 1);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
