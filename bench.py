@@ -168,10 +168,10 @@ CLASS_KERNELS = {
     "operator": (("eh::k_op2_lds<", "eh::k_op3_lds<"), None),
     "distribute": (("eh::k_distribute<",), None),
     "couple": (("eh::k_gcouple<",), None),
-    "dense": (("eh::k_gdense<", "eh::k_bt_rows<"), None),
+    "dense": (("eh::k_gdense<", "eh::k_bt_rows<", "eh::k_bt_sparse<"), None),
     # every timed multigrid kernel: the V-cycles of the three (four) blocks
     "vcycle": (("eh::k_fdown<", "eh::k_fup<", "eh::k_gdense<", "eh::k_gstencil<", "eh::k_gfine<",
-                "eh::k_gtransfer<", "eh::k_bt_rows<", "eh::k_gfine3_lds<",
+                "eh::k_gtransfer<", "eh::k_bt_rows<", "eh::k_bt_sparse<", "eh::k_gfine3_lds<",
                 "eh::k_gstencil3_lds<", "eh::k_grestrict3_lds<", "eh::k_gprolong3_lds<"), None),
 }
 DEFAULT_SOURCES = ["paper_2411_15897_amd/csrc/eh_fused_kernels.h", "paper_2411_15897_amd/csrc/eh_group_kernels.h",

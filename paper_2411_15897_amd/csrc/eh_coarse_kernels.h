@@ -20,6 +20,13 @@
 // [G_l | G_r], row-major; five matrices per group in all.  A solve is one
 // launch per level down, one for the dense rest and one per level back up.
 //
+// On the first level L_e, U_e, L_K and U_K are still the stencil's few entries
+// per row, so where its matrices are large the products with them run from
+// lists of these entries and only S_e^-1 is stored:
+//     v_e = S_e^-1 f_e,  f_K -= L_K v_e1 + U_K v_e2;
+//     x_e = S_e^-1 (f_e - L_e x_l - U_e x_r),
+// two matrices read per removed group instead of five for two more launches.
+//
 // Why levels: a sweep over the groups one after the other needs two launches
 // per group, each a few microseconds of dependent latency however small its
 // matrix; here the launches number 2 log2(groups), and a level's groups run
@@ -92,6 +99,35 @@ k_bt_couple_dense(BTPart pt, const c128* __restrict__ st, const BTBlock* __restr
             v = st[(int64_t)pt.offset_index(ox, oy, oz) * pt.d.np() + pt.point(cr)];
     }
     *out = v;
+}
+
+// The couplings of every row to its neighbouring groups as entry-major lists
+// in elimination order (perm: elimination order -> point, inv the other
+// way): coefficient and the neighbour's place, rows with fewer entries
+// filled with zeros.
+__global__ void __launch_bounds__(256)
+k_bt_couple_list(BTPart pt, const c128* __restrict__ st, const int* __restrict__ perm, const int* __restrict__ inv,
+                 int ne, c128* __restrict__ k, int* __restrict__ at) {
+    const int N = (int)pt.d.np();
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= N) return;
+    const int p = perm[q];
+    const int c[3] = {p % pt.d.g[0], (p / pt.d.g[0]) % pt.d.g[1], p / (pt.d.g[0] * pt.d.g[1])};
+    const int g = pt.group(c);
+    int e = 0;
+    for (int oz = -pt.w.w[2]; oz <= pt.w.w[2]; ++oz)
+    for (int oy = -pt.w.w[1]; oy <= pt.w.w[1]; ++oy)
+    for (int ox = -pt.w.w[0]; ox <= pt.w.w[0]; ++ox) {
+        const int n[3] = {c[0] + ox, c[1] + oy, c[2] + oz};
+        if (!pt.inside(n) || pt.group(n) == g) continue;
+        k[(int64_t)e * N + q] = st[(int64_t)pt.offset_index(ox, oy, oz) * N + p];
+        at[(int64_t)e * N + q] = inv[pt.point(n)];
+        ++e;
+    }
+    for (; e < ne; ++e) {
+        k[(int64_t)e * N + q] = mk(0.0, 0.0);
+        at[(int64_t)e * N + q] = q;
+    }
 }
 
 constexpr int GJB = 32;   // pivot block of the blocked Gauss-Jordan inversion
@@ -425,6 +461,7 @@ struct BTTask {
     int rows;
     int n[3], off[3];
     int out;
+    int add;        // down: the result is added to the right-hand side's entry
 };
 
 // One launch over up to BT_MAXS blocks.  Per slot: its tasks in this launch,
@@ -451,7 +488,8 @@ struct BTRun {
 };
 
 // Down (BACK false): y_K = f_K + G_l f_e1 + G_r f_e2 (a kept group without
-// removed neighbours has no columns: y_K = f_K).  Up (BACK true): x_e =
+// removed neighbours has no columns: y_K = f_K; without add, y_e = S_e^-1
+// f_e).  Up (BACK true): x_e =
 // S_e^-1 f_e - S_e^-1 L_e x_l - S_e^-1 U_e x_r, written to x and, in the
 // level's layout and precision, to e; also the dense rest (one vector).
 //
@@ -492,7 +530,7 @@ k_bt_rows(BTRun<T> a) {
     const bool wr = row < tk.rows && lane < cnt;
     const int po = (wr && (BACK || first)) ? perm[tk.out + row] : 0;
     c128 add = mk(0.0, 0.0);
-    if (!BACK && wr) {
+    if (!BACK && wr && tk.add) {
         if (first) add = ccast<double>(f[lane * vf + po]);
         else add = y[(int64_t)lane * N + tk.out + row];
     }
@@ -558,6 +596,70 @@ k_bt_rows(BTRun<T> a) {
     } else {
         y[o] = v;
     }
+}
+
+// First level's couplings: for the entries lo .. hi - 1 (elimination order)
+// of groups that are all removed, or all kept,
+//     y = f - (the couplings to the two neighbouring groups) v,
+// v the right-hand side y of the removed groups (v_e) or the solution x of
+// the kept ones.  A few thousand rows of 12 to 100 entries, so latency is all
+// there is to it: coefficients and vector positions lie in entry-major
+// lists (k_bt_couple_list), a row's entries are dealt to the workgroup's four
+// wavefronts, six in flight each.  (From the stencil itself, with the
+// neighbours' places worked out here: 13 to 20 us for 4500 rows.)
+// Grid (64 entries, slots, right-hand sides).
+template <class T>
+struct BTSparse {
+    int N[BT_MAXS], ne[BT_MAXS];             // points, entries per row
+    const c128* k[BT_MAXS];                  // [entry][N]
+    const int* at[BT_MAXS];                  // [entry][N]
+    const int* perm[BT_MAXS];
+    int lo[BT_MAXS], hi[BT_MAXS];
+    const cplx<T>* f[BT_MAXS];
+    int64_t vf[BT_MAXS];
+    const c128* v[BT_MAXS];
+    c128* y[BT_MAXS];
+};
+template <class T>
+__global__ void __launch_bounds__(256)
+k_bt_sparse(BTSparse<T> a) {
+    __shared__ c128 part[4][64];
+    const int s = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q0 = a.lo[s] + blockIdx.x * 64;
+    if (q0 >= a.hi[s]) return;               // uniform per workgroup
+    const bool mine = q0 + lane < a.hi[s];
+    const int q = mine ? q0 + lane : q0;
+    const int N = a.N[s], ne = a.ne[s];
+    const int64_t r = blockIdx.z;
+    const c128* __restrict__ v = a.v[s] + r * N;
+    const c128* __restrict__ k = a.k[s] + q;
+    const int* __restrict__ at = a.at[s] + q;
+    c128 fp = mk(0.0, 0.0);
+    if (wave == 0) fp = ccast<double>(a.f[s][r * a.vf[s] + a.perm[s][q]]);
+    c128 acc = mk(0.0, 0.0);
+    constexpr int U = 6;
+    for (int i0 = wave; i0 < ne; i0 += 4 * U) {
+        c128 kk[U], u[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int i = i0 + 4 * t < ne ? i0 + 4 * t : i0;
+            kk[t] = k[(int64_t)i * N];
+            u[t] = v[at[(int64_t)i * N]];
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            if (i0 + 4 * t < ne) {
+                acc.re = fmat(-kk[t].im, u[t].im, fmat(kk[t].re, u[t].re, acc.re));
+                acc.im = fmat(kk[t].im, u[t].re, fmat(kk[t].re, u[t].im, acc.im));
+            }
+        }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0 || !mine) return;
+    const c128 s0 = part[0][lane] + part[1][lane], s1 = part[2][lane] + part[3][lane];
+    a.y[s][r * N + q] = fp - (s0 + s1);
 }
 
 }  // namespace eh

@@ -111,6 +111,11 @@ struct BTData {
         double fmat = 0, fvec = 0, bmat = 0, bvec = 0;
     };
     int64_t N = 0;
+    bool sparse0 = false;        // the first level's couplings from lists of their entries
+    int64_t n0 = 0;              // entries of the groups it removes (they come first)
+    int ne = 0;                  // list entries per row
+    c128* lk = nullptr;          // [ne][N] coefficients and places
+    int* lat = nullptr;
     std::vector<Lev> lev;
     int tail = 0;                // the dense rest's task
     int ntail = 0;               // its rows
@@ -591,6 +596,11 @@ void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const i
 // Points left to the dense matrix that ends the elimination: one launch over
 // n^2 entries instead of two launches per further level.
 constexpr int64_t kBtTail = 1536;
+// Bytes of a block's first-level matrices worth the two launches of about 4 us
+// that spare them: at 40 MB (200 x 64 points, groups of 128) a whole W-cycle
+// preconditioner takes the same 0.51 ms either way, at 75 - 89 MB (24 x 20 x
+// 18, groups of 360) 0.95 against 0.86 ms.
+constexpr double kBtSparse = 48e6;
 
 // Eliminate the groups of pt: with `nested` every other group per level,
 // until at most kBtTail points (or one group) are left; else one group per
@@ -610,6 +620,12 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
     std::vector<int> active(nb), order;
     for (int I = 0; I < nb; ++I) active[I] = I;
     int64_t left = T.N, tot = 0;
+    if (nested && nb > 1 && left > kBtTail) {
+        // three matrices less per removed group on the first level
+        double less = 0.0;
+        for (int I = 0; I < nb; I += 2) less += (double)bs(I) * (2 * bs(I - 1) + 2 * bs(I + 1) - bs(I)) * sizeof(c128);
+        T.sparse0 = less >= kBtSparse;
+    }
     while (active.size() > 1 && !(nested && left <= kBtTail)) {
         Plan P;
         std::vector<int> next;
@@ -620,13 +636,13 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
             const int I = active[p];
             if (gone(p)) {
                 Elim e{I, at(p - 1), at(p + 1), tot};
-                tot += bs(I) * (bs(I) + bs(e.l) + bs(e.r));
+                tot += bs(I) * (bs(I) + (T.sparse0 && plan.empty() ? 0 : bs(e.l) + bs(e.r)));
                 P.el.push_back(e);
                 order.push_back(I);
                 left -= bs(I);
             } else {
                 Keep k{I, gone(p - 1) ? at(p - 1) : -1, gone(p + 1) ? at(p + 1) : -1, tot};
-                tot += bs(I) * (bs(k.e1) + bs(k.e2));
+                if (!(T.sparse0 && plan.empty())) tot += bs(I) * (bs(k.e1) + bs(k.e2));
                 // the first level also brings the untouched groups' f into y
                 if (k.e1 >= 0 || k.e2 >= 0 || plan.empty()) P.kp.push_back(k);
                 next.push_back(I);
@@ -656,9 +672,21 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
     auto vo = [&](int I) { return I < 0 ? 0 : (int)voff[I]; };
     for (const Plan& P : plan) {
         BTData::Lev L;
+        const bool sp = T.sparse0 && &P == &plan[0];
         L.f0 = (int)tasks.size();
+        if (sp) {
+            for (const Elim& e : P.el) {
+                BTTask t{e.mat, (int)bs(e.e), {(int)bs(e.e), 0, 0}, {vo(e.e), 0, 0}, vo(e.e), 0};
+                tasks.push_back(t);
+                L.fmax = std::max(L.fmax, t.rows);
+                L.fmat += (double)t.rows * t.rows;
+                L.fvec += 2.0 * t.rows;
+                T.n0 += t.rows;
+            }
+        }
         for (const Keep& k : P.kp) {
-            BTTask t{k.mat, (int)bs(k.k), {(int)bs(k.e1), (int)bs(k.e2), 0}, {vo(k.e1), vo(k.e2), 0}, vo(k.k)};
+            if (sp) break;
+            BTTask t{k.mat, (int)bs(k.k), {(int)bs(k.e1), (int)bs(k.e2), 0}, {vo(k.e1), vo(k.e2), 0}, vo(k.k), 1};
             tasks.push_back(t);
             L.fmax = std::max(L.fmax, t.rows);
             L.fmat += (double)t.rows * (t.n[0] + t.n[1]);
@@ -667,8 +695,8 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
         L.nf = (int)tasks.size() - L.f0;
         L.b0 = (int)tasks.size();
         for (const Elim& e : P.el) {
-            BTTask t{e.mat, (int)bs(e.e), {(int)bs(e.e), (int)bs(e.l), (int)bs(e.r)}, {vo(e.e), vo(e.l), vo(e.r)},
-                     vo(e.e)};
+            BTTask t{e.mat, (int)bs(e.e), {(int)bs(e.e), sp ? 0 : (int)bs(e.l), sp ? 0 : (int)bs(e.r)},
+                     {vo(e.e), vo(e.l), vo(e.r)}, vo(e.e), 0};
             tasks.push_back(t);
             L.bmax = std::max(L.bmax, t.rows);
             L.bmat += (double)t.rows * (t.n[0] + t.n[1] + t.n[2]);
@@ -679,11 +707,27 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
     }
     T.tail = (int)tasks.size();
     T.ntail = (int)left;
-    tasks.push_back({mtail, (int)left, {(int)left, 0, 0}, {(int)(T.N - left), 0, 0}, (int)(T.N - left)});
+    tasks.push_back({mtail, (int)left, {(int)left, 0, 0}, {(int)(T.N - left), 0, 0}, (int)(T.N - left), 0});
     T.mats = c->alloc<c128>((size_t)tot);
     T.perm = c->alloc<int>((size_t)T.N);
     T.tasks = c->alloc<BTTask>(tasks.size());
     HIPCHK(hipMemcpy(T.perm, perm.data(), perm.size() * sizeof(int), hipMemcpyHostToDevice));
+    if (T.sparse0) {
+        std::vector<int> inv((size_t)T.N);
+        for (int64_t q = 0; q < T.N; ++q) inv[(size_t)perm[(size_t)q]] = (int)q;
+        int* dinv = c->alloc<int>((size_t)T.N);
+        HIPCHK(hipMemcpy(dinv, inv.data(), inv.size() * sizeof(int), hipMemcpyHostToDevice));
+        // a row's offsets off its own plane (those that stay in its group are
+        // not couplings)
+        T.ne = pt.w.nst() / (2 * pt.gsz + 1) * (2 * pt.gsz);
+        T.lk = c->alloc<c128>((size_t)T.ne * T.N);
+        T.lat = c->alloc<int>((size_t)T.ne * T.N);
+        hipLaunchKernelGGL(k_bt_couple_list, dim3((unsigned)((T.N + 255) / 256)), dim3(256), 0, 0, pt, st, T.perm, dinv,
+                           T.ne, T.lk, T.lat);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipDeviceSynchronize());
+        c->release(dinv);
+    }
     HIPCHK(hipMemcpy(T.tasks, tasks.data(), tasks.size() * sizeof(BTTask), hipMemcpyHostToDevice));
     // the numbers
     int64_t bmax = 1;
@@ -740,10 +784,12 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
             std::vector<BTCopy> cp;
             std::vector<c128*> tmp;
             auto fresh = [&]() { tmp.push_back(g.get()); return tmp.back(); };
+            const bool sp = T.sparse0 && &P == &plan[0];
             for (const Elim& e : P.el) {
-                const int64_t b = bs(e.e), ld = b + bs(e.l) + bs(e.r);
+                const int64_t b = bs(e.e), ld = sp ? b : b + bs(e.l) + bs(e.r);
                 c128* dst = T.mats + e.mat;
                 cp.push_back({D[e.e], dst, (int)b, (int)b, bp, (int)ld});
+                if (sp) continue;
                 if (e.l >= 0) {
                     c128* E = fresh();
                     p1.push_back({D[e.e], L[e.e], E, -1.0, 0});
@@ -762,7 +808,7 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
                 if (k.e1 >= 0) {
                     c128* G = fresh();
                     p1.push_back({L[k.k], D[k.e1], G, -1.0, 0});
-                    cp.push_back({G, dst, (int)b, (int)bs(k.e1), bp, (int)ld});
+                    if (!sp) cp.push_back({G, dst, (int)b, (int)bs(k.e1), bp, (int)ld});
                     p2.push_back({G, U[k.e1], D[k.k], 1.0, 1});
                     c128* nl = nullptr;
                     if (L[k.e1]) {
@@ -774,7 +820,7 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
                 if (k.e2 >= 0) {
                     c128* G = fresh();
                     p1.push_back({U[k.k], D[k.e2], G, -1.0, 0});
-                    cp.push_back({G, dst + bs(k.e1), (int)b, (int)bs(k.e2), bp, (int)ld});
+                    if (!sp) cp.push_back({G, dst + bs(k.e1), (int)b, (int)bs(k.e2), bp, (int)ld});
                     p3.push_back({G, L[k.e2], D[k.k], 1.0, 1});
                     c128* nu = nullptr;
                     if (U[k.e2]) {
@@ -872,6 +918,8 @@ void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& 
         c->release(T.mats);
         c->release(T.perm);
         c->release(T.tasks);
+        c->release(T.lk);
+        c->release(T.lat);
         c->release(T.y);
         T = BTData{};
     };
@@ -1131,7 +1179,7 @@ void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const i
                 const BTData::Lev& L = bd.lev[l];
                 a.tasks[s] += back ? L.b0 : L.f0;
                 a.ntasks[s] = back ? L.nb : L.nf;
-                a.first[s] = l == 0;
+                a.first[s] = l == 0 && !(bd.sparse0 && back);
                 maxr = std::max(maxr, back ? L.bmax : L.fmax);
                 mat = back ? L.bmat : L.fmat;
                 vec = back ? L.bvec : L.fvec;
@@ -1149,9 +1197,45 @@ void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const i
 #undef EH_BT
         HIPCHK(hipGetLastError());
     };
-    for (int l = 0; l < nlev; ++l) launch(l, false);
+    // the first level's couplings: down onto the kept groups, up onto the
+    // removed ones (slots without the form have no entries)
+    auto couple = [&](bool back) {
+        BTSparse<T> b{};
+        int maxn = 0;
+        double by = 0.0;
+        for (int s = 0; s < ns; ++s) {
+            const BTData& bd = c->blk[kinds[s]].btd;
+            if (!bd.sparse0) continue;
+            b.N[s] = (int)bd.N;
+            b.ne[s] = bd.ne;
+            b.k[s] = bd.lk;
+            b.at[s] = bd.lat;
+            b.perm[s] = bd.perm;
+            b.lo[s] = back ? 0 : (int)bd.n0;
+            b.hi[s] = back ? (int)bd.n0 : (int)bd.N;
+            b.f[s] = a.f[s];
+            b.vf[s] = a.vf[s];
+            b.v[s] = back ? a.x[s] : a.y[s];
+            b.y[s] = a.y[s];
+            const int n = b.hi[s] - b.lo[s];
+            maxn = std::max(maxn, n);
+            by += (double)n * (bd.ne * (sizeof(c128) + sizeof(int)) + nrhs * (2.0 * sizeof(c128) + sizeof(cplx<T>)));
+        }
+        if (maxn == 0) return;
+        Timed tm(c, KC_DENSE, by);
+        hipLaunchKernelGGL((k_bt_sparse<T>), dim3((unsigned)((maxn + 63) / 64), (unsigned)ns, (unsigned)nrhs), dim3(256),
+                           0, c->s, b);
+        HIPCHK(hipGetLastError());
+    };
+    for (int l = 0; l < nlev; ++l) {
+        launch(l, false);
+        if (l == 0) couple(false);
+    }
     launch(-1, true);
-    for (int l = nlev - 1; l >= 0; --l) launch(l, true);
+    for (int l = nlev - 1; l >= 0; --l) {
+        if (l == 0) couple(true);
+        launch(l, true);
+    }
 }
 
 // The fused legs cover 2D V(1, nu2) cycles started from a zero guess.

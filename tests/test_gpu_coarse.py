@@ -185,6 +185,9 @@ def test_batch_equals_single(nrhs):
     (200, 9),
     (61, 64),        # 61 or 62 groups: the chain ends on a removed group
     (13, 14, 15),    # 3D, groups of one plane of about 180
+    (150, 151),      # groups of 150: the first level's couplings from lists, odd count
+    (160, 150),      # the same along the other axis, even count for two of the blocks
+    (18, 20, 23),    # and in 3D
 ])
 @pytest.mark.parametrize("nrhs", [1, 2, 3, 6])
 def test_elimination_levels(n, nrhs):
