@@ -8,7 +8,7 @@ namespace eh {
 #if EH_UP == 0
 
 template <class T>
-void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrhs) {
+void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrhs, const CplArgs<T>* cpl) {
     const FCfg k = kFDown[cfg];
     int gx = 1, gy = 1;
     for (int s = 0; s < a.ns; ++s) {
@@ -19,13 +19,16 @@ void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrh
     const int nch = (std::max(nrhs, 1) + rch - 1) / rch;
     const dim3 g((unsigned)gx, (unsigned)gy, (unsigned)(a.ns * nch)), blk((unsigned)k.threads);
     const bool pb = a.kind[0] == 2;
-#define EH_LFD(CF)                                                                               \
-    if (l == 0) {                                                                                \
-        if (pb) hipLaunchKernelGGL((k_fdown<T, true, CF, true>), g, blk, 0, stream, a, nrhs, rch);    \
-        else hipLaunchKernelGGL((k_fdown<T, true, CF, false>), g, blk, 0, stream, a, nrhs, rch);      \
-    } else {                                                                                     \
-        if (pb) hipLaunchKernelGGL((k_fdown<T, false, CF, true>), g, blk, 0, stream, a, nrhs, rch);   \
-        else hipLaunchKernelGGL((k_fdown<T, false, CF, false>), g, blk, 0, stream, a, nrhs, rch);     \
+    const NoCpl no{};
+#define EH_LFD(CF)                                                                                        \
+    if (cpl) {                                                                                            \
+        hipLaunchKernelGGL((k_fdown<T, true, CF, false, CplArgs<T>>), g, blk, 0, stream, a, nrhs, rch, *cpl); \
+    } else if (l == 0) {                                                                                  \
+        if (pb) hipLaunchKernelGGL((k_fdown<T, true, CF, true>), g, blk, 0, stream, a, nrhs, rch, no);    \
+        else hipLaunchKernelGGL((k_fdown<T, true, CF, false>), g, blk, 0, stream, a, nrhs, rch, no);      \
+    } else {                                                                                              \
+        if (pb) hipLaunchKernelGGL((k_fdown<T, false, CF, true>), g, blk, 0, stream, a, nrhs, rch, no);   \
+        else hipLaunchKernelGGL((k_fdown<T, false, CF, false>), g, blk, 0, stream, a, nrhs, rch, no);     \
     }
     switch (cfg) {
         case 0: EH_LFD(0) break;
@@ -36,7 +39,7 @@ void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrh
 #undef EH_LFD
 }
 
-template void launch_fdown<EH_T>(hipStream_t, const GArgs<EH_T>&, int, int, int);
+template void launch_fdown<EH_T>(hipStream_t, const GArgs<EH_T>&, int, int, int, const CplArgs<EH_T>*);
 
 #else
 

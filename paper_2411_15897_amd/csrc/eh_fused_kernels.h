@@ -37,6 +37,8 @@
 // its arithmetic.
 #pragma once
 
+#include <type_traits>
+
 #include "eh_common.h"
 #include "eh_launch.h"
 #include "eh_group_kernels.h"
@@ -171,9 +173,16 @@ struct PointOp {
 // ---------------------------------------------------------------------------
 // down leg: a.d = level l, a.dc = level l+1, a.f = f_l (vf), a.out = f_{l+1} (vo)
 
-template <class T, bool FINE, int KIND, int WX, int WY, int NM, bool MIXED, int CX, int CY, int NT>
+// CPL (fine level of the shear blocks): f itself is formed here, f = r_u -
+// B_k^T e_p at the staged points, and stored by the tile that owns the point,
+// so the coupling is no launch of its own and f is not read back.  The
+// support's f waits in RR, whose entry its thread then replaces by the
+// residual.  Bound by memory or, on small grids, by the launches around it;
+// figures at couple_in_leg.
+template <class T, bool FINE, int KIND, int WX, int WY, int NM, bool MIXED, int CX, int CY, int NT, bool CPL = false,
+          class CA = NoCpl>
 __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* lds, int r0, int r1, int tile_x,
-                                          int tile_y) {
+                                          int tile_y, const CA& cp = CA{}) {
     const Dims d = a.d[slot], dc = a.dc[slot];
     const int X0 = tile_x * CX, Y0 = tile_y * CY;
     if (X0 >= dc.g[0] || Y0 >= dc.g[1]) return;       // uniform per workgroup
@@ -210,6 +219,26 @@ __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* 
         if (q < UX * UY && gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
             up_[it] = gy * nx + gx;
             usc[it] = fuse_sc<T, FINE>(a, slot, up_[it]);
+        }
+    }
+    // CPL: the cell on the far side of the face of a staged point, bit 0/1 of
+    // cfl: the far / near cell exists, bit 2: this tile stores the point's f,
+    // bit 3: it is a support point
+    int ccell[NU], cfl[NU];
+    if constexpr (CPL) {
+#pragma unroll
+        for (int it = 0; it < NU; ++it) {
+            const int q = threadIdx.x + it * NT;
+            const int uy = q / UX, ux = q - uy * UX;
+            const int gx = rx0 - WX + ux, gy = ry0 - WY + uy;
+            constexpr int AX = NM == 1 ? 0 : 1;
+            const int ck = AX == 0 ? gx : gy, nk = AX == 0 ? cp.n0 : cp.n1;
+            ccell[it] = gy * cp.n0 + gx;
+            cfl[it] = 0;
+            if (up_[it] >= 0)
+                cfl[it] = (ck < nk ? 1 : 0) | (ck >= 1 ? 2 : 0) |
+                          (gx >= 2 * X0 && gx < 2 * X0 + 2 * CX && gy >= 2 * Y0 && gy < 2 * Y0 + 2 * CY ? 4 : 0);
+            if (q < UX * UY && ux >= WX && ux < WX + RX && uy >= WY && uy < WY + RY) cfl[it] |= 8;
         }
     }
     // Fine level with several support points per thread: their operators
@@ -252,10 +281,37 @@ __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* 
         }
         if (ONE_R) in_fr = f[rin ? rp : 0];
     };
+    // CPL: the same for r_u and e_p, the coupling's arithmetic as in k_gcouple
+    auto load_couple = [&](int r) {
+        if constexpr (CPL) {
+            constexpr int AX = NM == 1 ? 0 : 1;
+            const c128* __restrict__ ru = cp.c.ru[slot] + r * cp.vr;
+            const cplx<T>* __restrict__ ep = cp.ep + r * cp.ve;
+            const double sr = cp.c.rs ? cp.c.rs[r * cp.c.rss] : 1.0;
+            const double ihk = cp.c.ih[slot];
+            const int near = AX == 0 ? 1 : cp.n0;
+            c128 rv[NU];
+            cplx<T> e1[NU], e0[NU];
+#pragma unroll
+            for (int it = 0; it < NU; ++it) {
+                rv[it] = ru[up_[it] >= 0 ? up_[it] : 0];
+                e1[it] = ep[cfl[it] & 1 ? ccell[it] : 0];
+                e0[it] = ep[cfl[it] & 2 ? ccell[it] - near : 0];
+            }
+#pragma unroll
+            for (int it = 0; it < NU; ++it) {
+                c128 gr = mk(0.0, 0.0);
+                if (cfl[it] & 1) gr = gr + ccast<double>(e1[it]);
+                if (cfl[it] & 2) gr = gr - ccast<double>(e0[it]);
+                inu[it] = ccast<T>(sr * rv[it] - ihk * gr);
+            }
+        }
+    };
     if (!FINE) load_in(r0);
     for (int r = r0; r < r1; ++r) {
         const cplx<T>* __restrict__ f = a.f[slot] + r * a.vf[slot];
-        if (FINE) load_in(r);
+        if constexpr (CPL) load_couple(r);
+        else if (FINE) load_in(r);
         const cplx<T> fr = rin ? in_fr : czero<T>();
         cplx<T> fhold[NRF];
 #pragma unroll
@@ -266,19 +322,25 @@ __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* 
             const int q = threadIdx.x + it * NT;
             if (q >= UX * UY) break;
             U[q] = up_[it] >= 0 ? usc[it] * inu[it] : czero<T>();
+            if constexpr (CPL) {
+                const int uy = q / UX, ux = q - uy * UX;
+                if (cfl[it] & 8) RR[(uy - WY) * RX + (ux - WX)] = inu[it];
+                if (cfl[it] & 4) ((cplx<T>*)cp.c.g[slot])[r * cp.c.vg[slot] + up_[it]] = inu[it];
+            }
         }
         if (!FINE && r + 1 < r1) load_in(r + 1);
         lds_barrier();
         if (ONE_R) {
             if ((int)threadIdx.x < RX * RY)
-                RR[threadIdx.x] =
-                    rin ? rop.template first_resid<UX>(U, (my_ry + WY) * UX + (my_rx + WX), fr) : czero<T>();
+                RR[threadIdx.x] = rin ? rop.template first_resid<UX>(U, (my_ry + WY) * UX + (my_rx + WX),
+                                                                     CPL ? RR[threadIdx.x] : fr)
+                                      : czero<T>();
         } else if (HOLD) {
 #pragma unroll
             for (int it = 0; it < NR; ++it) {
                 const int q = threadIdx.x + it * NT;
                 if (q >= RX * RY) break;
-                RR[q] = hp[it] >= 0 ? hop[it].template first_resid<UX>(U, hl[it], fhold[it]) : czero<T>();
+                RR[q] = hp[it] >= 0 ? hop[it].template first_resid<UX>(U, hl[it], CPL ? RR[q] : fhold[it]) : czero<T>();
             }
         } else {
 #pragma unroll 1
@@ -326,9 +388,9 @@ __device__ __forceinline__ void down_body(const GArgs<T>& a, int slot, cplx<T>* 
 // 5 x 5 stencils of H_p set the registers of the shear blocks' launches too
 // (shear up leg on 512^2 of a 1024^2 solve 33.7 -> 26.7 us, on 1024^2 of a
 // batch of 8 332 -> 258 us).
-template <class T, bool FINE, int CFG, bool PB>
+template <class T, bool FINE, int CFG, bool PB, class CA = NoCpl>
 __global__ void __launch_bounds__(kFDown[CFG].threads)
-k_fdown(GArgs<T> a, int nrhs, int rch) {
+k_fdown(GArgs<T> a, int nrhs, int rch, CA cp) {
     constexpr int CX = kFDown[CFG].x, CY = kFDown[CFG].y, NT = kFDown[CFG].threads;
     __shared__ cplx<T> lds[fd_lds(CX, CY)];
     const int slot = blockIdx.z % a.ns;
@@ -337,7 +399,17 @@ k_fdown(GArgs<T> a, int nrhs, int rch) {
     int tx, ty;
     xcd_tile(tx, ty);
 #define EH_FD(FI, KI, WX, WY, NM, MX) down_body<T, FI, KI, WX, WY, NM, MX, CX, CY, NT>(a, slot, lds, r0, r1, tx, ty)
-    if constexpr (FINE && PB) {
+    if constexpr (!std::is_same_v<CA, NoCpl>) {
+#define EH_FDC(NM, MX) down_body<T, true, 0, 1, 1, NM, MX, CX, CY, NT, true>(a, slot, lds, r0, r1, tx, ty, cp)
+        if (a.mixed) {
+            if (kind == 0) EH_FDC(1, true);
+            else EH_FDC(2, true);
+        } else {
+            if (kind == 0) EH_FDC(1, false);
+            else EH_FDC(2, false);
+        }
+#undef EH_FDC
+    } else if constexpr (FINE && PB) {
         if (a.tilde) {
             if (a.mixed) EH_FD(true, 2, 1, 1, 0, true);
             else EH_FD(true, 2, 1, 1, 0, false);

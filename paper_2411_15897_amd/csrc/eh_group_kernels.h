@@ -495,6 +495,17 @@ struct CoupleArgs {
     int64_t rss;
 };
 
+// The same values formed by the fine down leg of the shear blocks while it
+// stages its points (a.d, a.ru, a.g, a.vg, a.ih as there; 2D).
+template <class T>
+struct CplArgs {
+    CoupleArgs c;
+    const cplx<T>* ep;
+    int64_t vr, ve;
+    int n0, n1;              // cells
+};
+struct NoCpl {};
+
 template <class T>
 __global__ void __launch_bounds__(256)
 k_gcouple(CoupleArgs a, Dims dc, const cplx<T>* __restrict__ ep, int nrhs, int64_t vr, int64_t ve, int rch) {

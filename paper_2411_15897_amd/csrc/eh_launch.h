@@ -59,9 +59,10 @@ dim3 ggrid(const GArgs<T>& a, const dim3& blk, int nrhs, int& rch) {
 }
 
 // Fused down leg on level l with tile configuration cfg: a.d / a.dc = levels
-// l / l+1, a.f = f_l, a.out = f_{l+1}. 
+// l / l+1, a.f = f_l, a.out = f_{l+1}.  With cpl (l = 0, shear blocks) the
+// launch forms and stores f_0 itself.
 template <class T>
-void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrhs);
+void launch_fdown(hipStream_t stream, const GArgs<T>& a, int l, int cfg, int nrhs, const CplArgs<T>* cpl = nullptr);
 
 // Fused up leg on level l with nu_post (1 or 2) sweeps: a.f = f_l, a.u =
 // e_{l+1}, a.out = e_l.

@@ -1262,7 +1262,7 @@ inline bool fused_cycle(const eh_ctx* c, bool guess) {
 
 template <class T>
 void fused_level(eh_ctx* c, const int* kinds, int ns, int l, const void* const* f, const int64_t* vf,
-                 void* const* out, const int64_t* vo, int nrhs) {
+                 void* const* out, const int64_t* vo, int nrhs, const CplArgs<T>* cpl = nullptr) {
     const bool P = kinds[0] == c->dim;
     const int grp = group_of(c, kinds[0]);
     const int lt = std::min(l, kMaxLevels - 1);
@@ -1289,8 +1289,10 @@ void fused_level(eh_ctx* c, const int* kinds, int ns, int l, const void* const* 
             a.out[s] = (cplx<T>*)cf[s];
             a.vo[s] = vcv[s];
         }
+        // (with cpl f is written instead of read, r_u and e_p read)
+        if (cpl) vdown += (double)(c->off[c->dim] * sizeof(c128) + c->ncell * cs);
         Timed tm(c, l == 0 ? KC_FINE_DOWN : KC_COARSE_DOWN, cbytes + nrhs * vdown);
-        launch_fdown<T>(c->s, a, l, c->fcfg[grp][lt][0], nrhs);
+        launch_fdown<T>(c->s, a, l, c->fcfg[grp][lt][0], nrhs, cpl);
         HIPCHK(hipGetLastError());
     }
     gcycle<T>(c, kinds, ns, l + 1, cf, vcv, ce, vcv, false, nrhs);
@@ -1857,6 +1859,23 @@ void residual_H(eh_ctx* c, const c128* x, const c128* b, c128* r, int nrhs, c128
     HIPCHK(hipGetLastError());
 }
 
+// Whether the shear blocks' fine down leg forms its right-hand side itself:
+// with fused legs and a level below (n is even there, so the coarse points
+// own two fine points each per axis and every fine point has an owner).
+// Below kCplSmall
+// cells times right-hand sides the launch saved counts (preconditioner, us,
+// own launch / in the leg: 64^2 56 / 52, 128^2 x 4 92 / 86, 256^2 113 / 109,
+// 512^2 x 4 232 / 226, 1024^2 312 / 311); above kCplLarge, out of the 256 MB
+// cache, the pass over memory (1024^2 x 16 1720 / 1682, 2048^2 x 4 1990 / 1970,
+// x 16 6125 / 5990).  Between them f comes back from the cache and r_u under
+// the tiles' halos costs more (512^2 x 16 542 / 546, 2048^2 915 / 929).
+// Bitwise the same either way.
+constexpr int64_t kCplSmall = 1 << 20, kCplLarge = 1 << 24;
+bool couple_in_leg(const eh_ctx* c, int nrhs) {
+    const int64_t n = c->ncell * nrhs;
+    return fused_cycle(c, false) && c->o.levels >= 2 && (n <= kCplSmall || n >= kCplLarge);
+}
+
 // z = P^{-1} D_L r: r complex128 (stride vr), z multigrid precision (stride vz)
 //
 // With rs given, the input of RHS q is rs[q * rss] times the stored r (an
@@ -1927,6 +1946,11 @@ void apply_M(eh_ctx* c, const c128* r, int64_t vr, void* z, int64_t vz, int nrhs
         ca.vg[k] = Lk.d.np();
         ca.ih[k] = 1.0 / c->h[k];
         by += (double)nrhs * (Lk.d.np() * (16.0 + sizeof(cplx<T>)) + c->ncell * sizeof(cplx<T>));
+    }
+    if (couple_in_leg(c, nrhs)) {
+        const CplArgs<T> cp{ca, (const cplx<T>*)ep, vr, vz, (int)c->n[0], (int)c->n[1]};
+        fused_level<T>(c, kinds, d, 0, f, vf, out, vo, nrhs, &cp);
+        return;
     }
     {
         Timed tm(c, KC_COUPLE, by);
