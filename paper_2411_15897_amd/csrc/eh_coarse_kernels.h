@@ -104,10 +104,12 @@ k_bt_couple_dense(BTPart pt, const c128* __restrict__ st, const BTBlock* __restr
 // The couplings of every row to its neighbouring groups as entry-major lists
 // in elimination order (perm: elimination order -> point, inv the other
 // way): coefficient and the neighbour's place, rows with fewer entries
-// filled with zeros.
+// filled with zero coefficients at a place on the other side of the coupling
+// (removed entries are 0 .. n0 - 1, kept ones follow), which k_bt_sparse finds
+// written: its own side still holds what an earlier solve left, or nothing.
 __global__ void __launch_bounds__(256)
 k_bt_couple_list(BTPart pt, const c128* __restrict__ st, const int* __restrict__ perm, const int* __restrict__ inv,
-                 int ne, c128* __restrict__ k, int* __restrict__ at) {
+                 int ne, int n0, c128* __restrict__ k, int* __restrict__ at) {
     const int N = (int)pt.d.np();
     const int q = blockIdx.x * 256 + threadIdx.x;
     if (q >= N) return;
@@ -126,7 +128,7 @@ k_bt_couple_list(BTPart pt, const c128* __restrict__ st, const int* __restrict__
     }
     for (; e < ne; ++e) {
         k[(int64_t)e * N + q] = mk(0.0, 0.0);
-        at[(int64_t)e * N + q] = q;
+        at[(int64_t)e * N + q] = q < n0 ? n0 : 0;
     }
 }
 

@@ -724,7 +724,7 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
         T.lk = c->alloc<c128>((size_t)T.ne * T.N);
         T.lat = c->alloc<int>((size_t)T.ne * T.N);
         hipLaunchKernelGGL(k_bt_couple_list, dim3((unsigned)((T.N + 255) / 256)), dim3(256), 0, 0, pt, st, T.perm, dinv,
-                           T.ne, T.lk, T.lat);
+                           T.ne, (int)T.n0, T.lk, T.lat);
         HIPCHK(hipGetLastError());
         HIPCHK(hipDeviceSynchronize());
         c->release(dinv);

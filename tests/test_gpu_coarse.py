@@ -231,3 +231,22 @@ def test_dense_inverse_with_small_pivot_blocks():
         cond = np.linalg.cond(X.toarray())
         assert rel(e, spla.splu(X).solve(f)) <= max(1e-10, 1e-11 * cond), b
     gpu.close()
+
+
+@pytest.mark.parametrize("n,solver", [
+    ((150, 151), "bt"),      # the first level's couplings from lists
+    ((18, 20, 23), "bt"),    # and in 3D
+    ((50, 41), "bt"),
+    ((24, 20), "dense"),
+])
+@pytest.mark.parametrize("nrhs", [1, 4])
+def test_no_trace_of_an_earlier_solve(n, solver, nrhs):
+    """What a solve leaves in the work vectors (here NaN everywhere, as fresh
+    memory may hold) does not enter the next one: bitwise the same."""
+    gpu, s = make(n, seed=12, levels=1, alpha=0.3, mg_precision=64, coarse_solver=solver)
+    for b in range(s.dim + 1):
+        f = to_dev(crand((nrhs, block_op(s, b, 0.3).shape[0]), 80 + b))
+        e = gpu.block_cycle(b, f)
+        assert torch.isnan(torch.view_as_real(gpu.block_cycle(b, torch.full_like(f, float("nan"))))).any()
+        assert torch.equal(gpu.block_cycle(b, f), e), b
+    gpu.close()
