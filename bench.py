@@ -174,7 +174,8 @@ CLASS_KERNELS = {
                 "eh::k_gtransfer<", "eh::k_bt_rows<", "eh::k_bt_sparse<", "eh::k_gfine3_lds<",
                 "eh::k_gstencil3_lds<", "eh::k_grestrict3_lds<", "eh::k_gprolong3_lds<"), None),
 }
-DEFAULT_SOURCES = ["paper_2411_15897_amd/csrc/eh_fused_kernels.h", "paper_2411_15897_amd/csrc/eh_group_kernels.h",
+DEFAULT_SOURCES = ["paper_2411_15897_amd/csrc/eh_fused_kernels.h", "paper_2411_15897_amd/csrc/eh_launch.h",
+                   "paper_2411_15897_amd/csrc/eh_group_kernels.h",
                    "paper_2411_15897_amd/csrc/eh_mg_kernels.h", "paper_2411_15897_amd/csrc/eh_op_kernels.h",
                    "paper_2411_15897_amd/csrc/eh_common.h"]
 _FINE3 = DEFAULT_SOURCES + ["paper_2411_15897_amd/csrc/eh_fine3_kernels.h"]

@@ -87,14 +87,18 @@ typedef struct {
                                H_p = B B^T + A_p C (eq. Hp), the paper's choice; 1: the alternative of the
                                Remark after eq. prec, A~_p = B A_f(mu) B^T - w^2 M_p, in both */
     int coarse_solver;      /* direct solve of the coarsest level (Section 4.4.1), FP64 either way:
-                               1: explicit dense inverse (Gauss-Jordan, partial pivoting), applied as a
-                                  matrix-vector product; at most 6000 points per block;
-                               2: block-tridiagonal LU over groups of planes (lines in 2D) normal to one
-                                  axis, each group as wide as the coarse stencil's half width along it;
-                                  Schur complements inverted by blocked Gauss-Jordan (partial pivoting
-                                  inside 32 x 32 pivot blocks), applied as a forward and a back sweep of
-                                  one launch per group; the factors are checked at create by one solve
-                                  whose FP64 residual must stay below 1e-8 (EH_ERR_ARG otherwise);
+                               1: explicit dense inverse (blocked Gauss-Jordan, checked at create by one
+                                  product whose residual must stay below 1e-11, else formed again with
+                                  partial pivoting over all rows), applied as a matrix-vector product;
+                                  at most 6000 points per block;
+                               2: block elimination over groups of planes (lines in 2D) normal to one
+                                  axis, each group as wide as the coarse stencil's half width along it:
+                                  every other group per level, the last ones as one dense inverse, one
+                                  launch per level down and back up; Schur complements inverted by
+                                  blocked Gauss-Jordan (partial pivoting inside 32 x 32 pivot blocks); the
+                                  factors are checked at create by one solve whose FP64 residual must
+                                  stay below 1e-8 -- else, or where they do not fit, the groups are
+                                  eliminated one after the other, and EH_ERR_ARG if that fails too;
                                0: 1 while every block's coarsest grid has at most 6000 points, else 2 */
     int drop_converged;     /* 1: at each FGMRES restart, right-hand sides whose true residual is below tol
                                leave the batch -- the others are gathered into the first slots and every
