@@ -150,7 +150,8 @@ def _gfine(*modes):
 
 
 CLASS_KERNELS = {
-    "krylov": (("eh::k_gs<", "eh::k_reduce_partials", "eh::k_xupdate<"), ("eh::k_gs<", "eh::k_xupdate<")),
+    "krylov": (("eh::k_gs<", "eh::k_gs2_tiles(", "eh::k_reduce_partials", "eh::k_xupdate<"),
+               ("eh::k_gs<", "eh::k_gs2_tiles(", "eh::k_xupdate<")),
     "fine_down": (("eh::k_fdown<float, true", "eh::k_fdown<double, true"), None),
     "fine_up": (("eh::k_fup<float, true", "eh::k_fup<double, true"), None),
     "coarse_down": (("eh::k_fdown<float, false", "eh::k_fdown<double, false"), None),

@@ -97,4 +97,22 @@ __device__ __forceinline__ int wave_sums(double (&v)[V]) {
     }
 }
 
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own
+// L2.  Renumber the tiles of one slot so that every XCD gets a contiguous
+// run of tiles in row-major order: neighbouring tiles, whose halos
+// overlap, then read them through the same L2.  A bijection on the tiles.
+__device__ __forceinline__ void xcd_tile(int& tx, int& ty) {
+    const int n = gridDim.x * gridDim.y;
+    const int b = blockIdx.y * gridDim.x + blockIdx.x;
+    int t = b;
+    if (n >= 16) {
+        const int m = (n + 7) / 8;             // tiles per XCD, rounded up
+        const int full = n - 8 * (m - 1);      // XCDs that get m tiles
+        const int r = b % 8, q = b / 8;
+        t = r < full ? r * m + q : full * m + (r - full) * (m - 1) + q;
+    }
+    ty = t / gridDim.x;
+    tx = t - ty * gridDim.x;
+}
+
 }  // namespace eh

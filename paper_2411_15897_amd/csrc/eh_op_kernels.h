@@ -29,16 +29,16 @@ struct ResArgs {
     int blk0;            // first workgroup index of this launch
 };
 
-__device__ __forceinline__ void res_partial(const ResArgs& ra, int r, int kz, double v) {
+__device__ __forceinline__ void res_partial(const ResArgs& ra, int r, int bx, int by, int kz, double v) {
     __shared__ double sv[4];
     const int tid = threadIdx.y * blockDim.x + threadIdx.x;
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     if ((tid & 63) == 0) sv[tid >> 6] = v;
     __syncthreads();
     if (tid == 0) {
-        // the workgroup's place in the plane grid (kz = its plane), not its
-        // chunk of the batch: every chunk writes the rows of its own RHS
-        const int blk = ra.blk0 + (kz * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        // the workgroup's place (bx, by) in the plane grid (kz = its plane), not
+        // its chunk of the batch: every chunk writes the rows of its own RHS
+        const int blk = ra.blk0 + (kz * gridDim.y + by) * gridDim.x + bx;
         ra.partial[(int64_t)r * ra.nblk + blk] = mk((sv[0] + sv[1]) + (sv[2] + sv[3]), 0.0);
     }
     __syncthreads();       // sv is reused by the next right-hand side
@@ -162,10 +162,10 @@ __device__ __forceinline__ void gs_first_pass(const DotArgs& da, int r, int64_t 
     __syncthreads();   // red is reused by the next right-hand side
 }
 
-// The UPD epilogue for right-hand side r: the second Gram-Schmidt pass on the
-// w the launch has just formed, v = w - sum_t coef_t V_t over the thread's
-// degrees of freedom, two columns' loads in flight.  Returns the thread's
-// part of |v|^2.
+// The second Gram-Schmidt pass for right-hand side r: v = w - sum_t coef_t V_t
+// over the thread's degrees of freedom, two columns' loads in flight.  Returns
+// the thread's part of |v|^2.  The w in yk has just been formed (OP_UPDATE) or
+// read (k_gs2_tiles): fixed multiply-adds, so that both give the same bits.
 template <int NE>
 __device__ __forceinline__ double gs_update(const DotArgs& da, int r, int64_t vs, const bool* has, const int64_t* at,
                                             c128* yk) {
@@ -184,12 +184,13 @@ __device__ __forceinline__ double gs_update(const DotArgs& da, int r, int64_t vs
             if (t + q >= J) break;
             const c128 c = cf[t + q];
 #pragma unroll
-            for (int e = 0; e < NE; ++e) yk[e] = yk[e] - c * v[q][e];
+            for (int e = 0; e < NE; ++e) yk[e] = cfma(mk(-c.re, -c.im), v[q][e], yk[e]);
         }
     }
     double a = 0.0;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) a += has[e] ? yk[e].re * yk[e].re + yk[e].im * yk[e].im : 0.0;
+    for (int e = 0; e < NE; ++e)
+        if (has[e]) a = fmat(yk[e].im, yk[e].im, fmat(yk[e].re, yk[e].re, a));
     return a;
 }
 
@@ -329,13 +330,37 @@ k_op2_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
             for (int e = 0; e < 3; ++e)
                 if (has[e]) y[r * vs_out + at[e]] = yk[e];
         }
-        if (RES || UPD) res_partial(ra, r, 0, rr);
+        if (RES || UPD) res_partial(ra, r, blockIdx.x, blockIdx.y, 0, rr);
         if (DOTS) {
             const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
             gs_first_pass<3>(da, r, vs_out, has, at, yk, blk, (int64_t)gridDim.x * gridDim.y, t0,
                              min(da.J, t0 + da.jc));
         }
     }
+}
+
+// The second Gram-Schmidt pass on a stored w: v = w - sum_t coef_t V_t and
+// partial sums of |v|^2, the degrees of freedom owned as in k_op2_lds, so that
+// the sums are the same trees as OP_UPDATE's.  Grid (x tiles, y tiles,
+// right-hand sides).
+__global__ void __launch_bounds__(256)
+k_gs2_tiles(OpArgs o, const c128* __restrict__ w, c128* __restrict__ v, int64_t vs, ResArgs ra, DotArgs da) {
+    int bx, by;
+    xcd_tile(bx, by);
+    const int i = bx * OTX + threadIdx.x % OTX, j = by * OTY + threadIdx.x / OTX;
+    const int r = blockIdx.z;
+    const int n0 = o.dc.g[0], n1 = o.dc.g[1];
+    const bool has[3] = {i <= n0 && j < n1, i < n0 && j <= n1, i < n0 && j < n1};
+    const int64_t at[3] = {o.off[0] + (int64_t)j * (n0 + 1) + i, o.off[1] + (int64_t)j * n0 + i,
+                           o.off[2] + (int64_t)j * n0 + i};
+    c128 y[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) y[e] = has[e] ? w[r * vs + at[e]] : mk(0.0, 0.0);
+    const double a = gs_update<3>(da, r, vs, has, at, y);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+        if (has[e]) v[r * vs + at[e]] = y[e];
+    res_partial(ra, r, bx, by, 0, a);
 }
 
 // 3D, several right-hand sides per workgroup, each right-hand side's plane
@@ -501,7 +526,7 @@ k_op3_lds(OpArgs o, const cplx<Tin>* __restrict__ x, c128* __restrict__ y, int n
             }
             y[r * vs_out + o.off[3] + pc] = yv;
         }
-        if (RES) res_partial(ra, r, k, rr);
+        if (RES) res_partial(ra, r, blockIdx.x, blockIdx.y, k, rr);
     }
 }
 

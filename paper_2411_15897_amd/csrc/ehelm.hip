@@ -1822,21 +1822,29 @@ int apply_H_dots(eh_ctx* c, const void* z, c128* w, int nrhs, const c128* V, int
 }
 
 // v = H z - sum_t coef_t V_t and nrm = |v|^2 per right-hand side (2D): the
-// second Gram-Schmidt pass with H z formed again.
+// second Gram-Schmidt pass on w = H z, read, or formed again where w is null.
+// Bitwise the same either way.
 template <class Tin>
-void apply_H_update(eh_ctx* c, const void* z, c128* v, int nrhs, const c128* V, int64_t vstep, int J, const c128* coef,
-                    c128* nrm) {
-    double coefb = 8.0 * c->ncell;
-    for (int k = 0; k < c->dim; ++k) coefb += (double)c->fsize[k] * (8.0 * c->dim + 16.0);
-    Timed tm(c, KC_OPERATOR, coefb + (double)nrhs * c->ndof * (sizeof(cplx<Tin>) + (J + 1) * sizeof(c128)));
+void apply_H_update(eh_ctx* c, const void* z, const c128* w, c128* v, int nrhs, const c128* V, int64_t vstep, int J,
+                    const c128* coef, c128* nrm) {
     const dim3 g = op_grid(c);
     const int nblk = (int)(g.x * g.y);
-    const int rch = rhs_chunk(nblk, 1, nrhs);
-    const dim3 gc(g.x, g.y, (unsigned)((std::max(nrhs, 1) + rch - 1) / rch));
     const ResArgs ra{nullptr, c->res_partial, nblk, 0};
     const DotArgs da{V, vstep, J, 0, 1, nullptr, coef};
-    hipLaunchKernelGGL((k_op2_lds<Tin, OP_UPDATE>), gc, dim3(256), 0, c->s, op_args(c), (const cplx<Tin>*)z, v, nrhs,
-                       c->ndof, c->ndof, ra, rch, da);
+    double by = (double)nrhs * c->ndof * (J + 1) * sizeof(c128);
+    if (w) by += (double)nrhs * c->ndof * sizeof(c128);
+    else by += 8.0 * c->ncell + (double)nrhs * c->ndof * sizeof(cplx<Tin>);
+    for (int k = 0; k < c->dim && !w; ++k) by += (double)c->fsize[k] * (8.0 * c->dim + 16.0);
+    Timed tm(c, w ? KC_KRYLOV : KC_OPERATOR, by);
+    if (w) {
+        hipLaunchKernelGGL(k_gs2_tiles, dim3(g.x, g.y, (unsigned)nrhs), dim3(256), 0, c->s, op_args(c), w, v, c->ndof,
+                           ra, da);
+    } else {
+        const int rch = rhs_chunk(nblk, 1, nrhs);
+        const dim3 gc(g.x, g.y, (unsigned)((std::max(nrhs, 1) + rch - 1) / rch));
+        hipLaunchKernelGGL((k_op2_lds<Tin, OP_UPDATE>), gc, dim3(256), 0, c->s, op_args(c), (const cplx<Tin>*)z, v,
+                           nrhs, c->ndof, c->ndof, ra, rch, da);
+    }
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(k_reduce_partials, dim3(1, nrhs), dim3(256), 0, c->s, nblk, 1, nrhs, c->res_partial, nrm);
     HIPCHK(hipGetLastError());
@@ -2066,6 +2074,14 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
     return 0;
 }
 
+// 2D vectors of kTileSum entries or more (256^2 cells; 325 operator tiles) take
+// the second Gram-Schmidt pass by operator tiles (apply_H_update), whose sums
+// do not depend on how a batch forms w; shorter ones by k_gs, w always stored.
+// One source, us per FGMRES step, tiles / k_gs: 128^2 99.8 / 96.6, 256^2 131.2 /
+// 133.4, 1024^2 449 / 446, 2048^2 1354 / 1351.
+constexpr int64_t kTileSum = 3 << 16;
+// A batch of kAgainBytes per basis vector, out of the 256 MB cache with the
+// vectors around it, forms w again.
 constexpr double kAgainBytes = 128.0 * 1024 * 1024;
 
 // Flexible GMRES(m) with right preconditioning, x_0 = 0.  Every Arnoldi
@@ -2087,10 +2103,10 @@ constexpr double kAgainBytes = 128.0 * 1024 * 1024;
 //                             sums in d1, the number of workgroups whose
 //                             partial sums are in c->partial, or -1 where the
 //                             problem does not provide it
-//   op_upd(z_j, v, nb, V, vstep, J, coef, nrm)
+//   op_upd(z_j, W, v, nb, V, vstep, J, coef, nrm)
 //                             v = X z_j - sum_t coef_t V_t and nrm = |v|^2,
-//                             after an op_zd without W (op_upd chosen by the
-//                             caller through `again`)
+//                             X z_j = W, or formed again after an op_zd
+//                             without W (used with `tiled`)
 //   prec(v, sv, z_j, nb)      z_j = M (sv[q * (m+1)] v) per right-hand side q
 //   op_res(x, b, r, nrm, nb)  r = b - X x and nrm = |r|^2 in one pass, or false
 //                             where the problem does not provide it
@@ -2108,7 +2124,7 @@ constexpr double kAgainBytes = 128.0 * 1024 * 1024;
 template <class T, class OpX, class OpZ, class OpZD, class OpUpd, class Prec, class OpRes>
 eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, OpUpd op_upd, Prec prec, bool graphs,
                       const c128* b, c128* x, int nrhs, double tol, int maxit, eh_info* info, OpRes op_res,
-                      bool recompute) {
+                      bool tiled) {
     const int m = c->o.restart;
     int nb = nrhs;                               // right-hand sides in the batch
     int64_t vstep = (int64_t)nb * n;             // distance between basis vectors
@@ -2123,9 +2139,8 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, OpUp
     unsigned rgrid = (unsigned)((nb + 63) / 64);
     // w = X z_j is formed again for the second Gram-Schmidt pass instead of
     // written and read back where its vectors pass through memory and several
-    // right-hand sides share the coefficients (decided by the call, so that a
-    // batch that shrinks keeps its arithmetic)
-    const bool again = recompute && nrhs >= 4 && (double)nrhs * (double)n * sizeof(c128) >= kAgainBytes;
+    // right-hand sides share the coefficients
+    const bool again = tiled && nrhs >= 4 && (double)nrhs * (double)n * sizeof(c128) >= kAgainBytes;
     // predicted estimate below this multiple of tol: wait for the step
     constexpr double kNear = 3.0;
     HIPCHK(hipMemsetAsync(x, 0, (size_t)nrhs * n * sizeof(c128), c->s));
@@ -2248,8 +2263,8 @@ eh_status fgmres_core(eh_ctx* c, int64_t n, OpX op_x, OpZ op_z, OpZD op_zd, OpUp
                 hipLaunchKernelGGL(k_arn_coef, dim3(nb), dim3(ARN_THREADS), 0, c->s, S, j,
                                    (const c128*)(fold > 0 ? c->partial : d1), fold, d2);
                 HIPCHK(hipGetLastError());
-                if (again) {
-                    op_upd(Zj, Vj + vstep, nb, c->V, vstep, j + 1, d2, d3);
+                if (tiled) {
+                    op_upd(Zj, again ? nullptr : c->W, Vj + vstep, nb, c->V, vstep, j + 1, d2, d3);
                     fold = 0;
                 } else {
                     fold = gs_pass<2>(c, n, j + 1, nb, c->V, c->W, d2, d3, Vj + vstep, NRM_FOLD);
@@ -2360,11 +2375,11 @@ eh_status solve_impl(eh_ctx* c, const c128* b, c128* x, int nrhs, double tol, in
     auto op_zd = [&](const cplx<T>* z, c128* w, int nb, const c128* V, int64_t vstep, int J, c128* d1) {
         return apply_H_dots<T>(c, z, w, nb, V, vstep, J, d1);
     };
-    auto op_upd = [&](const cplx<T>* z, c128* v, int nb, const c128* V, int64_t vstep, int J, const c128* coef,
-                      c128* nrm) { apply_H_update<T>(c, z, v, nb, V, vstep, J, coef, nrm); };
-    const bool again = c->dim == 2 && m <= OP_MAXJ;
+    auto op_upd = [&](const cplx<T>* z, const c128* w, c128* v, int nb, const c128* V, int64_t vstep, int J,
+                      const c128* coef, c128* nrm) { apply_H_update<T>(c, z, w, v, nb, V, vstep, J, coef, nrm); };
+    const bool tiled = c->dim == 2 && m <= OP_MAXJ && n >= kTileSum;
     return fgmres_core<T>(c, n, op_x, op_z, op_zd, op_upd, prec, c->o.graphs != 0, b, x, nrhs, tol, maxit, info, op_res,
-                          again);
+                          tiled);
 }
 
 eh_status fail(eh_ctx* c, eh_status st, const std::string& msg);
@@ -2412,7 +2427,7 @@ eh_status block_solve_impl(eh_ctx* c, int block, const c128* f, c128* x, int nrh
     };
     auto no_res = [](const c128*, const c128*, c128*, c128*, int) { return false; };
     auto no_zd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, c128*) { return -1; };
-    auto no_upd = [](const cplx<T>*, c128*, int, const c128*, int64_t, int, const c128*, c128*) {};
+    auto no_upd = [](const cplx<T>*, const c128*, c128*, int, const c128*, int64_t, int, const c128*, c128*) {};
     return fgmres_core<T>(c, n, op_x, op_z, no_zd, no_upd, prec, false, f, x, nrhs, tol, maxit, info, no_res, false);
 }
 

@@ -91,3 +91,40 @@ def test_second_pass_forms_the_vector_again(n, nsrc, restart):
         assert info[q]["converged"] and rr < 1e-6
         assert abs(info[q]["relres_est"] - rr) <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("n,nsrc,precision", [
+    ((848, 840), 4, 32),     # the batch forms H z twice, a source alone writes and reads it
+    ((624, 600), 8, 64),
+    ((256, 256), 43, 32),    # the shortest vectors summed by tiles
+    ((256, 248), 44, 32),    # just shorter
+])
+def test_batch_gives_each_source_what_it_gets_alone(n, nsrc, precision):
+    """Batches above 128 MiB per basis vector, of which sources leave on the
+    way: x and the counts of every source are bitwise those it gets alone,
+    in a pair, and with drop_converged off."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    ndof = (n[0] + 1) * n[1] + n[0] * (n[1] + 1) + n[0] * n[1]
+    assert nsrc * ndof * 16 >= 128 * 2**20
+    h = (1.0, 1.0)
+    vp, vs, rho = W.layered_medium(n, seed=5)
+    omega = W.omega_for_ppw(vs, h, 12.0)
+    kw = dict(levels=4, alpha=0.5, restart=3, abc_width=20, abc_sides=W.abc_all_but_top(2),
+              mg_precision=precision)
+    # from the middle of the top to inside the absorbing layer at the bottom
+    b = W.point_source_rhs(n, h, [(1, (n[0] // 2 + q, 1 + q * (n[1] - 3) // (nsrc - 1))) for q in range(nsrc)])
+    bt = torch.from_numpy(b).cuda()
+    s = ElasticHelmholtz(n, h, vp, vs, rho, omega, **kw)
+    x, info = s.solve(bt, tol=1e-3, maxit=90)
+    its = [i["iters"] for i in info]
+    assert min(its) < max(its)
+    for q in (0, nsrc // 2, nsrc - 1):
+        x1, i1 = s.solve(bt[q:q + 1], tol=1e-3, maxit=90)
+        assert i1[0]["iters"] == its[q] and torch.equal(x1[0], x[q]), q
+    x2, _ = s.solve(bt[:2], tol=1e-3, maxit=90)
+    assert torch.equal(x2, x[:2])
+    s.close()
+    s = ElasticHelmholtz(n, h, vp, vs, rho, omega, drop_converged=False, **kw)
+    xn, info = s.solve(bt, tol=1e-3, maxit=90)
+    assert [i["iters"] for i in info] == its and torch.equal(xn, x)
+    s.close()
