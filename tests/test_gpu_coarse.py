@@ -250,3 +250,70 @@ def test_no_trace_of_an_earlier_solve(n, solver, nrhs):
         assert torch.isnan(torch.view_as_real(gpu.block_cycle(b, torch.full_like(f, float("nan"))))).any()
         assert torch.equal(gpu.block_cycle(b, f), e), b
     gpu.close()
+
+
+@pytest.mark.parametrize("n", [(24, 20), (11, 12)])
+def test_dense_inverse_with_pivoting_over_all_rows(n):
+    """The blocked inverse pivots inside its 32 x 32 blocks only.  Without
+    shift and attenuation, at the frequency where the stiffness of the
+    pressure block's diagonal equals the mass, its leading block is singular
+    (asserted here) while the matrix is not, so the inverse has to come from
+    the elimination that pivots over all rows: against splu within 1e-11,
+    the residual the set-up asks of the blocked form, times the condition."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    say("dense inverse, pivoting over all rows", n)
+    h, shape = (1.0, 1.0), tuple(reversed(n))
+    vp, vs, rho = np.full(shape, 2.0), np.full(shape, 1.0), np.ones(shape)
+    # (1 + mu / (lambda + mu)) * 4 = omega^2 rho / (lambda + mu), lambda + mu = 3
+    omega = float(np.sqrt(4.0 * (1.0 + 1.0 / 3.0) * 3.0))
+    s = ElasticSystem(n, h, vp, vs, rho, omega, 0, 0xF, gamma0=0.0)
+    lead = np.linalg.svd(s.H_p(0.0).toarray()[:32, :32], compute_uv=False)
+    assert lead[-1] <= 1e-14 * lead[0]
+    gpu = ElasticHelmholtz(n, h, vp, vs, rho, omega, levels=1, alpha=0.0, abc_width=0, abc_sides=0xF, gamma0=0.0,
+                           mg_precision=64, coarse_solver="dense")
+    for b in range(3):
+        X = block_op(s, b, 0.0).tocsc()
+        cond = np.linalg.cond(X.toarray())
+        assert cond < 1e3
+        f = crand((3, X.shape[0]), 95 + b)
+        e = gpu.block_cycle(b, to_dev(f)).cpu().numpy()
+        for k in range(3):
+            assert rel(e[k], spla.splu(X).solve(f[k])) <= 1e-11 * max(cond, 10.0), (b, k)
+    gpu.close()
+
+
+@pytest.mark.parametrize("n,k,delta,limit", [
+    ((40, 50), 13, 0.0, 1e-11),      # 50 groups of 40
+    ((150, 160), 20, 0.0, 5e-11),    # matrices large enough for the first level's lists, dropped with them
+])
+def test_groups_eliminated_one_after_the_other(n, k, delta, limit):
+    """A line of cells whose own block of the pressure operator is singular
+    to `delta` (asserted here), the third of the chain: removing every other
+    group meets it as it is, removing the groups one after the other adds a
+    Schur complement first.  The lines around it are stiff, no shift, no
+    attenuation.  Limits: 30 times and more the residual of a NumPy replay
+    of that order with these right-hand sides (2e-13, 1.5e-12)."""
+    from paper_2411_15897_amd import ElasticHelmholtz
+    say("groups one after the other", n)
+    h, rng = (1.0, 1.0), np.random.default_rng(0)
+    line = 3.0 + rng.random(n[1])
+    line[2] = 1.0
+    vs = np.repeat(line[:, None], n[0], 1)
+    vp, rho = 2.0 * vs, np.ones_like(vs)
+    # the k-th eigenvalue of line 2: lambda + mu = 3, mu = 1
+    omega = float(np.sqrt(3.0 * (4.0 / 3.0 * (4.0 - 2.0 * np.cos(k * np.pi / (n[0] + 1))) - delta)))
+    s = ElasticSystem(n, h, vp, vs, rho, omega, 0, 0xF, gamma0=0.0)
+    X = s.H_p(0.0).tocsr()
+    own = slice(2 * n[0], 3 * n[0])
+    assert abs(np.linalg.svd(X[own, own].toarray(), compute_uv=False)[-1] - delta) <= 1e-12
+    gpu = ElasticHelmholtz(n, h, vp, vs, rho, omega, levels=1, alpha=0.0, abc_width=0, abc_sides=0xF, gamma0=0.0,
+                           mg_precision=64, coarse_solver="bt")
+    f = crand((3, X.shape[0]), 99)
+    e = gpu.block_cycle(2, to_dev(f)).cpu().numpy()
+    e1 = gpu.block_cycle(2, to_dev(f[1])).cpu().numpy()
+    gpu.close()
+    for q in range(3):
+        res = rel(X @ e[q], f[q])
+        say(f"  residual {res:.1e}")
+        assert res <= limit, q
+    assert np.array_equal(e1, e[1])
