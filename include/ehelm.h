@@ -99,6 +99,8 @@ typedef struct {
                                   factors are checked at create by one solve whose FP64 residual must
                                   stay below 1e-8 -- else, or where they do not fit, the groups are
                                   eliminated one after the other, and EH_ERR_ARG if that fails too;
+                                  with mg_precision 64 that order is also tried from 1e-11 on, and the
+                                  one with the smaller residual kept;
                                0: 1 while every block's coarsest grid has at most 6000 points, else 2 */
     int drop_converged;     /* 1: at each FGMRES restart, right-hand sides whose true residual is below tol
                                leave the batch -- the others are gathered into the first slots and every

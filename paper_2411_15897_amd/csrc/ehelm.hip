@@ -894,7 +894,10 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
 // Elimination without pivoting between groups can meet a near-singular
 // Schur complement that another order avoids (or its larger factors may not
 // fit), so when the nested order fails the groups are eliminated one after
-// the other.
+// the other.  Under FP64 multigrid, whose cycles show every digit the coarsest
+// solve loses, so they are when the nested order's residual is above
+// kDenseCheck, and the order with the smaller residual stays.
+constexpr double kBtCheck = 1e-8;
 void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& d) {
     BTPart pt{};
     pt.d = d;
@@ -924,18 +927,31 @@ void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& 
         c->release(T.y);
         T = BTData{};
     };
-    double rel = 1.0;
-    try {
-        rel = bt_factor(c, B, st, pt, true);
-    } catch (const HipError& e) {
-        if (e.e != hipErrorOutOfMemory) throw;
-        (void)hipGetLastError();
-    }
-    if (!(rel < 1e-8)) {
+    // residual of a factorisation; where one that fails is no loss (`spare`),
+    // 1 when it does not fit
+    auto attempt = [&](bool nested, bool spare) {
+        try {
+            return bt_factor(c, B, st, pt, nested);
+        } catch (const HipError& e) {
+            if (!spare || e.e != hipErrorOutOfMemory) throw;
+            (void)hipGetLastError();
+            return 1.0;
+        }
+    };
+    const double enough = c->o.mg_precision == 32 ? kBtCheck : kDenseCheck;
+    double rel = attempt(true, true);
+    if (!(rel < enough)) {
+        const bool usable = rel < kBtCheck;
         drop();
-        rel = bt_factor(c, B, st, pt, false);
+        const double one = attempt(false, usable);
+        if (usable && !(one < rel)) {
+            drop();
+            rel = attempt(true, false);
+        } else {
+            rel = one;
+        }
     }
-    if (!(rel < 1e-8)) {
+    if (!(rel < kBtCheck)) {
         char msg[160];
         std::snprintf(msg, sizeof msg, "coarsest level: block-tridiagonal factorisation inaccurate (relative "
                       "residual %.3g)", rel);
