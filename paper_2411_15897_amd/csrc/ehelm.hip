@@ -530,61 +530,74 @@ void dense_apply_f64(eh_ctx* c, const Block& B, const c128* f, c128* x) {
     HIPCHK(hipGetLastError());
 }
 
-// Coarsest solves by explicit dense inverses (FP64), applied later as
-// matrix-vector products: every block inverted side by side by blocked
-// Gauss-Jordan, which pivots inside its 32 x 32 pivot blocks.  512^2 with 5
-// levels (three blocks of 1024-1056 points): 65 ms of one-column steps on
-// the device before, see the figures at k_gj_diag.  The inverse is checked
-// by one solve; a block whose residual is not below kDenseCheck (the pivot
-// blocks met too small pivots) is inverted again with pivoting over all
-// rows.
+// Blocked Gauss-Jordan inverses of the blocks b0 .. b1 - 1, side by side.  The
+// blocked form pivots inside its 32 x 32 pivot blocks only, so each inverse is
+// checked by one solve; again[b] tells the residual is not below kDenseCheck.
 constexpr double kDenseCheck = 1e-11;
-void build_dense(eh_ctx* c, c128* const* st, const Widths* w) {
-    std::vector<GJMat> mats;
+void dense_blocked(eh_ctx* c, c128* const* st, const Widths* w, int b0, int b1, bool* again) {
     int bpmax = 0;
-    for (int b = 0; b <= c->dim; ++b) {
-        const int64_t N = c->blk[b].lev.back().d.np();
-        // the dense inverse costs 16 N^2 bytes and O(N^3) setup: keep N modest
-        if (N > kDenseMax)
-            throw ArgError{"coarsest grid too large for the dense direct solve (use the block-tridiagonal solve)"};
-        bpmax = std::max(bpmax, pad_gj(N));
+    int64_t Nmax = 1;
+    for (int b = b0; b < b1; ++b) {
+        Block& B = c->blk[b];
+        B.Nc = B.lev.back().d.np();
+        bpmax = std::max(bpmax, pad_gj(B.Nc));
+        Nmax = std::max(Nmax, B.Nc);
     }
-    bool again[4] = {false, false, false, false};
-    {
-        GJScratch g(c, (size_t)bpmax * bpmax);
-        for (int b = 0; b <= c->dim; ++b) {
-            const Dims d = c->blk[b].lev.back().d;
-            GJMat m{g.get(), pad_gj(d.np())};
-            hipLaunchKernelGGL(k_gj_identity, dim3((unsigned)((m.bp + 255) / 256), (unsigned)m.bp), dim3(256), 0, 0,
-                               m.M, m.bp);
-            hipLaunchKernelGGL(k_dense_from_stencil, dim3(lin_grid(d.np(), 64, 1 << 30)), dim3(64), 0, 0, d, w[b],
-                               st[b], m.M, (int64_t)m.bp, 0);
-            HIPCHK(hipGetLastError());
-            mats.push_back(m);
-        }
-        gj_invert(g, mats);
-        const bool zero = g.zero_pivot();
-        std::vector<BTCopy> cp;
-        int64_t Nmax = 1;
-        for (int b = 0; b <= c->dim; ++b) {
-            Block& B = c->blk[b];
-            const int64_t N = B.lev.back().d.np();
-            B.Nc = N;
-            B.Ainv = c->alloc<c128>((size_t)N * N);
-            cp.push_back({mats[b].M, B.Ainv, (int)N, (int)N, mats[b].bp, (int)N});
-            Nmax = std::max(Nmax, N);
-        }
-        hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((Nmax + 255) / 256), (unsigned)Nmax, (unsigned)cp.size()),
-                           dim3(256), 0, 0, g.upload(cp));
+    GJScratch g(c, (size_t)bpmax * bpmax);
+    std::vector<GJMat> mats;
+    for (int b = b0; b < b1; ++b) {
+        const Dims d = c->blk[b].lev.back().d;
+        GJMat m{g.get(), pad_gj(d.np())};
+        hipLaunchKernelGGL(k_gj_identity, dim3((unsigned)((m.bp + 255) / 256), (unsigned)m.bp), dim3(256), 0, 0, m.M,
+                           m.bp);
+        hipLaunchKernelGGL(k_dense_from_stencil, dim3(lin_grid(d.np(), 64, 1 << 30)), dim3(64), 0, 0, d, w[b], st[b],
+                           m.M, (int64_t)m.bp, 0);
         HIPCHK(hipGetLastError());
-        for (int b = 0; b <= c->dim; ++b) {
-            const Block& B = c->blk[b];
-            const double rel = zero ? 1.0
-                                    : coarse_residual(c, st[b], w[b], B.lev.back().d, [&](const c128* f, c128* x) {
-                                          dense_apply_f64(c, B, f, x);
-                                      });
-            again[b] = !(rel < kDenseCheck);
+        mats.push_back(m);
+    }
+    gj_invert(g, mats);
+    const bool zero = g.zero_pivot();
+    std::vector<BTCopy> cp;
+    for (int b = b0; b < b1; ++b) {
+        Block& B = c->blk[b];
+        const int N = (int)B.Nc;
+        B.Ainv = c->alloc<c128>((size_t)N * N);
+        cp.push_back({mats[b - b0].M, B.Ainv, N, N, mats[b - b0].bp, N});
+    }
+    hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((Nmax + 255) / 256), (unsigned)Nmax, (unsigned)cp.size()),
+                       dim3(256), 0, 0, g.upload(cp));
+    HIPCHK(hipGetLastError());
+    for (int b = b0; b < b1; ++b) {
+        const Block& B = c->blk[b];
+        const double rel = zero ? 1.0 : coarse_residual(c, st[b], w[b], B.lev.back().d, [&](const c128* f, c128* x) {
+            dense_apply_f64(c, B, f, x);
+        });
+        again[b] = !(rel < kDenseCheck);
+    }
+}
+
+// Coarsest solves by explicit dense inverses (FP64), applied later as
+// matrix-vector products: every block inverted side by side, or one after the
+// other where the matrices do not fit together (512^2 with 5 levels, three
+// blocks of 1024-1056 points: one-column steps took 65 ms on the device).
+// A block whose blocked inverse fails its check is inverted again with
+// pivoting over all rows.
+void build_dense(eh_ctx* c, c128* const* st, const Widths* w) {
+    for (int b = 0; b <= c->dim; ++b)
+        // the dense inverse costs 16 N^2 bytes and O(N^3) setup: keep N modest
+        if (c->blk[b].lev.back().d.np() > kDenseMax)
+            throw ArgError{"coarsest grid too large for the dense direct solve (use the block-tridiagonal solve)"};
+    bool again[4] = {false, false, false, false};
+    try {
+        dense_blocked(c, st, w, 0, c->nblocks, again);
+    } catch (const HipError& e) {
+        if (e.e != hipErrorOutOfMemory) throw;
+        (void)hipGetLastError();
+        for (int b = 0; b < c->nblocks; ++b) {
+            c->release(c->blk[b].Ainv);
+            c->blk[b].Ainv = nullptr;
         }
+        for (int b = 0; b < c->nblocks; ++b) dense_blocked(c, st, w, b, b + 1, again);
     }
     for (int b = 0; b <= c->dim; ++b)
         if (again[b]) dense_pivoted(c, c->blk[b], st[b], w[b], c->blk[b].lev.back().d);
