@@ -100,7 +100,9 @@ typedef struct {
                                   stay below 1e-8 -- else, or where they do not fit, the groups are
                                   eliminated one after the other, and EH_ERR_ARG if that fails too;
                                   with mg_precision 64 that order is also tried from 1e-11 on, and the
-                                  one with the smaller residual kept;
+                                  one with the smaller residual kept; 16 bytes x 3 b^2 per group of
+                                  b points that way; 5 b^2 in levels, 3 b^2 or less where three b^2 of
+                                  every other group are 48 MB or more;
                                0: 1 while every block's coarsest grid has at most 6000 points, else 2 */
     int drop_converged;     /* 1: at each FGMRES restart, right-hand sides whose true residual is below tol
                                leave the batch -- the others are gathered into the first slots and every

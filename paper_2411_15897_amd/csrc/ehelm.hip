@@ -901,6 +901,17 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
     });
 }
 
+void drop_bt(eh_ctx* c, Block& B) {
+    BTData& T = B.btd;
+    c->release(T.mats);
+    c->release(T.perm);
+    c->release(T.tasks);
+    c->release(T.lk);
+    c->release(T.lat);
+    c->release(T.y);
+    T = BTData{};
+}
+
 // Coarsest solve by block elimination over groups of planes normal to the
 // axis that gives the smallest groups (eh_coarse_kernels.h); the factors are
 // checked by solving one system and recomputing its residual in FP64.
@@ -909,9 +920,10 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
 // fit), so when the nested order fails the groups are eliminated one after
 // the other.  Under FP64 multigrid, whose cycles show every digit the coarsest
 // solve loses, so they are when the nested order's residual is above
-// kDenseCheck, and the order with the smaller residual stays.
+// kDenseCheck, and the order with the smaller residual stays.  Without
+// `nested` only the other order is used.
 constexpr double kBtCheck = 1e-8;
-void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& d) {
+void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& d, bool nested) {
     BTPart pt{};
     pt.d = d;
     pt.w = w;
@@ -930,16 +942,6 @@ void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& 
     pt.gsz = w.w[best];
     pt.nb = (d.g[best] + pt.gsz - 1) / pt.gsz;
     pt.P = (int)(N / d.g[best]);
-    auto drop = [&]() {
-        BTData& T = B.btd;
-        c->release(T.mats);
-        c->release(T.perm);
-        c->release(T.tasks);
-        c->release(T.lk);
-        c->release(T.lat);
-        c->release(T.y);
-        T = BTData{};
-    };
     // residual of a factorisation; where one that fails is no loss (`spare`),
     // 1 when it does not fit
     auto attempt = [&](bool nested, bool spare) {
@@ -952,13 +954,13 @@ void build_bt(eh_ctx* c, Block& B, const c128* st, const Widths& w, const Dims& 
         }
     };
     const double enough = c->o.mg_precision == 32 ? kBtCheck : kDenseCheck;
-    double rel = attempt(true, true);
+    double rel = nested ? attempt(true, true) : 1.0;
     if (!(rel < enough)) {
         const bool usable = rel < kBtCheck;
-        drop();
+        drop_bt(c, B);
         const double one = attempt(false, usable);
         if (usable && !(one < rel)) {
-            drop();
+            drop_bt(c, B);
             rel = attempt(true, false);
         } else {
             rel = one;
@@ -2743,7 +2745,23 @@ eh_status eh_create(eh_ctx** out, int dim, const int64_t* n, const double* h, co
             build_hierarchy(c, B, st0, cst[b], cw[b]);
         }
         if (c->use_bt) {
-            for (int b = 0; b <= dim; ++b) build_bt(c, c->blk[b], cst[b], cw[b], c->blk[b].lev[o.levels - 1].d);
+            auto factor = [&](int b, bool nested) {
+                build_bt(c, c->blk[b], cst[b], cw[b], c->blk[b].lev[o.levels - 1].d, nested);
+            };
+            try {
+                for (int b = 0; b <= dim; ++b) factor(b, true);
+            } catch (const HipError& e) {
+                // a block's smaller factors did not fit beside the earlier
+                // blocks' larger ones: the smaller ones for every block
+                if (e.e != hipErrorOutOfMemory) throw;
+                (void)hipGetLastError();
+                for (int b = 0; b <= dim; ++b) drop_bt(c, c->blk[b]);
+                for (int b = 0; b <= dim; ++b) {
+                    factor(b, false);
+                    c->release(cst[b]);
+                    cst[b] = nullptr;
+                }
+            }
         } else {
             build_dense(c, cst, cw);
         }

@@ -136,3 +136,34 @@ done(more=more, steady=steady, peak=peak, steady2=steady2, peak2=peak2, diff=wor
 """)
     assert r["peak"] > r["more"] >= r["peak2"]
     assert r["steady"] == r["steady2"] and r["diff"] == 0.0
+
+
+def test_eliminations_that_fit_only_in_the_smaller_order(run):
+    """Removing every other group stores five matrices per group here, the
+    groups one after the other three, and needs every group's blocks at
+    once.  Whatever room there is beyond the smaller factors of all blocks
+    (and a tenth), the context is made -- also where the first blocks' larger
+    factors fit and would leave too little for the last one's smaller ones --
+    and its solves stay as accurate."""
+    r = run("""
+n = (15, 6, 120)                                   # groups: planes of 90 to 105 points
+s, (steady, peak, _) = context(n, coarse_solver="bt")
+ref = blocks(s)
+dims = [tuple(int(v) for v in s.block_dims(b, 0)) for b in range(4)]
+s.close()
+one = sum(16 * 3 * (m[0] * m[1]) ** 2 * m[2] for m in dims)
+out = []
+for more in (1.1, 1.2, 1.25, 1.33, 1.4, 1.5, 2.0):
+    try:
+        t, (steady2, peak2, _) = context(n, int(more * one), coarse_solver="bt")
+    except EhelmError as e:
+        out.append((more, str(e), 0, 1.0))
+        continue
+    out.append((more, "", peak2, worst(blocks(t), ref)))
+    t.close()
+done(one=one, steady=steady, peak=peak, out=out)
+""")
+    print(r)
+    assert r["peak"] > 2.0 * r["one"]
+    for more, err, peak, diff in r["out"]:
+        assert not err and peak <= more * r["one"] and diff <= 1e-11, more
