@@ -2563,6 +2563,8 @@ eh_status from_hip(eh_ctx* c, const HipError& e) {
     std::string m = std::string("HIP error ") + hipGetErrorString(e.e) + " in " + e.where;
     if (c) { c->err = m; c->broken = true; }
     else g_create_error = m;
+    // reported here: the next launch's check, maybe another context's, is not to find it
+    (void)hipGetLastError();
     return e.e == hipErrorOutOfMemory ? EH_ERR_OOM : EH_ERR_HIP;
 }
 

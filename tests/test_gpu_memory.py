@@ -167,3 +167,25 @@ done(one=one, steady=steady, peak=peak, out=out)
     assert r["peak"] > 2.0 * r["one"]
     for more, err, peak, diff in r["out"]:
         assert not err and peak <= more * r["one"] and diff <= 1e-11, more
+
+
+def test_refused_context_leaves_others_alone(run):
+    """A creation refused for memory is EH_ERR_OOM, and neither a context
+    that exists nor the next creation meets its error."""
+    r = run("""
+s, (steady, _, _) = context((40, 32), coarse_solver="dense")
+ref = blocks(s)
+status = None
+try:
+    context((40, 32), steady // 2, coarse_solver="dense")
+except EhelmError as e:
+    status = e.status
+after = worst(blocks(s), ref)
+try:
+    context((40, 32), 1000, coarse_solver="bt")
+except EhelmError:
+    pass
+t, _ = context((40, 32), coarse_solver="dense")
+done(status=status, after=after, new=worst(blocks(t), ref), live=shim.shim_live())
+""")
+    assert r["status"] == -3 and r["after"] == 0.0 and r["new"] == 0.0
