@@ -189,3 +189,14 @@ t, _ = context((40, 32), coarse_solver="dense")
 done(status=status, after=after, new=worst(blocks(t), ref), live=shim.shim_live())
 """)
     assert r["status"] == -3 and r["after"] == 0.0 and r["new"] == 0.0
+
+
+def test_long_chain_in_few_allocations(run):
+    """6000 groups of 4 points: their matrices do not take an allocation
+    each (three per group and more)."""
+    r = run("""
+s, (steady, peak, calls) = context((6000, 4), coarse_solver="bt")
+done(calls=calls, steady=steady, peak=peak)
+""")
+    print(r)
+    assert r["calls"] < 1000
