@@ -444,20 +444,30 @@ struct GJScratch {
     }
 };
 
+// A batched launch over n descriptors, one per blockIdx.z, in parts within the
+// 65536 workgroups that the device states for that axis: the first level of a
+// long chain has three blocks per group.
+template <class D, class F>
+void batched(const D* d, size_t n, F launch) {
+    constexpr size_t kMaxZ = 1 << 15;
+    for (size_t i = 0; i < n; i += kMaxZ) launch(d + i, (unsigned)std::min(kMaxZ, n - i));
+    HIPCHK(hipGetLastError());
+}
+
 // In-place inverses of several padded matrices, side by side.
 void gj_invert(GJScratch& g, const std::vector<GJMat>& mats) {
     if (mats.empty()) return;
-    const GJMat* dm = g.upload(mats);
     int bp = 0;
     for (const GJMat& m : mats) bp = std::max(bp, m.bp);
-    const unsigned t64 = (unsigned)((bp + 63) / 64), nz = (unsigned)mats.size();
-    for (int K = 0; K < bp / GJB; ++K) {
-        hipLaunchKernelGGL(k_gj_diag, dim3(1, 1, nz), dim3(256), 0, 0, dm, K, g.bad);
-        hipLaunchKernelGGL(k_gj_rowpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
-        hipLaunchKernelGGL(k_gj_update, dim3(t64, t64, nz), dim3(256), 0, 0, dm, K);
-        hipLaunchKernelGGL(k_gj_colpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
-    }
-    HIPCHK(hipGetLastError());
+    const unsigned t64 = (unsigned)((bp + 63) / 64);
+    batched(g.upload(mats), mats.size(), [&](const GJMat* dm, unsigned nz) {
+        for (int K = 0; K < bp / GJB; ++K) {
+            hipLaunchKernelGGL(k_gj_diag, dim3(1, 1, nz), dim3(256), 0, 0, dm, K, g.bad);
+            hipLaunchKernelGGL(k_gj_rowpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
+            hipLaunchKernelGGL(k_gj_update, dim3(t64, t64, nz), dim3(256), 0, 0, dm, K);
+            hipLaunchKernelGGL(k_gj_colpanel, dim3(t64, 1, nz), dim3(256), 0, 0, dm, K);
+        }
+    });
 }
 
 inline int pad_gj(int64_t b) { return (int)((b + GJB - 1) / GJB * GJB); }
@@ -767,24 +777,27 @@ double bt_factor(eh_ctx* c, Block& B, const c128* st, const BTPart& pt, bool nes
         };
         auto run_expand = [&]() {
             if (ex.empty()) return;
-            hipLaunchKernelGGL(k_bt_couple_dense, dim3((unsigned)((bp + 255) / 256), (unsigned)bp, (unsigned)ex.size()),
-                               dim3(256), 0, 0, pt, st, g.upload(ex), bp);
-            HIPCHK(hipGetLastError());
+            batched(g.upload(ex), ex.size(), [&](const BTBlock* d, unsigned nz) {
+                hipLaunchKernelGGL(k_bt_couple_dense, dim3((unsigned)((bp + 255) / 256), (unsigned)bp, nz), dim3(256), 0,
+                                   0, pt, st, d, bp);
+            });
             ex.clear();
         };
         auto run_products = [&](const std::vector<GJProd>& pr) {
             if (pr.empty()) return;
             const unsigned t64 = (unsigned)((bp + 63) / 64);
-            hipLaunchKernelGGL(k_gj_product, dim3(t64, t64, (unsigned)pr.size()), dim3(256), 0, 0, g.upload(pr), bp);
-            HIPCHK(hipGetLastError());
+            batched(g.upload(pr), pr.size(), [&](const GJProd* d, unsigned nz) {
+                hipLaunchKernelGGL(k_gj_product, dim3(t64, t64, nz), dim3(256), 0, 0, d, bp);
+            });
         };
         auto run_copies = [&](const std::vector<BTCopy>& cp) {
             int rows = 1, cols = 1;
             for (const BTCopy& k : cp) { rows = std::max(rows, k.rows); cols = std::max(cols, k.cols); }
             if (cp.empty()) return;
-            hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((cols + 255) / 256), (unsigned)rows, (unsigned)cp.size()),
-                               dim3(256), 0, 0, g.upload(cp));
-            HIPCHK(hipGetLastError());
+            batched(g.upload(cp), cp.size(), [&](const BTCopy* d, unsigned nz) {
+                hipLaunchKernelGGL(k_bt_store_inv, dim3((unsigned)((cols + 255) / 256), (unsigned)rows, nz), dim3(256), 0,
+                                   0, d);
+            });
         };
         for (const Plan& P : plan) {
             for (const Elim& e : P.el) {

@@ -318,3 +318,16 @@ def test_groups_eliminated_one_after_the_other(n, k, delta, limit):
         say(f"  residual {res:.1e}")
         assert res <= limit, q
     assert np.array_equal(e1, e[1])
+
+
+def test_chain_beyond_one_launch():
+    """24 000 groups of two points: the first level's 72 000 blocks and its
+    inverses take several launches; FP64 against splu, 1e-10 as above."""
+    n, alpha = (24000, 2), 0.3
+    say("long chain", n)
+    gpu, s = make(n, seed=13, levels=1, alpha=alpha, mg_precision=64, coarse_solver="bt")
+    for b in range(3):
+        X = block_op(s, b, alpha).tocsc()
+        f = crand(X.shape[0], 60 + b)
+        assert rel(gpu.block_cycle(b, to_dev(f)).cpu().numpy(), spla.splu(X).solve(f)) <= 1e-10, b
+    gpu.close()
