@@ -13,15 +13,13 @@ namespace eh {
 constexpr int KRY_THREADS = 256;
 constexpr int KRY_MAXM = 32;   // columns handled by one pass
 
-// MODE 0: partial[i] = sum_p conj(V_i[p]) w[p]                   (i < m)
-// MODE 1: wout <- w - sum_i c_i V_i;  partial[i] = sum conj(V_i) wout   (update + dot)
 // MODE 2: wout <- w - sum_i c_i V_i;  partial[0] = sum |wout|^2         (update + norm)
 // MODE 3: partial[0] = sum |w|^2
 // MODE 4: partial[i] = sum conj(V_i) w and partial[m + i] = sum conj(V_i) V_{m-1}
 //         (projections of w and the newest column of the Gram matrix V^H V)
 // grid: (nblk, nrhs); block b owns the E * 256 entries starting at
 // b * E * 256 (each thread E of them, 256 apart: coalesced).
-// partial layout [r][i][blk] (i < m, or 1 for norms); coef layout [r][i].
+// partial layout [r][i][blk] (i < 2 m, or 1 for norms); coef layout [r][i].
 // E entries per thread: KRY_E, or 1 on vectors so short that KRY_E would
 // leave most compute units idle (then the update's columns are loaded four
 // at a time instead).  The choice depends on n alone (kry_entries).
@@ -47,7 +45,7 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
         const int64_t p = base + e * KRY_THREADS;
         wv[e] = p < n ? wr[p] : mk(0.0, 0.0);
     }
-    if (MODE == 1 || MODE == 2) {
+    if (MODE == 2) {
         constexpr int UT = E == 1 ? 4 : 1;         // columns in flight
         int t = 0;
         if (UT > 1) {
@@ -112,26 +110,6 @@ k_gs(int64_t n, int m, int nrhs, const c128* __restrict__ V, const c128* w,
                 lre[wave][t] = ar; lim[wave][t] = ai;
                 lre[wave][m + t] = gr; lim[wave][m + t] = gi;
             }
-        }
-    } else if (MODE == 0 || MODE == 1) {
-        mm = m;
-        for (int t = 0; t < m; ++t) {
-            const c128* Vt = V + ((int64_t)t * nrhs + r) * n;
-            double ar = 0.0, ai = 0.0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int64_t p = base + e * KRY_THREADS;
-                if (p < n) {
-                    const c128 v = Vt[p];
-                    ar += v.re * wv[e].re + v.im * wv[e].im;
-                    ai += v.re * wv[e].im - v.im * wv[e].re;
-                }
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                ar += __shfl_xor(ar, off, 64);
-                ai += __shfl_xor(ai, off, 64);
-            }
-            if (lane == 0) { lre[wave][t] = ar; lim[wave][t] = ai; }
         }
     } else {
         double a = 0.0;

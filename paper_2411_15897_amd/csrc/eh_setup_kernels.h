@@ -1,6 +1,7 @@
 // Setup kernels (FP64, run once per context):
 //  k_galerkin_medium / _shear / _pressure: the medium's cell arrays and the
-//                   fine-level operators, one cell or face per thread;
+//                   fine-level operators, what the Galerkin products start
+//                   from, one cell or face per thread;
 //  k_galerkin       coarse stencil of X_H = R X_h P (eq. galerkin) in stencil
 //                   form, one thread per coarse point;
 //  k_dense_from_stencil / Gauss-Jordan kernels: explicit inverse of the

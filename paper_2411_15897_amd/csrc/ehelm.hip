@@ -626,7 +626,10 @@ void bt_solve(eh_ctx* c, const int* kinds, int ns, const void* const* f, const i
               const int64_t* vo, int nrhs);
 
 // Points left to the dense matrix that ends the elimination: one launch over
-// n^2 entries instead of two launches per further level.
+// n^2 entries instead of two launches per further level.  Preconditioner with
+// one-level blocks, us at 768 / 1536 / 3072: 128 x 128 179 / 168 / 175, 400 x 30
+// 117 / 109 / 142, 24 x 20 x 18 224 / 207 / 209 (16 right-hand sides 955 / 911 /
+// 996).
 constexpr int64_t kBtTail = 1536;
 // Bytes of a block's first-level matrices worth the two launches of about 4 us
 // that spare them: at 40 MB (200 x 64 points, groups of 128) a whole W-cycle
@@ -2110,7 +2113,7 @@ template <int MODE>
 int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w, const c128* coef, c128* out,
             c128* wout = nullptr, int fold = 0) {
     const int nblk = kry_blocks(n);
-    const double vecs = (MODE == 0 || MODE == 4) ? m + 1 : (MODE == 3 ? 1 : m + 2);
+    const double vecs = MODE == 4 ? m + 1 : (MODE == 3 ? 1 : m + 2);
     Timed tm(c, KC_KRYLOV, vecs * nrhs * n * sizeof(c128));
     if (kry_entries(n) == 1)
         hipLaunchKernelGGL((k_gs<MODE, 1>), dim3(nblk, nrhs), dim3(KRY_THREADS), 0, c->s, n, m, nrhs, V, w, coef,
@@ -2120,7 +2123,7 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
                            c->partial, wout);
     HIPCHK(hipGetLastError());
     if (nblk <= fold) return nblk;
-    const int mm = (MODE == 0 || MODE == 1) ? m : (MODE == 4 ? 2 * m : 1);
+    const int mm = MODE == 4 ? 2 * m : 1;
     hipLaunchKernelGGL(k_reduce_partials, dim3(mm, nrhs), dim3(256), 0, c->s, nblk, mm, nrhs, c->partial, out);
     HIPCHK(hipGetLastError());
     return 0;
@@ -2132,8 +2135,12 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
 // One source, us per FGMRES step, tiles / k_gs: 128^2 99.8 / 96.6, 256^2 131.2 /
 // 133.4, 1024^2 449 / 446, 2048^2 1354 / 1351.
 constexpr int64_t kTileSum = 3 << 16;
-// A batch of kAgainBytes per basis vector, out of the 256 MB cache with the
-// vectors around it, forms w again.
+// A batch of four or more, of kAgainBytes per basis vector (out of the 256 MB
+// cache with the vectors around it), forms w again.  us per FGMRES(4) step, w read /
+// formed again: 2048^2 x 8 6160 / 5840, x 4 3450 / 3290, 1024^2 x 4 (201 MB) 1016 /
+// 987, 512^2 x 11 (139 MB) 723 / 698, 256^2 x 64 (202 MB) 946 / 918; below the line
+// 512^2 x 8 (101 MB) 572; one source of 2048^2 loses (1373 / 1377), two and three
+// would gain (2087 / 2031, 2771 / 2671).
 constexpr double kAgainBytes = 128.0 * 1024 * 1024;
 
 // Flexible GMRES(m) with right preconditioning, x_0 = 0.  Every Arnoldi
