@@ -189,8 +189,7 @@ __device__ __forceinline__ double gs_update(const DotArgs& da, int r, int64_t vs
     }
     double a = 0.0;
 #pragma unroll
-    for (int e = 0; e < NE; ++e)
-        if (has[e]) a = fmat(yk[e].im, yk[e].im, fmat(yk[e].re, yk[e].re, a));
+    for (int e = 0; e < NE; ++e) a += has[e] ? fmat(yk[e].im, yk[e].im, yk[e].re * yk[e].re) : 0.0;
     return a;
 }
 

@@ -2132,8 +2132,9 @@ int gs_pass(eh_ctx* c, int64_t n, int m, int nrhs, const c128* V, const c128* w,
 // 2D vectors of kTileSum entries or more (256^2 cells; 325 operator tiles) take
 // the second Gram-Schmidt pass by operator tiles (apply_H_update), whose sums
 // do not depend on how a batch forms w; shorter ones by k_gs, w always stored.
-// One source, us per FGMRES step, tiles / k_gs: 128^2 99.8 / 96.6, 256^2 131.2 /
-// 133.4, 1024^2 449 / 446, 2048^2 1354 / 1351.
+// us per FGMRES(4) step, tiles / k_gs: one source 128^2 (restart 20) 99.8 / 96.6,
+// 256^2 131.2 / 133.4, 512^2 203 / 201, 1024^2 449 / 446, 2048^2 1378 / 1369, three
+// 2777 / 2754 (a tile in 33 owns one column of points).
 constexpr int64_t kTileSum = 3 << 16;
 // A batch of four or more, of kAgainBytes per basis vector (out of the 256 MB
 // cache with the vectors around it), forms w again.  us per FGMRES(4) step, w read /
